@@ -1686,14 +1686,6 @@ __global__ __launch_bounds__(kWgThreads) void combine_kernel(KernelArgs a)
     }
 }
 
-__global__ void clear_header_kernel(WsHeader *hdr)
-{
-    uint32_t *p = (uint32_t *)hdr;
-    for (int i = threadIdx.x + blockIdx.x * blockDim.x; i < (int)(sizeof(WsHeader) / 4);
-         i += blockDim.x * gridDim.x)
-        p[i] = 0u;
-}
-
 // ------------------------------------------------------------------------------------------
 // Host-side launchers.
 // ------------------------------------------------------------------------------------------
@@ -1746,7 +1738,7 @@ static hipError_t launch_variant(int which, const KernelArgs &a, hipStream_t str
 }
 
 template <int DT, int D>
-static hipError_t launch_layout(int which, const KernelArgs &a, int layout, hipStream_t stream)
+hipError_t launch_layout(int which, const KernelArgs &a, int layout, hipStream_t stream)
 {
     switch (layout) {
     case kLayoutContiguous: return launch_variant<DT, D, kLayoutContiguous>(which, a, stream);
@@ -1754,6 +1746,26 @@ static hipError_t launch_layout(int which, const KernelArgs &a, int layout, hipS
     case kLayoutPagedAny: return launch_variant<DT, D, kLayoutPagedAny>(which, a, stream);
     default: return hipErrorInvalidValue;
     }
+}
+
+// This file is compiled once per (16-bit type, head_dim), which holds the kernels of that pair, and
+// once without, which holds the rest: the compilations run side by side.
+#if defined(POD_INSTANCE_DT)
+template hipError_t launch_layout<POD_INSTANCE_DT, POD_INSTANCE_D>(int, const KernelArgs &, int, hipStream_t);
+#else
+extern template hipError_t launch_layout<0, 64>(int, const KernelArgs &, int, hipStream_t);
+extern template hipError_t launch_layout<0, 128>(int, const KernelArgs &, int, hipStream_t);
+extern template hipError_t launch_layout<0, 256>(int, const KernelArgs &, int, hipStream_t);
+extern template hipError_t launch_layout<1, 64>(int, const KernelArgs &, int, hipStream_t);
+extern template hipError_t launch_layout<1, 128>(int, const KernelArgs &, int, hipStream_t);
+extern template hipError_t launch_layout<1, 256>(int, const KernelArgs &, int, hipStream_t);
+
+__global__ void clear_header_kernel(WsHeader *hdr)
+{
+    uint32_t *p = (uint32_t *)hdr;
+    for (int i = threadIdx.x + blockIdx.x * blockDim.x; i < (int)(sizeof(WsHeader) / 4);
+         i += blockDim.x * gridDim.x)
+        p[i] = 0u;
 }
 
 hipError_t launch(int which, const KernelArgs &a, int dtype, int head_dim, bool paged, hipStream_t stream)
@@ -1802,5 +1814,6 @@ hipError_t static_scratch(void **ptr)
     *ptr = per_device[dev];
     return hipSuccess;
 }
+#endif  // POD_INSTANCE_DT
 
 }  // namespace pod
