@@ -53,7 +53,8 @@ typedef enum { POD_F16 = 0, POD_BF16 = 1 } pod_dtype;
 
 /* How pod_attn_forward schedules the two operations. */
 typedef enum {
-    POD_MODE_FUSED = 0,         /* one launch, roles bound per workgroup at run time (Section 4.1) */
+    POD_MODE_FUSED = 0,         /* one launch, roles bound per workgroup at run time (Section 4.1);
+                                   a batch with one operation runs that operation's own kernel      */
     POD_MODE_SERIAL = 1,        /* prefill kernel, then decode kernel, one stream (Section 3.1)    */
     POD_MODE_STREAMS = 2,       /* the same two kernels on two streams, joined (Section 3.1)       */
     POD_MODE_PREFILL_ONLY = 3,  /* only the prefill rows of `out` are written                      */
@@ -296,13 +297,14 @@ int32_t pod_attn_role_for_ticket(int32_t ticket, int32_t prefill_ratio, int32_t 
  *   unit_of_wg[w]  hardware unit id (xcc << 6 | se << 4 | cu, < 1024) workgroup w lands on
  *   order[k]       actor whose next step runs at time k.  Actor 4w is workgroup w's leader, whose
  *                  steps are: take the unit's ticket and pick the first operation; as a prefill
- *                  worker, one claim on the prefill queue it is at (its XCD's queue first, then the
- *                  others; a used-up queue moves it on, after all eight the operation is done); as
+ *                  worker, one claim on the prefill queue it is at (its XCD's queue first), or, after that
+ *                  queue was found used up, one look at all eight (the nearest one with work is
+ *                  next; if none has any the operation is done); as
  *                  a decode worker, take a seat (workers beyond the plan's seats skip the
  *                  operation).  Actors 4w .. 4w+3 are its wavefronts while it is a decode worker:
  *                  the fixed first unit 4 * seat + v of the first seats without a claim, then one
- *                  claim per step on the decode queue the wavefront is at (same walk over the eight
- *                  queues).  A workgroup switches operation once and then ends.  Entries naming an
+ *                  claim per step on the decode queue the wavefront is at (its XCD's queue first,
+ *                  then the others; after all eight it is done).  A workgroup switches operation once and then ends.  Entries naming an
  *                  actor that has nothing to do at that moment are skipped; when `order` is used
  *                  up, all unfinished actors run on in turn until the launch has drained.
  * Outputs (host, each may be NULL): first_role[w] 0 prefill / 1 decode; seat_of_wg[w] (untouched if

@@ -712,6 +712,40 @@ template <int D, int LAYOUT> struct DecodeRing {
 // move it to vector registers).  Emits no instruction.
 __device__ __forceinline__ void lane_test_done() { __builtin_amdgcn_wave_barrier(); }
 
+// A prefill worker whose queue has run out looks at all eight counters at once, with plain loads,
+// and claims only from a queue that still has work: the nearest one from `q` on, going round; -1 if
+// none has.  (A claim on each of the other seven sent 8 atomics per worker to counters that no longer
+// mattered; while the counters shared a line, which serves one atomic per 11 ns, that was the last
+// 10-30 us of a launch.)  The counters only grow, so a queue seen used up stays so; one seen open
+// may run out before the claim arrives, and then the claim fails and the counters are looked at again.
+// (Decode wavefronts do not look: in the middle of their stream a claim on the next queue costs
+// less than the look, 641 against 659 us on 8192 units.)
+__device__ __forceinline__ int prefill_open_queue(const KernelArgs &a, int q)
+{
+    uint32_t open = 0;
+#pragma unroll
+    for (int i = 0; i < kXcdQueues; ++i) {
+        const uint32_t next = __hip_atomic_load(&a.hdr->next_pitem_xcd[i][0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        open |= (next < (uint32_t)(a.pq_begin[i + 1] - a.pq_begin[i]) ? 1u : 0u) << i;
+    }
+    const uint32_t turned = (open >> q) | (open << (kXcdQueues - q));
+    return open == 0u ? -1 : (q + __builtin_ctz(turned)) & (kXcdQueues - 1);
+}
+
+// One claim from decode queue cq.  It is waited for on the spot and is one opaque instruction pair
+// (see "claims" in the decode worker).
+__device__ __forceinline__ int decode_claim(const KernelArgs &a, int cq, int lane)
+{
+    uint32_t v = 0;
+    if (lane == 0) {
+        uint32_t *ctr = &a.hdr->next_dunit_xcd[cq][0];
+        asm volatile("global_atomic_add %0, %1, %2, off sc0\n\ts_waitcnt vmcnt(0)"
+                     : "=&v"(v) : "v"(ctr), "v"(1u) : "memory");
+    }
+    lane_test_done();
+    return (int)__builtin_amdgcn_readfirstlane(v);
+}
+
 template <int N_OPS> __device__ __forceinline__ void wait_loads_but()
 {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N_OPS) : "memory");
@@ -774,16 +808,7 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
     // ahead of its use is part of every turn of the ring: a turn that wants no unit adds zero to
     // a word of its own workgroup instead.
     int cq = __builtin_amdgcn_readfirstlane(xcd) & (kXcdQueues - 1), tried = 0;
-    auto claim_now = [&]() __attribute__((always_inline)) -> int {
-        uint32_t v = 0;
-        if (lane == 0) {
-            uint32_t *ctr = &a.hdr->next_dunit_xcd[cq][0];
-            asm volatile("global_atomic_add %0, %1, %2, off sc0\n\ts_waitcnt vmcnt(0)"
-                         : "=&v"(v) : "v"(ctr), "v"(1u) : "memory");
-        }
-        lane_test_done();
-        return (int)__builtin_amdgcn_readfirstlane(v);
-    };
+    auto claim_now = [&]() __attribute__((always_inline)) -> int { return decode_claim(a, cq, lane); };
     // Turns a claimed counter value into a unit index.  When the queue is used up it claims from
     // the next queues (and waits for those claims); -1 when no unit is left anywhere.
     auto claim_resolve = [&](int k) __attribute__((always_inline)) -> int {
@@ -1125,14 +1150,16 @@ template <int D> struct FusedLds {
 };
 
 // ------------------------------------------------------------------------------------------
-// Stand-alone kernels: the in-house serial and two-stream baselines (Section 3.1).
+// Stand-alone kernels: the in-house serial and two-stream baselines (Section 3.1), and what a
+// batch with one operation runs.
 // ------------------------------------------------------------------------------------------
 template <int DT, int D, int LAYOUT>
 __global__ __launch_bounds__(kWgThreads, 2) void prefill_kernel(KernelArgs a)
 {
     __shared__ __attribute__((aligned(16))) unsigned char smem[PrefillLds<D>::kBytes];
-    const uint64_t t0 = a.trace ? wall_clock64() : 0;
+    const uint64_t t0 = a.trace || a.evlog ? wall_clock64() : 0;
     prefill_item_run<DT, D, LAYOUT>(a, a.pitems_by_wg[blockIdx.x], smem);
+    if (a.evlog && threadIdx.x == 0) log_event(a, kPrefill, a.pitem_of_wg[blockIdx.x], t0);
     if (a.trace && threadIdx.x == 0)
         write_trace(a, blockIdx.x, __smid() & (kCuSlots - 1), kPrefill, 1, 0, t0, wall_clock64());
 }
@@ -1144,20 +1171,19 @@ template <int DT, int D, int LAYOUT>
 __device__ __forceinline__ int prefill_worker_run(const KernelArgs &a, unsigned char *smem, int *slot, int xcd)
 {
     int n_done = 0;
-    int q = xcd & (kXcdQueues - 1), tried = 0;
+    int q = xcd & (kXcdQueues - 1);
     for (;;) {
         __syncthreads();                            // previous item done with LDS and with *slot
         if (threadIdx.x == 0) {
             int item = -1;
-            while (tried < kXcdQueues) {
+            do {
                 const int len = a.pq_begin[q + 1] - a.pq_begin[q];
-                const int k = len > 0 ? (int)atomicAdd(&a.hdr->next_pitem_xcd[q], 1u) : len;
+                const int k = len > 0 ? (int)atomicAdd(&a.hdr->next_pitem_xcd[q][0], 1u) : len;
                 if (k < len) { item = a.pq_begin[q] + k; break; }
-                q = (q + 1) & (kXcdQueues - 1);     // this queue is empty for good: move on
-                ++tried;
-            }
+                q = prefill_open_queue(a, q);       // this queue is empty for good: move on
+            } while (q >= 0);
             slot[0] = item;
-            slot[1] = q | (tried << 8);
+            slot[1] = q;
         }
         __syncthreads();
         // The claimed index is the same for every thread, but it comes out of LDS: say so, and read
@@ -1166,9 +1192,7 @@ __device__ __forceinline__ int prefill_worker_run(const KernelArgs &a, unsigned 
         // stand-alone kernel.  Held in vector registers it cost the tile loop ~15 registers it
         // needs to keep LDS reads ahead of the matrix instructions.
         const int item = __builtin_amdgcn_readfirstlane(slot[0]);
-        const int packed = __builtin_amdgcn_readfirstlane(slot[1]);
-        q = packed & 255;
-        tried = packed >> 8;
+        q = __builtin_amdgcn_readfirstlane(slot[1]);
         if (item < 0) break;
         const uint64_t tb = a.evlog ? wall_clock64() : 0;
         PrefillItem it;
@@ -1189,19 +1213,19 @@ __device__ __forceinline__ void finish_and_reset(WsHeader *hdr, int *flag)
 {
     __syncthreads();
     if (threadIdx.x == 0) {
-        __threadfence();
-        const uint32_t done = atomicAdd(&hdr->done, 1u);
+        // (every claim of this workgroup has returned: their values have been used)
+        const uint32_t done = atomicAdd(&hdr->done[0][0], 1u);
         *flag = (done == gridDim.x - 1) ? 1 : 0;
     }
     __syncthreads();
     if (*flag) {
         for (int i = threadIdx.x; i < kCuSlots; i += kWgThreads) hdr->cu_state[i] = 0u;
         if (threadIdx.x == 0) {
-            hdr->next_item[0] = 0u;
-            hdr->next_item[1] = 0u;
+            hdr->next_id[0][0] = 0u;
+            hdr->next_id[1][0] = 0u;
             for (int q = 0; q < kXcdQueues; ++q) hdr->next_dunit_xcd[q][0] = 0u;
-            hdr->done = 0u;
-            for (int q = 0; q < kXcdQueues; ++q) hdr->next_pitem_xcd[q] = 0u;
+            hdr->done[0][0] = 0u;
+            for (int q = 0; q < kXcdQueues; ++q) hdr->next_pitem_xcd[q][0] = 0u;
         }
     }
 }
@@ -1291,29 +1315,17 @@ __global__ __launch_bounds__(kWgThreads) __attribute__((amdgpu_num_vgpr(kLiteVgp
 
     // ---- unit claims (the protocol of the decode worker: fixed first units, then the queues) ----
     int cq = __builtin_amdgcn_readfirstlane((int)(__smid() >> 6)) & (kXcdQueues - 1), tried = 0;
-    auto claim_now = [&]() __attribute__((always_inline)) -> int {
-        uint32_t v = 0;
-        if (lane == 0) {
-            uint32_t *ctr = &a.hdr->next_dunit_xcd[cq][0];
-            asm volatile("global_atomic_add %0, %1, %2, off sc0\n\ts_waitcnt vmcnt(0)"
-                         : "=&v"(v) : "v"(ctr), "v"(1u) : "memory");
-        }
-        lane_test_done();
-        return (int)__builtin_amdgcn_readfirstlane(v);
-    };
     auto claim_unit = [&]() __attribute__((always_inline)) -> int {
-        if (tried >= kXcdQueues) return -1;
-        int k = claim_now();
-        for (;;) {
+        while (tried < kXcdQueues) {
             const int q0 = dq[cq], q1 = dq[cq + 1];
-            if (k < q1 - q0) return q0 + k;
-            do {
-                cq = (cq + 1) & (kXcdQueues - 1);
-                ++tried;
-            } while (tried < kXcdQueues && dq[cq + 1] == dq[cq]);
-            if (tried >= kXcdQueues) return -1;
-            k = claim_now();
+            if (q1 > q0) {
+                const int k = decode_claim(a, cq, lane);
+                if (k < q1 - q0) return q0 + k;
+            }
+            cq = (cq + 1) & (kXcdQueues - 1);
+            ++tried;
         }
+        return -1;
     };
 
     int n_done = 0;
@@ -1548,7 +1560,7 @@ __global__ __launch_bounds__(kWgThreads, 2) void fused_kernel(KernelArgs a)
     // n_dwgs workgroups, so all seats, and with them all fixed first units, are taken.
     auto take_seat = [&]() {
         __syncthreads();
-        if (threadIdx.x == 0) bind[1] = (int)atomicAdd(&hdr->next_item[kDecode], 1u);
+        if (threadIdx.x == 0) bind[1] = (int)atomicAdd(&hdr->next_id[kDecode][0], 1u);
         __syncthreads();
         const int seat = bind[1];
         return seat;
@@ -1592,7 +1604,7 @@ __global__ __launch_bounds__(kWgThreads, 2) void fused_cta_kernel(KernelArgs a)
         int id = -1;
         for (int attempt = 0; attempt < 2 && id < 0; ++attempt) {
             const uint32_t limit = (uint32_t)(role == kPrefill ? a.n_pitems : a.n_dctas);
-            const uint32_t k = atomicAdd(&hdr->next_item[role], 1u);
+            const uint32_t k = atomicAdd(&hdr->next_id[role][0], 1u);
             if (k < limit) id = (int)k;
             else role ^= 1;                                  // that operation has no work left: the other one
         }

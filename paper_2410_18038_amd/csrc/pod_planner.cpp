@@ -245,17 +245,22 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
         {
             const int n = (int)plan.pitems.size();
             plan.pitems_by_wg.assign((size_t)n, PrefillItem{});
+            plan.pitem_of_wg.assign((size_t)n, 0);
+            auto place = [&](int b, int item) {
+                plan.pitems_by_wg[(size_t)b] = plan.pitems[(size_t)item];
+                plan.pitem_of_wg[(size_t)b] = item;
+            };
             int next[kXcdQueues];
             for (int q = 0; q < kXcdQueues; ++q) next[q] = plan.pq_begin[q];
             std::vector<int> unfilled;
             for (int b = 0; b < n; ++b) {
                 const int q = b % kXcdQueues;
-                if (next[q] < plan.pq_begin[q + 1]) plan.pitems_by_wg[(size_t)b] = plan.pitems[(size_t)next[q]++];
+                if (next[q] < plan.pq_begin[q + 1]) place(b, next[q]++);
                 else unfilled.push_back(b);
             }
             size_t u = 0;
             for (int q = 0; q < kXcdQueues; ++q)
-                while (next[q] < plan.pq_begin[q + 1]) plan.pitems_by_wg[(size_t)unfilled[u++]] = plan.pitems[(size_t)next[q]++];
+                while (next[q] < plan.pq_begin[q + 1]) place(unfilled[u++], next[q]++);
         }
     }
 
@@ -397,6 +402,7 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
     size_t off = align256(sizeof(WsHeader));
     plan.off_pitems = off;   off = align256(off + plan.pitems.size() * sizeof(PrefillItem));
     plan.off_pitems_by_wg = off; off = align256(off + plan.pitems_by_wg.size() * sizeof(PrefillItem));
+    plan.off_pitem_of_wg = off; off = align256(off + plan.pitem_of_wg.size() * sizeof(int32_t));
     plan.off_dunits = off;   off = align256(off + plan.dunits.size() * sizeof(DecodeUnit));
     plan.off_centries = off; off = align256(off + plan.centries.size() * sizeof(CombineEntry));
     plan.off_crows = off;    off = align256(off + plan.crows.size() * sizeof(int32_t));

@@ -22,6 +22,7 @@ struct Plan {
     // The same items in the order the stand-alone prefill kernels take them by workgroup index: the
     // hardware deals workgroups to the XCDs round-robin, so workgroup b gets an item of queue b % 8.
     std::vector<PrefillItem> pitems_by_wg;
+    std::vector<int32_t> pitem_of_wg;       // index in pitems of each of them
     std::vector<DecodeUnit> dunits;
     std::vector<CombineEntry> centries;
     std::vector<int32_t> crows;             // (entry, row) pairs, prefill entries first
@@ -37,7 +38,7 @@ struct Plan {
     int n_dwgs = 0;                         // decode workers: workgroups of the stand-alone decode kernel, decode seats of the fused one
     int fused_grid = 0;                     // workgroups of the fused kernel
     // byte offsets inside the workspace (each 256-byte aligned)
-    size_t off_pitems = 0, off_pitems_by_wg = 0, off_dunits = 0, off_centries = 0, off_crows = 0, off_dq = 0, off_part_o = 0, off_part_ml = 0;
+    size_t off_pitems = 0, off_pitems_by_wg = 0, off_pitem_of_wg = 0, off_dunits = 0, off_centries = 0, off_crows = 0, off_dq = 0, off_part_o = 0, off_part_ml = 0;
     size_t ws_bytes = 0;
     // events of the two-kernel modes (fork, two joins), created on first use
     void *events[3] = {nullptr, nullptr, nullptr};

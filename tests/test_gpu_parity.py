@@ -262,6 +262,25 @@ def test_event_log_holds_every_item_and_unit_once():
     attn.close()
 
 
+@pytest.mark.parametrize("prefill,decode", [([(300, 900), (1, 1), (129, 200)], []), ([], [500] * 40 + [33, 1])])
+def test_batches_with_one_operation(prefill, decode):
+    """A batch with one operation runs that operation's own kernel in the fused mode: results, the
+    event log (every work id once) and the counters (a second launch gives the same) hold there too."""
+    batch = wl.make_batch("one-op", prefill=prefill, decode_kv_lens=decode, n_q_heads=8, n_kv_heads=2,
+                          head_dim=128, dtype=wl.BF16, seed=101, block_size=16, poison=float("nan"))
+    check(batch)
+    dev_batch = batch.to("cuda:0")
+    attn = pod.HybridAttention(dev_batch, decode_chunk=128)
+    plain = attn.forward(dev_batch).clone()
+    attn.enable_event_log()
+    logged = attn.forward(dev_batch)
+    ev = attn.read_event_log()
+    assert torch.equal(plain.view(torch.int16), logged.view(torch.int16))
+    for kind, n in ((0, attn.info.n_prefill_items), (1, attn.info.n_decode_units)):
+        assert np.sort(ev["item"][ev["kind"] == kind]).tolist() == list(range(n))
+    attn.close()
+
+
 def _sample_rows(batch, n_p, n_d, seed):
     rng = np.random.Generator(np.random.PCG64(seed))
     npr, nd = batch.n_prefill_rows, batch.n_decode
