@@ -159,9 +159,13 @@ __device__ __forceinline__ void write_trace(const KernelArgs &a, int slot, int c
 // still safe with extra stores in flight: loads complete in order among themselves, so by the
 // time all but the newest N operations have completed, the oldest load is among the completed.
 // Nothing in these kernels reads the stored data back, and a kernel's end completes its stores.
+// The 16-byte form writes through to memory (sc1).  Left in L2, a result is evicted whenever the K/V stream
+// pushes it out, a line at a time, and each such write turns a memory channel around between reads:
+// 20280 units of 512 keys (41 MB of partial rows beside 5 GB of K/V) took 852 us, 782 with their stores left
+// out, and take 816 with whole rows written through at once; units of 2048 keys 797 -> 784.
 __device__ __forceinline__ void store16_untracked(void *p, u32x4 v)
 {
-    asm volatile("global_store_dwordx4 %0, %1, off" ::"v"(p), "v"(v) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory");
 }
 __device__ __forceinline__ void store8_untracked(void *p, u32x2 v)
 {
@@ -1024,31 +1028,47 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
         }
         wave_lds_sync();                           // all reads issued before the next step overwrites
     };
-    // o[mb][r] is channel mb*16 + 4*b4 + r of query column n16.
+    // A finished unit's rows go out as whole lines: o[mb][r] is channel mb*16 + 4*b4 + r of query column
+    // n16, so a store from the accumulators would send 64 bytes to each of `group` rows, D / 16 times
+    // over, with 4 * group lanes active.  The rows pass through the wavefront's K/V area instead (free
+    // between two steps) and leave with all lanes storing consecutive 16-byte pieces.
+    static_assert(QC * D * 4 <= L::kKBytes + L::kVBytes, "a unit's rows fit the K/V area");
     auto finish_unit = [&](const Desc &d) __attribute__((always_inline)) {
         const float l_tot = sum_across_32(sum_across_16(l_run));
-        if (col_ok) {
-        if (d.prow0 < 0) {
+        const bool whole = d.prow0 < 0;
+        char *dst;
+        int n_pieces;                              // of 16 bytes, over all rows
+        if (whole) {
             const float inv = 1.f / l_tot;
-            elem *op = (elem *)a.out +
-                ((int64_t)(a.n_prefill_rows + d.q_start) * a.n_q_heads + d.kv_head * group + n16) * D;
+            if (col_ok) {
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) {
-                typename N::v4 w;
+                for (int mb = 0; mb < MB; ++mb) {
+                    typename N::v4 w;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) w[e] = (elem)(o[mb][e] * inv);
-                store8_untracked(op + mb * 16 + 4 * b4, __builtin_bit_cast(u32x2, w));
+                    for (int e = 0; e < 4; ++e) w[e] = (elem)(o[mb][e] * inv);
+                    *(POD_LDS u32x2 *)(lds_k + (n16 * D + mb * 16 + 4 * b4) * 2) = __builtin_bit_cast(u32x2, w);
+                }
             }
+            lane_test_done();
+            dst = (char *)((elem *)a.out + ((int64_t)(a.n_prefill_rows + d.q_start) * a.n_q_heads + d.kv_head * group) * D);
+            n_pieces = group * (D / 8);
         } else {
-            const int64_t prow = (int64_t)d.prow0 + n16;
-            float *po = a.part_o + prow * D;
+            if (col_ok) {
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) store16_untracked(po + mb * 16 + 4 * b4, __builtin_bit_cast(u32x4, o[mb]));
-            if (b4 == 0)
-                store8_untracked(a.part_ml + prow * 2, u32x2{__float_as_uint(m_run), __float_as_uint(l_tot)});
+                for (int mb = 0; mb < MB; ++mb) *(POD_LDS f32x4 *)(lds_k + (n16 * D + mb * 16 + 4 * b4) * 4) = o[mb];
+                if (b4 == 0)
+                    store8_untracked(a.part_ml + ((int64_t)d.prow0 + n16) * 2, u32x2{__float_as_uint(m_run), __float_as_uint(l_tot)});
+            }
+            lane_test_done();
+            dst = (char *)(a.part_o + (int64_t)d.prow0 * D);
+            n_pieces = group * (D / 4);
         }
+        wave_lds_sync();
+        for (int i = 0; i < n_pieces; i += kWaveSize) {
+            if (i + lane < n_pieces) store16_untracked(dst + (i + lane) * 16, *(const POD_LDS u32x4 *)(lds_k + (i + lane) * 16));
+            lane_test_done();
         }
-        lane_test_done();
+        wave_lds_sync();                           // read before the next step's rows overwrite them
     };
 
     // ---- first unit -------------------------------------------------------------------------------
