@@ -96,6 +96,7 @@ pod::KernelArgs make_args(const pod::Plan &p, const void *prefill_q, const void 
         while ((1 << s) < p.prm.block_size) ++s;
         a.bs_shift = s;
     }
+    if (p.prm.block_size > 1) a.bs_magic = (uint32_t)(((uint64_t(1) << 32) + (uint64_t)p.prm.block_size - 1) / (uint64_t)p.prm.block_size);
     a.n_pitems = (int)p.pitems.size();
     a.n_dunits = (int)p.dunits.size();
     a.n_dwgs = p.n_dwgs;

@@ -115,6 +115,16 @@ __device__ __forceinline__ s16x4 lds_read_tr(const POD_LDS unsigned char *p)
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((POD_LDS s16x4 *)p);
 }
 
+// Block of token t and t's offset inside it, in scalar arithmetic, for block sizes above 1: the
+// product with ceil(2^32 / block_size) is at most one too large for any 31-bit t.
+__device__ __forceinline__ int block_of(const KernelArgs &a, int t, int &offset)
+{
+    int q = (int)(((uint64_t)(uint32_t)t * a.bs_magic) >> 32);
+    offset = t - q * a.block_size;
+    if (offset < 0) { --q; offset += a.block_size; }
+    return q;
+}
+
 // Element offset (head 0, channel 0) of token t of a cache row.  Both cache orders go through the
 // same three strides: elements between the tokens of a head, between the heads of a sequence or
 // block (added by the callers), and between blocks.
@@ -377,6 +387,12 @@ __device__ __forceinline__ void prefill_item_run(const KernelArgs &a, const Pref
                     tb.id[p] = table[t >> a.bs_shift];
                 }
             }
+        } else if constexpr (LAYOUT == kLayoutPagedRows) {
+#pragma unroll
+            for (int p = 0; p < NPASS; ++p) {
+                int off;
+                tb.id[p] = table[block_of(a, min(it.kv_begin + jt * T + p * RPP + wave * RPW, it.kv_end - 1), off)];
+            }
         } else {
 #pragma unroll
             for (int p = 0; p < NPASS; ++p) tb.id[p] = 0;
@@ -401,13 +417,20 @@ __device__ __forceinline__ void prefill_item_run(const KernelArgs &a, const Pref
                 const uint64_t row_off = (uint64_t)((t & (uint32_t)(a.block_size - 1)) * (uint32_t)tok_bytes);
                 tb.b[p] = (int64_t)(blocks16 ? block_off : block_off + row_off);
             }
+        } else if constexpr (LAYOUT == kLayoutPagedRows) {
+#pragma unroll
+            for (int p = 0; p < NPASS; ++p) {
+                int off;
+                block_of(a, j0 + p * RPP + wave * RPW, off);
+                tb.b[p] = ((int64_t)blk.id[p] * a.block_elems + (int64_t)off * token_elems) * 2;
+            }
         } else {
 #pragma unroll
             for (int p = 0; p < NPASS; ++p) tb.b[p] = 0;
         }
         return tb;
     };
-    // Fast path for a full tile of the contiguous layout and of paged layouts with power-of-two blocks.
+    // Fast path for a full tile of every layout whose passes have a uniform base.
     auto issue_fast = [&](const TileBases &tb, int buf, bool is_k) {
         const char *src = is_k ? (const char *)kc : (const char *)vc;
 #pragma unroll
@@ -443,9 +466,13 @@ __device__ __forceinline__ void prefill_item_run(const KernelArgs &a, const Pref
                 int64_t base;
                 if constexpr (LAYOUT == kLayoutContiguous) {
                     base = (int64_t)cache_row * a.kv_seq_stride + (int64_t)t * token_elems;
-                } else {
+                } else if constexpr (LAYOUT == kLayoutPaged16) {
                     const int blk = table[t >> a.bs_shift];
                     base = (int64_t)blk * a.block_elems + (int64_t)(t & (a.block_size - 1)) * token_elems;
+                } else {
+                    int off;
+                    const int blk = table[block_of(a, t, off)];
+                    base = (int64_t)blk * a.block_elems + (int64_t)off * token_elems;
                 }
                 const int lrow = row_base + wr_row;
                 const int rl = min(lrow, last_row) - base_eff;
@@ -875,8 +902,10 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
     Desc hu, cu, nx;                               // units of the head, of the tail, and the one fetched ahead
     int h_t = 0;                                   // first key of the head's next step; >= hu.t1: the head has run out
     int h_addr_t = 0;                              // first key of the step the addresses below point at
-    int64_t h_base = 0;                            // element offset (head 0, channel 0) of that step
-    uint32_t voff[NLD];                            // per-lane byte offsets inside that step
+    // element offset (head 0, channel 0) of that step, or of the rows of each of its loads
+    constexpr int NB = LAYOUT == kLayoutPagedRows ? NLD : 1;
+    int64_t h_base[NB] = {};
+    uint32_t voff[NLD];                            // per-lane byte offsets from those
     const elem *kc = nullptr, *vc = nullptr;
     const POD_CONST int32_t *table = nullptr;
     // State bits (one word: separate flags end up addressed through a common pointer and then
@@ -898,20 +927,27 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
         const int last_row = min(t1 - 1 - t_first, STEP - 1);
 #pragma unroll
         for (int p = 0; p < NLD; ++p) {
-            const int row = min(p * RPI + ld_row, last_row);
+            int row = min(p * RPI + ld_row, last_row);
+            if constexpr (LAYOUT == kLayoutPagedRows) row -= min(p * RPI, last_row & ~(RPI - 1));
             voff[p] = (uint32_t)(row * token_elems + ld_chunk * 8) * 2u;
         }
     };
-    auto base_of = [&](int cache_row, int t) __attribute__((always_inline)) -> int64_t {
+    auto set_base = [&](int cache_row, int t, int t1) __attribute__((always_inline)) {
         if constexpr (LAYOUT == kLayoutContiguous) {
-            return (int64_t)cache_row * a.kv_seq_stride + (int64_t)t * token_elems;
+            h_base[0] = (int64_t)cache_row * a.kv_seq_stride + (int64_t)t * token_elems;
         } else if constexpr (LAYOUT == kLayoutPaged16) {
             // block_size is a power of two >= 16 and t a multiple of 16: a step never straddles blocks
             const int bi = t >> a.bs_shift, off = t & (a.block_size - 1);
             const int blk = table[bi];
-            return (int64_t)blk * a.block_elems + (int64_t)off * token_elems;
-        } else {
-            return 0;
+            h_base[0] = (int64_t)blk * a.block_elems + (int64_t)off * token_elems;
+        } else if constexpr (LAYOUT == kLayoutPagedRows) {
+            // t is a multiple of the rows of a load and so is block_size: a load never straddles blocks
+            const int last_row = min(t1 - 1 - t, STEP - 1);
+            int blk[NLD], off[NLD];
+#pragma unroll
+            for (int p = 0; p < NLD; ++p) blk[p] = table[block_of(a, t + min(p * RPI, last_row & ~(RPI - 1)), off[p])];
+#pragma unroll
+            for (int p = 0; p < NLD; ++p) h_base[p] = (int64_t)blk[p] * a.block_elems + (int64_t)off[p] * token_elems;
         }
     };
     auto set_head = [&](const Desc &d) __attribute__((always_inline)) {
@@ -921,7 +957,7 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
         kc = (const elem *)a.k_cache + d.kv_head * a.head_stride;
         vc = (const elem *)a.v_cache + d.kv_head * a.head_stride;
         table = (const POD_CONST int32_t *)a.block_table + (int64_t)d.cache_row * a.max_blocks_per_seq;
-        h_base = base_of(d.cache_row, d.t0);
+        set_base(d.cache_row, d.t0, d.t1);
         set_voff(d.t0, d.t1);
     };
 
@@ -940,10 +976,10 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
                 sl.v[p] = load16_stream(vc + off);
             }
         } else {
-            const char *kb = (const char *)(kc + h_base);
-            const char *vb = (const char *)(vc + h_base);
 #pragma unroll
             for (int p = 0; p < NLD; ++p) {
+                const char *kb = (const char *)(kc + h_base[NB == 1 ? 0 : p]);
+                const char *vb = (const char *)(vc + h_base[NB == 1 ? 0 : p]);
                 sl.k[p] = load16_stream(kb + voff[p]);
                 sl.v[p] = load16_stream(vb + voff[p]);
             }
@@ -955,8 +991,8 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
             h_t += STEP;
             if (h_t < hu.t1) {
                 h_addr_t = h_t;
-                if constexpr (LAYOUT == kLayoutContiguous) h_base += (int64_t)STEP * token_elems;
-                else h_base = base_of(hu.cache_row, h_t);
+                if constexpr (LAYOUT == kLayoutContiguous) h_base[0] += (int64_t)STEP * token_elems;
+                else set_base(hu.cache_row, h_t, hu.t1);
                 if (h_t + STEP > hu.t1) set_voff(h_t, hu.t1);     // ragged last step
             }
         }
@@ -1742,7 +1778,7 @@ static hipError_t launch_variant(int which, const KernelArgs &a, hipStream_t str
             fused_cta_kernel<DT, D, LAYOUT><<<dim3(a.n_pitems + a.n_dctas), dim3(kWgThreads), 0, stream>>>(a);
         break;
     case kLaunchPrefillHeavy:
-        if constexpr (D == 128 && LAYOUT != kLayoutPagedAny) {
+        if constexpr (D == 128 && (LAYOUT == kLayoutContiguous || LAYOUT == kLayoutPaged16)) {
             if (a.n_pitems > 0)
                 prefill_heavy_kernel<DT, D, LAYOUT><<<dim3(a.n_pitems), dim3(kWgThreads), 0, stream>>>(a);
         } else {
@@ -1750,7 +1786,7 @@ static hipError_t launch_variant(int which, const KernelArgs &a, hipStream_t str
         }
         break;
     case kLaunchDecodeLite:
-        if constexpr (D == 128 && LAYOUT != kLayoutPagedAny) {
+        if constexpr (D == 128 && (LAYOUT == kLayoutContiguous || LAYOUT == kLayoutPaged16)) {
             if (a.n_dwgs > 0)
                 decode_lite_kernel<DT, LAYOUT><<<dim3(a.n_dwgs), dim3(kWgThreads), 0, stream>>>(a);
         } else {
@@ -1775,6 +1811,7 @@ hipError_t launch_layout(int which, const KernelArgs &a, int layout, hipStream_t
     switch (layout) {
     case kLayoutContiguous: return launch_variant<DT, D, kLayoutContiguous>(which, a, stream);
     case kLayoutPaged16: return launch_variant<DT, D, kLayoutPaged16>(which, a, stream);
+    case kLayoutPagedRows: return launch_variant<DT, D, kLayoutPagedRows>(which, a, stream);
     case kLayoutPagedAny: return launch_variant<DT, D, kLayoutPagedAny>(which, a, stream);
     default: return hipErrorInvalidValue;
     }
@@ -1802,9 +1839,11 @@ __global__ void clear_header_kernel(WsHeader *hdr)
 
 hipError_t launch(int which, const KernelArgs &a, int dtype, int head_dim, bool paged, hipStream_t stream)
 {
-    // The block-wise paths want power-of-two blocks of at least 16 keys whose byte size fits 32 bits.
+    // The block-wise path wants power-of-two blocks of at least 16 keys whose byte size fits 32 bits;
+    // the row-wise one, blocks that every load instruction stays inside of.
     const bool block_wise = a.bs_shift >= 4 && a.block_elems * 2 < (1ll << 32);
-    const int layout = !paged ? kLayoutContiguous : (block_wise ? kLayoutPaged16 : kLayoutPagedAny);
+    const bool row_wise = a.block_size > 1 && a.block_size % (kWaveSize / (head_dim / 8)) == 0;
+    const int layout = !paged ? kLayoutContiguous : block_wise ? kLayoutPaged16 : row_wise ? kLayoutPagedRows : kLayoutPagedAny;
     if (dtype == 0 && head_dim == 128) return launch_layout<0, 128>(which, a, layout, stream);
     if (dtype == 0 && head_dim == 64) return launch_layout<0, 64>(which, a, layout, stream);
     if (dtype == 1 && head_dim == 128) return launch_layout<1, 128>(which, a, layout, stream);

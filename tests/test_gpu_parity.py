@@ -92,6 +92,22 @@ def test_token_sizes_that_are_no_power_of_two(hq, hkv, d, block_size):
     check(batch, "serial", decode_chunk=256, prefill_split_len=128, max_prefill_waves=64)
 
 
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("block_size", [1, 2, 4, 6, 8, 12, 40])
+@pytest.mark.parametrize("head_major", [False, True])
+def test_block_sizes_at_the_edges_of_the_row_wise_layout(d, block_size, head_major):
+    """Block sizes that are, or just miss being, a multiple of the rows of one load (8, 4, 2 at 64, 128, 256
+    channels): smaller than a step, larger than one, dividing neither a step nor a tile; contexts that
+    end inside, at and after a block edge."""
+    batch = wl.make_batch(f"rows-d{d}-bs{block_size}", prefill=[(70, 203), (1, 41)], n_q_heads=6, n_kv_heads=3,
+                          decode_kv_lens=[1, block_size, 3 * block_size - 1, 3 * block_size + 1, 399, 640], head_dim=d,
+                          dtype=wl.F16, seed=4000 + d + block_size, block_size=block_size, poison=float("nan"))
+    if head_major:
+        batch = wl.to_head_major(batch)
+    check(batch, "fused")
+    check(batch, "serial", decode_chunk=256, prefill_split_len=64, max_prefill_waves=64)
+
+
 @pytest.mark.parametrize("dtype,hq,hkv,d", [(wl.F16, 8, 2, 128), (wl.BF16, 6, 3, 64), (wl.F16, 4, 4, 128), (wl.BF16, 8, 2, 256)])
 @pytest.mark.parametrize("block_size", [0, 16, 32, 24])
 def test_head_major_cache(dtype, hq, hkv, d, block_size):
