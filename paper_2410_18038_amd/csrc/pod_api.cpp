@@ -67,9 +67,9 @@ pod::KernelArgs make_args(const pod::Plan &p, const void *prefill_q, const void 
     a.pitems_by_wg = (const pod::PrefillItem *)(ws + p.off_pitems_by_wg);
     a.pitem_of_wg = (const int32_t *)(ws + p.off_pitem_of_wg);
     a.dunits = (const pod::DecodeUnit *)(ws + p.off_dunits);
-    a.centries = (const pod::CombineEntry *)(ws + p.off_centries);
-    a.crows = (const int32_t *)(ws + p.off_crows);
-    a.n_crows = (int)(p.crows.size() / 2);
+    a.crows = (const pod::CombineRow *)(ws + p.off_crows);
+    a.n_crows = (int)p.merge_rows.size();
+    a.combine_groups = p.combine_groups;
     a.part_o = (float *)(ws + p.off_part_o);
     a.part_ml = (float *)(ws + p.off_part_ml);
     a.kv_seq_stride = p.prm.kv_seq_stride;
@@ -109,7 +109,6 @@ pod::KernelArgs make_args(const pod::Plan &p, const void *prefill_q, const void 
     a.n_static_seats = p.n_static_seats;
     a.n_dctas = ((int)p.dunits.size() + pod::kWavesPerWg - 1) / pod::kWavesPerWg;
     a.single_unit = 0;
-    a.n_combine = (int)p.centries.size();
     a.n_prefill_rows = (int)p.n_prefill_rows;
     a.p_ratio = p.p_ratio;
     a.d_ratio = p.d_ratio;
@@ -151,14 +150,13 @@ pod_status upload_tables(const pod::Plan &p, void *workspace, hipStream_t s)
     hipError_t e = pod::clear_header((pod::WsHeader *)ws, s);
     if (e != hipSuccess) return fail_hip(e, "clearing workspace counters");
     struct Part { size_t off; const void *src; size_t bytes; };
-    const Part parts[7] = {
+    const Part parts[6] = {
         {p.off_pitem_of_wg, p.pitem_of_wg.data(), p.pitem_of_wg.size() * sizeof(int32_t)},
         {p.off_pitems_by_wg, p.pitems_by_wg.data(), p.pitems_by_wg.size() * sizeof(pod::PrefillItem)},
         {p.off_dq, p.dq_begin, sizeof p.dq_begin},
         {p.off_pitems, p.pitems.data(), p.pitems.size() * sizeof(pod::PrefillItem)},
         {p.off_dunits, p.dunits.data(), p.dunits.size() * sizeof(pod::DecodeUnit)},
-        {p.off_centries, p.centries.data(), p.centries.size() * sizeof(pod::CombineEntry)},
-        {p.off_crows, p.crows.data(), p.crows.size() * sizeof(int32_t)}};
+        {p.off_crows, p.merge_rows.data(), p.merge_rows.size() * sizeof(pod::CombineRow)}};
     for (const Part &part : parts) {
         if (part.bytes == 0) continue;
         e = hipMemcpyAsync(ws + part.off, part.src, part.bytes, hipMemcpyHostToDevice, s);
@@ -384,7 +382,7 @@ static pod_status forward_impl(const void *prefill_q, const void *decode_q, cons
     // holds the rows of prefill groups first, then those of decode groups.
     pod::KernelArgs only_p = a, only_d = a;
     only_p.n_crows = p.n_crows_prefill;
-    only_d.crows = a.crows + 2 * (size_t)p.n_crows_prefill;
+    only_d.crows = a.crows + p.n_crows_prefill;
     only_d.n_crows = a.n_crows - p.n_crows_prefill;
 
     // Prefill kernel and decode kernel on the library's two side streams, forked from and joined

@@ -30,6 +30,7 @@ constexpr int kMaxGroup = 16;              // query heads per K/V head a decode 
 constexpr int kXcdQueues = 8;               // work is queued per XCD (one L2 each); a queue's counter is claimed mostly from its own XCD
 constexpr int kSlotsPerUnit = 2;            // resident workgroups per compute unit (register and LDS budget)
 constexpr int kNullClaimLines = 512;       // power of two, at least the number of resident workgroups
+constexpr int kCombineFetch = 8;            // splits a thread group of the combine kernel fetches together (independent loads)
 constexpr int kCuSlots = 1024;             // hardware unit ids are sparse: (xcc << 6 | se << 4 | cu) < 1024
 
 enum Role : int { kPrefill = 0, kDecode = 1, kNone = -1 };
@@ -69,6 +70,14 @@ struct CombineEntry {
     int32_t n_splits, prow0, split_stride; // partial row of split s, row r: prow0 + s*split_stride + r
     int32_t q_start, q_len;                // copied from the request, so the merge needs no second lookup
     int32_t pad0, pad1;
+};
+
+// One merged output row as the combine kernel reads it: everything in one 16-byte lookup.
+struct CombineRow {
+    int32_t prow;                          // partial row of split 0; split s is one item's or unit's rows further
+    int32_t n_splits;
+    uint32_t out_row_lo, out_row_hi;       // row of `out` counted in heads (token row * n_q_heads + query head);
+                                           // the top bit is set for a decode row
 };
 
 // Counters at the head of the device workspace.  All zero between launches: the last
@@ -134,8 +143,7 @@ struct KernelArgs {
     const PrefillItem *pitems_by_wg;       // the same items in workgroup order, for the kernels that run item blockIdx.x
     const int32_t *pitem_of_wg;            // their indices in `pitems` (what the event log names)
     const DecodeUnit *dunits;
-    const CombineEntry *centries;
-    const int32_t *crows;                  // [n_crows][2] = (combine entry, row inside it): one merged output row each
+    const CombineRow *crows;
     float *part_o;                         // [n_partial_rows][d]  un-normalised fp32 output
     float *part_ml;                        // [n_partial_rows][2]  running max (log2 domain), weight sum
     WsHeader *hdr;
@@ -153,7 +161,8 @@ struct KernelArgs {
     int32_t bs_shift;                      // log2(block_size) when it is a power of two, else -1
     uint32_t bs_magic;                     // ceil(2^32 / block_size) for block sizes above 1 (block_of)
     int32_t n_crows;
-    int32_t n_pitems, n_dunits, n_dwgs, n_combine;   // n_dwgs: decode worker workgroups
+    int32_t combine_groups;                // thread groups of the combine kernel that share a row's splits
+    int32_t n_pitems, n_dunits, n_dwgs;      // n_dwgs: decode worker workgroups
     int32_t n_prefill_rows;
     int32_t fused_grid;
     int32_t pq_begin[kXcdQueues + 1];      // prefill queue q holds items pq_begin[q] .. pq_begin[q+1]-1

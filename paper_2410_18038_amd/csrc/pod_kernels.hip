@@ -1690,44 +1690,41 @@ __global__ __launch_bounds__(kWgThreads, 2) void fused_cta_kernel(KernelArgs a)
 // ------------------------------------------------------------------------------------------
 // Combine: merge split-KV partials.  With running maxima m_s (log2 domain), weight sums l_s and
 // un-normalised outputs O_s:  M = max m_s,  out = sum_s O_s 2^(m_s - M) / sum_s l_s 2^(m_s - M).
+// A row is merged by `combine_groups` groups of D / 4 threads, each of which fetches kCombineFetch splits
+// at a time; what bounds the kernel is its chain of dependent memory round trips (row, partials, and
+// one more for every further fetch), not its bytes, so rows with many splits are shared by more groups.
+// (32 rows of 94 splits: 15.8 us with one group per row, a row list and an entry lookup before it; 5.2 now.)
 // ------------------------------------------------------------------------------------------
 template <int DT, int D>
 __global__ __launch_bounds__(kWgThreads) void combine_kernel(KernelArgs a)
 {
     using N = Num<DT>;
-    constexpr int TPR = D / 4;                      // threads per row, 4 channels each
-    constexpr int RPP = kWgThreads / TPR;           // rows per pass
-    constexpr int U = 8;                            // splits fetched together (independent loads)
-    // every group of TPR threads merges one output row; a workgroup takes RPP rows of the list
-    const int group = a.group;
+    constexpr int TPR = D / 4;                      // threads per group, 4 channels each
+    constexpr int GPW = kWgThreads / TPR;           // groups of the workgroup
+    constexpr int U = kCombineFetch;
+    __shared__ f32x4 part_acc[GPW][TPR];
+    __shared__ float part_m[GPW], part_l[GPW];
     const int sub = threadIdx.x % TPR;
-    const int crow = blockIdx.x * RPP + threadIdx.x / TPR;
-    if (crow < a.n_crows) {
-        const int2 er = *(const int2 *)(a.crows + 2 * (int64_t)crow);
-        const CombineEntry e = a.centries[er.x];
-        const int r = er.y;
-        int64_t out_row;
-        int hq;
-        if (e.kind == kPrefill) {
-            const int R = e.row0 + r;
-            const int tok = R / group;
-            hq = e.kv_head * group + (R - tok * group);
-            out_row = e.q_start + tok;
-        } else {
-            hq = e.kv_head * group + r;
-            out_row = (int64_t)a.n_prefill_rows + e.q_start;
-        }
-        float M = neg_inf(), lsum = 0.f;
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        for (int s0 = 0; s0 < e.n_splits; s0 += U) {
+    const int grp = threadIdx.x / TPR;
+    const int G = a.combine_groups;                 // a power of two, at most GPW
+    const int share = grp & (G - 1);                // this group's part of its row's splits
+    const int crow = (blockIdx.x * GPW + grp) / G;
+    const bool row_ok = crow < a.n_crows;
+    float M = neg_inf(), lsum = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    int64_t out_row = 0;
+    if (row_ok) {
+        const u32x4 w = load16(a.crows + crow);
+        const int n_splits = (int)w[1], stride = (int)w[3] < 0 ? a.group : prefill_item_rows(D);
+        out_row = (int64_t)((uint64_t)w[2] | (uint64_t)(w[3] & 0x7fffffffu) << 32);
+        for (int s0 = share * U; s0 < n_splits; s0 += G * U) {
             float ms[U], ls[U];
             f32x4 v[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int s = min(s0 + u, e.n_splits - 1);
-                const int64_t prow = (int64_t)e.prow0 + (int64_t)s * e.split_stride + r;
+                const int64_t prow = (int64_t)(int)w[0] + (int64_t)min(s0 + u, n_splits - 1) * stride;
                 const float2 ml = *(const float2 *)(a.part_ml + prow * 2);
-                ms[u] = (s0 + u < e.n_splits) ? ml.x : neg_inf();
+                ms[u] = (s0 + u < n_splits) ? ml.x : neg_inf();
                 ls[u] = ml.y;
                 v[u] = *(const f32x4 *)(a.part_o + prow * D + sub * 4);
             }
@@ -1740,17 +1737,35 @@ __global__ __launch_bounds__(kWgThreads) void combine_kernel(KernelArgs a)
             acc = acc * keep;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const float w = fast_exp2(ms[u] - Mn);   // 0 for a split that saw no key
-                lsum += ls[u] * w;
-                acc += v[u] * w;
+                const float wt = fast_exp2(ms[u] - Mn);  // 0 for a split that saw no key
+                lsum += ls[u] * wt;
+                acc += v[u] * wt;
             }
             M = Mn;
         }
+    }
+    if (G > 1) {
+        part_acc[grp][sub] = acc;
+        if (sub == 0) { part_m[grp] = M; part_l[grp] = lsum; }
+        __syncthreads();
+        if (share != 0) return;
+        float Mn = M;
+        for (int g = 1; g < G; ++g) Mn = fmaxf(Mn, part_m[grp + g]);
+        const float keep = fast_exp2(M - Mn);       // some group saw a key: Mn is finite
+        lsum *= keep;
+        acc = acc * keep;
+        for (int g = 1; g < G; ++g) {
+            const float wt = fast_exp2(part_m[grp + g] - Mn);
+            lsum += part_l[grp + g] * wt;
+            acc += part_acc[grp + g][sub] * wt;
+        }
+    }
+    if (row_ok) {
         const float inv = 1.f / lsum;
         typename N::v4 w4;
 #pragma unroll
         for (int i = 0; i < 4; ++i) w4[i] = (typename N::elem)(acc[i] * inv);
-        *(typename N::v4 *)((typename N::elem *)a.out + (out_row * a.n_q_heads + hq) * D + sub * 4) = w4;
+        *(typename N::v4 *)((typename N::elem *)a.out + out_row * D + sub * 4) = w4;
     }
 }
 
@@ -1795,8 +1810,8 @@ static hipError_t launch_variant(int which, const KernelArgs &a, hipStream_t str
         break;
     case kLaunchCombine:
         if (a.n_crows > 0) {
-            constexpr int kRowsPerWg = kWgThreads / (D / 4);
-            combine_kernel<DT, D><<<dim3((a.n_crows + kRowsPerWg - 1) / kRowsPerWg), dim3(kWgThreads), 0, stream>>>(a);
+            const int rows_per_wg = kWgThreads / (D / 4) / a.combine_groups;
+            combine_kernel<DT, D><<<dim3((a.n_crows + rows_per_wg - 1) / rows_per_wg), dim3(kWgThreads), 0, stream>>>(a);
         }
         break;
     default:

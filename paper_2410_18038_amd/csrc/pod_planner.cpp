@@ -352,6 +352,7 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
         size_t n_pairs = 0;
         for (const CombineEntry &c : plan.centries) n_pairs += (size_t)c.n_rows;
         plan.crows.reserve(2 * n_pairs);
+        plan.merge_rows.reserve(n_pairs);
     }
     for (size_t e = 0; e < plan.centries.size(); ++e) {
         const CombineEntry &c = plan.centries[e];
@@ -359,9 +360,19 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
             if (c.kind == kPrefill && (c.row0 + r) / group >= c.q_len) continue;
             plan.crows.push_back((int32_t)e);
             plan.crows.push_back(r);
+            const int64_t token_row = c.kind == kPrefill ? c.q_start + (c.row0 + r) / group : n_prefill_rows + c.q_start;
+            const int head = c.kv_head * group + (c.kind == kPrefill ? (c.row0 + r) % group : r);
+            const uint64_t out_row = (uint64_t)(token_row * prm.n_q_heads + head) | (uint64_t)(c.kind == kDecode) << 63;
+            plan.merge_rows.push_back(CombineRow{c.prow0 + r, c.n_splits, (uint32_t)out_row, (uint32_t)(out_row >> 32)});
         }
         if (c.kind == kPrefill) plan.n_crows_prefill = (int)(plan.crows.size() / 2);
     }
+
+    // A group of the combine kernel fetches kCombineFetch splits at a time; as many groups share a row as
+    // its splits need to be fetched at once, as far as a workgroup has groups.
+    while (plan.combine_groups < kWgThreads / (prm.head_dim / 4) &&
+           plan.combine_groups * kCombineFetch < std::max(plan.max_psplits, plan.max_dsplits))
+        plan.combine_groups *= 2;
 
     // The ratio compares workgroup counts as the paper does (Section 4.1): decode work counts as the
     // workgroups it would fill at one wavefront per unit, up to one resident round.
@@ -404,8 +415,7 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
     plan.off_pitems_by_wg = off; off = align256(off + plan.pitems_by_wg.size() * sizeof(PrefillItem));
     plan.off_pitem_of_wg = off; off = align256(off + plan.pitem_of_wg.size() * sizeof(int32_t));
     plan.off_dunits = off;   off = align256(off + plan.dunits.size() * sizeof(DecodeUnit));
-    plan.off_centries = off; off = align256(off + plan.centries.size() * sizeof(CombineEntry));
-    plan.off_crows = off;    off = align256(off + plan.crows.size() * sizeof(int32_t));
+    plan.off_crows = off;    off = align256(off + plan.merge_rows.size() * sizeof(CombineRow));
     plan.off_dq = off;       off = align256(off + sizeof plan.dq_begin);
     plan.off_part_o = off;   off = align256(off + (size_t)plan.n_partial_rows * prm.head_dim * sizeof(float));
     plan.off_part_ml = off;  off = align256(off + (size_t)plan.n_partial_rows * 2 * sizeof(float));

@@ -26,6 +26,8 @@ struct Plan {
     std::vector<DecodeUnit> dunits;
     std::vector<CombineEntry> centries;
     std::vector<int32_t> crows;             // (entry, row) pairs, prefill entries first
+    std::vector<CombineRow> merge_rows;     // the same rows as the combine kernel reads them
+    int combine_groups = 1;                 // thread groups that share a row's splits
     int n_crows_prefill = 0;
     int64_t n_prefill_rows = 0;
     int64_t n_partial_rows = 0;
@@ -38,7 +40,7 @@ struct Plan {
     int n_dwgs = 0;                         // decode workers: workgroups of the stand-alone decode kernel, decode seats of the fused one
     int fused_grid = 0;                     // workgroups of the fused kernel
     // byte offsets inside the workspace (each 256-byte aligned)
-    size_t off_pitems = 0, off_pitems_by_wg = 0, off_pitem_of_wg = 0, off_dunits = 0, off_centries = 0, off_crows = 0, off_dq = 0, off_part_o = 0, off_part_ml = 0;
+    size_t off_pitems = 0, off_pitems_by_wg = 0, off_pitem_of_wg = 0, off_dunits = 0, off_crows = 0, off_dq = 0, off_part_o = 0, off_part_ml = 0;
     size_t ws_bytes = 0;
     // events of the two-kernel modes (fork, two joins), created on first use
     void *events[3] = {nullptr, nullptr, nullptr};
