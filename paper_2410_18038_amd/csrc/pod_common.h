@@ -29,7 +29,6 @@ constexpr int kMaxGroup256 = 8;            // query heads per K/V head at head_d
 constexpr int kMaxGroup = 16;              // query heads per K/V head a decode unit can hold
 constexpr int kXcdQueues = 8;               // work is queued per XCD (one L2 each); a queue's counter is claimed mostly from its own XCD
 constexpr int kSlotsPerUnit = 2;            // resident workgroups per compute unit (register and LDS budget)
-constexpr int kNullClaimLines = 512;       // power of two, at least the number of resident workgroups
 constexpr int kCombineFetch = 8;            // splits a thread group of the combine kernel fetches together (independent loads)
 constexpr int kCuSlots = 1024;             // hardware unit ids are sparse: (xcc << 6 | se << 4 | cu) < 1024
 
@@ -94,9 +93,7 @@ struct WsHeader {
     uint32_t next_pitem_xcd[kXcdQueues][32];
     // Next decode unit of each per-XCD queue (offset inside the queue), claimed by wavefronts.
     uint32_t next_dunit_xcd[kXcdQueues][32];
-    // Words that decode wavefronts add zero to in the turns in which they claim nothing (one
-    // line per workgroup; see the decode worker).  Always zero.
-    uint32_t null_claim[kNullClaimLines][32];
+    uint32_t reserved[512][32];            // zero
 };
 
 // Which operation the workgroup holding `ticket` on hardware unit `unit` starts with: the ticket

@@ -834,10 +834,11 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
 
     // ---- claims ------------------------------------------------------------------------
     // The compiler keeps exact counts of the loads in flight only as long as every path through
-    // the ring's loop issues the same memory operations.  So a claim that must be waited for on
-    // the spot is one opaque instruction pair (the atomic and its wait), and the claim issued
-    // ahead of its use is part of every turn of the ring: a turn that wants no unit adds zero to
-    // a word of its own workgroup instead.
+    // the ring's loop issues the same memory operations it knows of.  A claim is therefore one opaque
+    // instruction pair, the atomic and its wait.  (Before, the claim was an ordinary atomic issued ahead in
+    // every turn of the ring, adding zero to a word of the workgroup in the turns that wanted no unit;
+    // 430 such atomics per us on the chip cost the stream 5 % of its rate, 7.1 against 7.5 TB/s in the
+    // steady state of 2048 units of 4096 keys, more than waiting for one claim per unit does.)
     int cq = __builtin_amdgcn_readfirstlane(xcd) & (kXcdQueues - 1), tried = 0;
     auto claim_now = [&]() __attribute__((always_inline)) -> int { return decode_claim(a, cq, lane); };
     // Turns a claimed counter value into a unit index.  When the queue is used up it claims from
@@ -912,13 +913,11 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
     // live in scratch memory).
     constexpr uint32_t kHeadInTail = 1u;           // head and tail are in the same unit
     constexpr uint32_t kNextValid = 2u;            // `nx` holds a fetched unit, its query heads are in (or on their way to) LDS
-    constexpr uint32_t kClaimPending = 4u;         // a claim has been issued and not looked at yet
     constexpr uint32_t kExhausted = 8u;            // every queue has been found empty
     constexpr uint32_t kDone = 16u;                // the tail has finished the last unit
     // In the CTA-parallel launch a wavefront runs the one unit it was given: the queues count as
     // used up from the start, so no claim is ever issued and the worker ends with its unit.
     uint32_t st = kHeadInTail | (a.single_unit ? kExhausted : 0u);
-    uint32_t claim_v = 0;                          // lane 0: counter value returned by the claim of the current turn
     int n_iss = 0, q_mark = 0;                     // steps issued so far; their count when the last Q copy was issued
 
     // Rows past the end of a unit's last step re-read its last row (the keys are masked out of the
@@ -1000,9 +999,7 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
     // Claim result -> descriptor -> query copy.  Waits for the claim and for the descriptor.
     auto fetch_next = [&]() __attribute__((always_inline)) {
         int idx = -1;
-        if (st & kClaimPending) idx = claim_resolve((int)__builtin_amdgcn_readfirstlane(claim_v));
-        else if (!(st & kExhausted)) idx = claim_resolve(claim_now());
-        st &= ~kClaimPending;
+        if (!(st & kExhausted)) idx = claim_resolve(claim_now());
         nx = load_desc(max(idx, 0));
         q_mark = idx >= 0 ? n_iss : q_mark;
         st |= idx >= 0 ? kNextValid : kExhausted;
@@ -1123,7 +1120,6 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
 
     Slot ring[R];
     int slot_t[R];
-    uint32_t *const null_ctr = &a.hdr->null_claim[blockIdx.x & (kNullClaimLines - 1)][wave];
 #pragma unroll
     for (int r = 0; r < R - 1; ++r) {
         issue_step(ring[r], slot_t[r]);
@@ -1140,16 +1136,9 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
     while (!(st & kDone)) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            if (r == 0) {
-                // Claim ahead, once the head is close to the end of its unit: the answer is picked
-                // up at the end of this turn, by when the slot requested right after the claim
-                // has been waited for, and memory operations return in issue order.
-                const bool want = st == kHeadInTail && hu.t1 - h_t <= kClaimAhead * STEP;
-                st |= want ? kClaimPending : 0u;
-                uint32_t *ctr = want ? &a.hdr->next_dunit_xcd[cq][0] : null_ctr;
-                if (lane == 0) claim_v = atomicAdd(ctr, want ? 1u : 0u);
-                lane_test_done();
-            }
+            // Claim ahead, once the head is close to the end of its unit.  The claim is waited for, which
+            // at this point waits for the slot that is consumed next anyway.
+            if (r == 0 && st == kHeadInTail && hu.t1 - h_t <= kClaimAhead * STEP) fetch_next();
             // The head moves on once it has run out of its unit, the next unit is known and the
             // tail has reached the head's unit (the ring holds at most one unit boundary).
             if (h_t >= hu.t1 && (st & (kNextValid | kHeadInTail)) == (kNextValid | kHeadInTail)) {
@@ -1187,12 +1176,6 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
                 q_from_lds();
                 reset_acc();
                 if (a.evlog) tb = wall_clock64();
-            }
-            if (r == R - 1) {
-                // (the claim's answer is read in every turn, wanted or not, so that every path
-                // through a turn has the same outstanding operations)
-                claim_v = (uint32_t)__builtin_amdgcn_readfirstlane(claim_v);
-                if (st & kClaimPending) fetch_next();
             }
         }
     }
@@ -1257,7 +1240,16 @@ __device__ __forceinline__ int prefill_worker_run(const KernelArgs &a, unsigned 
             it.req = w[0]; it.kv_head = w[1]; it.row0 = w[2]; it.n_rows = w[3];
             it.kv_begin = w[4]; it.kv_end = w[5]; it.prow0 = w[6]; it.split = w[7];
         }
+        // Of the two workgroups on a unit the hardware serves the older one's memory operations first.
+        // A prefill workgroup that is the younger one beside a decode worker waits behind a stream that
+        // always has the next load ready (items of 300-700 us where older ones take 120-230, chunk of 1024
+        // + 64 decodes, MHA), so its wavefronts ask for issue priority: all items then take 140-230 us.
+        // us per call without and with it: 680 / 671 there, 149.7 / 142.4 (512 + 16 decodes), 99.9 / 91.8
+        // (64 channels), 1250 / 1228 (32K contexts); at 256 channels, where an item moves twice the bytes
+        // per row, the stream pays for it: 476 / 484, so it is left out.
+        if constexpr (D <= 128) __builtin_amdgcn_s_setprio(3);
         prefill_item_run<DT, D, LAYOUT>(a, it, smem);
+        if constexpr (D <= 128) __builtin_amdgcn_s_setprio(0);
         if (a.evlog && threadIdx.x == 0) log_event(a, kPrefill, item, tb);
         ++n_done;
     }
