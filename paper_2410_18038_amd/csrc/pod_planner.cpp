@@ -22,6 +22,18 @@ std::string fmt(const char *f, long long a = 0, long long b = 0, long long c = 0
     return buf;
 }
 
+// Up to this many keys per wavefront the decode work is cut into one round of equal units.
+constexpr int kOneRoundShare = 320;
+
+// Decode units when every request is cut into pieces of `chunk` keys.
+int64_t units_of_length(const pod_attn_params &prm, const int32_t *seq_meta, int chunk)
+{
+    int64_t n = 0;
+    for (int r = prm.n_prefill; r < prm.n_prefill + prm.n_decode; ++r)
+        n += (int64_t)prm.n_kv_heads * ceil_div(seq_meta[4 * r + 2], chunk);
+    return n;
+}
+
 }  // namespace
 
 void role_ratio(int policy, int n_prefill_wgs, int n_decode_wgs, int &p, int &d)
@@ -140,31 +152,19 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
 
     int64_t next_prow = 0;
 
-    // ---- decode chunk (needed first: how much decode there is decides the prefill split cap) ------
+    // ---- how much decode there is (decides the prefill split cap) ------------------------
     int64_t token_heads = 0;
-    for (int r = prm.n_prefill; r < n_req; ++r) token_heads += (int64_t)seq_meta[4 * r + 2] * prm.n_kv_heads;
-    int decode_chunk = prm.decode_chunk;
-    if (decode_chunk <= 0) {
-        // About four units per streaming wavefront (there are four of those per compute unit):
-        // ragged contexts and wavefronts of unequal speed still balance (units are claimed
-        // longest first), and units stay long enough (>= 512 keys) that their partial rows
-        // stay small next to the stream.  (Measured: between 1024 and 4096 keys the choice
-        // moves the time by 1 %; finer cuts gain nothing once the ring runs on across unit
-        // boundaries, and cost partial rows and claims.)
-        const int64_t slots = (int64_t)n_cus * 8;
-        // The floor is 768 keys as long as that still leaves a unit for every streaming wavefront
-        // (measured on batches of 16 requests at 4K-16K keys, 1.5-2.2 units per wavefront: 2-6 %
-        // faster than 512, which in turn beats 256 and 384; 1024 is slower again), else 512.
-        const int64_t floor_keys = token_heads / 768 >= (int64_t)n_cus * kWavesPerWg ? 768 : 512;
-        decode_chunk = (int)std::min<int64_t>(2048, std::max<int64_t>(floor_keys, (token_heads + 2 * slots - 1) / (2 * slots)));
-        decode_chunk = round_up(decode_chunk, 256);
+    int longest_decode = 0;
+    for (int r = prm.n_prefill; r < n_req; ++r) {
+        token_heads += (int64_t)seq_meta[4 * r + 2] * prm.n_kv_heads;
+        longest_decode = std::max(longest_decode, seq_meta[4 * r + 2]);
     }
-    decode_chunk = round_up(std::max(decode_chunk, kDecodeStep), kDecodeStep);
-    // Does the decode work seat a worker on every compute unit (at least four units for each)?
-    int64_t decode_units_at_least = 0;
-    for (int r = prm.n_prefill; r < n_req; ++r)
-        decode_units_at_least += (int64_t)prm.n_kv_heads * ceil_div(seq_meta[4 * r + 2], decode_chunk);
-    const bool decode_on_every_unit = decode_units_at_least >= (int64_t)kWavesPerWg * n_cus;
+    // Keys per streaming wavefront (there are four of those per compute unit).
+    const int64_t n_waves = (int64_t)n_cus * kWavesPerWg;
+    const int64_t share = (token_heads + n_waves - 1) / n_waves;
+    // Does the decode work hold a worker on every compute unit for a good part of the launch?
+    const int given_chunk = prm.decode_chunk > 0 ? round_up(prm.decode_chunk, kDecodeStep) : 0;
+    const bool decode_on_every_unit = given_chunk > 0 ? units_of_length(prm, seq_meta, given_chunk) >= n_waves : share >= 512;
 
     // ---- prefill items -----------------------------------------------------------------
     // Row blocks of 128 packed rows per K/V head; split-KV only when there are too few blocks to
@@ -266,13 +266,46 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
 
     // ---- decode units ------------------------------------------------------------------
     {
-        const int chunk = decode_chunk;
+        int longest_item = 0;                    // keys of the longest prefill item
+        for (const PrefillItem &it : plan.pitems) longest_item = std::max(longest_item, it.kv_end - it.kv_begin);
+        const bool one_round = prm.decode_chunk <= 0 && share <= kOneRoundShare;
+        const int shortest = std::max(64, 8 * group);    // a unit's partial rows stay below 1/8 of its K/V bytes
+        int chunk;
+        if (given_chunk > 0) {
+            chunk = given_chunk;
+        } else if (one_round) {
+            // Little work: what counts is the length of the one unit a wavefront runs (16 keys take about
+            // 0.7 us), so requests are cut into equal pieces as short as one round of the chip allows.
+            // Cutting costs a merge pass, about as long as a hundred keys: it is not worth it when
+            // the whole requests are short, nor when the prefill items beside them take longer anyway (a
+            // tile of 64 keys takes about 1.1 us) and need no merge themselves.
+            // us per call, units of at least 512 keys before: one decode of 6007 keys 31.9 -> 14.4,
+            // three at 4K (8 heads per K/V head) 31.8 -> 18.1, 128 short ones 21.1 -> 15.0.
+            chunk = shortest;
+            if (longest_decode <= shortest + 112 || (longest_item > 0 && plan.centries.empty() && longest_decode <= longest_item / 8 + 150))
+                chunk = round_up(std::max(longest_decode, kDecodeStep), kDecodeStep);
+            else
+                while (chunk < std::min<int64_t>(longest_decode, 2 * share) && units_of_length(prm, seq_meta, chunk) > n_waves)
+                    chunk += kDecodeStep;
+        } else {
+            // Enough work for every wavefront: pieces of at most one wavefront's share, and the second
+            // half of every request in pieces that halve down to a quarter of that.  Wavefronts do not
+            // stream at one rate (those of every second XCD get 10-20 % less), units are claimed longest
+            // first, and the short ones are what is left to even that out at the end.  A piece is no
+            // longer than about 1 MB of K/V: with long ones the slow wavefronts finish late (pieces of
+            // 4096 keys instead of 2048, 64 x 4096 keys x 32 heads: 659 against 641 us; of 1296 against
+            // 2592 keys of 256 channels: 464 against 483).  us per call, pieces of a quarter share or 768 keys
+            // before: 8 decodes 62.6 -> 59.6, 512 + 16 decodes 140.7 -> 135.9, 256 channels 473 -> 464,
+            // 15 / 5 heads 95 -> 86, 84 decodes at 0.5K-1K 66.8 -> 57.7.
+            const int cap = 2048 * 128 / std::max(128, prm.head_dim);
+            chunk = round_up((int)std::min<int64_t>(std::max<int64_t>(share, shortest), cap), kDecodeStep);
+        }
         plan.decode_chunk = chunk;
         std::vector<int> cuts;
         {
             size_t n_est = 0;
             for (int r = prm.n_prefill; r < n_req; ++r)
-                n_est += (size_t)prm.n_kv_heads * (size_t)(seq_meta[4 * r + 2] / chunk + 3);
+                n_est += (size_t)prm.n_kv_heads * (size_t)(seq_meta[4 * r + 2] / chunk + 5);
             plan.dunits.reserve(n_est);
             plan.centries.reserve(plan.centries.size() + (size_t)prm.n_decode * prm.n_kv_heads);
         }
@@ -280,14 +313,30 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
             const int kv_len = seq_meta[4 * r + 2];
             const int s = ceil_div(kv_len, chunk);
             const int tps = round_up(ceil_div(kv_len, s), kDecodeStep);
-            // Token ranges of the request: equal pieces of tps keys, except that the last piece
-            // is cut again into a half and two quarters when those are still at least 128 keys
-            // (a request that fits one piece stays whole and needs no merge).
+            // Token ranges of the request.  With a length given by the caller: equal pieces of tps keys,
+            // except that the last piece is cut again into a half and two quarters when those are
+            // still at least 128 keys (a request that fits one piece stays whole and needs no merge).
             // Units are claimed longest first, so the short pieces are what is left at the end of
             // a launch, when the wavefronts that are still busy decide when it ends.
             cuts.clear();
-            for (int t = 0; t < kv_len; t += tps) cuts.push_back(t);
-            {
+            const bool taper = prm.decode_chunk <= 0 && !one_round;
+            const int last = round_up(std::max(chunk / 4, shortest), kDecodeStep);     // shortest piece of a taper
+            if (taper && kv_len > chunk + last / 2) {
+                const int tail = kv_len / 2 >= 2 * last ? kv_len / 2 : 0;
+                const int big = kv_len - tail, piece = round_up(ceil_div(big, ceil_div(big, chunk)), kDecodeStep);
+                int t = 0;
+                for (; t < big; t += piece) cuts.push_back(t);
+                for (t = std::min(t, kv_len); t < kv_len;) {
+                    cuts.push_back(t);
+                    const int left = kv_len - t, half = std::min(chunk, left / 2 / kDecodeStep * kDecodeStep);
+                    t += half >= last ? half : left >= 2 * last ? last : left;
+                }
+            } else if (taper) {
+                cuts.push_back(0);
+            } else {
+                for (int t = 0; t < kv_len; t += tps) cuts.push_back(t);
+            }
+            if (prm.decode_chunk > 0) {
                 const int t_last = cuts.back(), len = kv_len - t_last;
                 const int quarter = round_up(len / 4, kDecodeStep);
                 const int half = (len - 2 * quarter) / kDecodeStep * kDecodeStep;    // cuts stay multiples of a step

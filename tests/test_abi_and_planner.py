@@ -589,6 +589,24 @@ def test_decode_last_piece_is_cut_into_half_and_quarters():
     plan.close(); plan2.close()
 
 
+@pytest.mark.parametrize("hkv,group,lens", [
+    (8, 1, [64]), (8, 1, [176]), (8, 1, [177]), (8, 8, [6007]), (1, 16, [128, 241, 40000]),      # below one round
+    (8, 4, [40960]), (8, 4, [40960 + 128]),                # 320 keys per wavefront, and just above
+    (32, 1, [512, 4096, 17, 2300]), (8, 4, [16384] * 16), (4, 8, [32768] * 32), (1, 2, [1] * 3000)])
+def test_automatic_decode_cuts_cover_every_token(hkv, group, lens):
+    """Decode units of automatic length on both sides of the rule that picks them: one round of equal
+    pieces for little work, else pieces of a wavefront's share with a taper."""
+    prm, meta = meta_only("auto", [], lens, hq=hkv * group, hkv=hkv)
+    prm.n_compute_units = 256
+    info = coverage_check(prm, meta)
+    share = -(-sum(lens) * hkv // 1024)
+    assert info.decode_chunk % 16 == 0
+    if share <= 320 and len(lens) * hkv <= 1024 and max(lens) <= 2 * share:
+        assert info.n_decode_units <= 1024
+    if max(lens) <= 176:
+        assert info.n_combine == 0
+
+
 def test_binder_spreads_a_long_pattern_over_the_units():
     """A unit holds two workgroups, so unit u counts its tickets from 2u: with 4 prefill : 1 decode
     every fifth slot of the chip starts in the decode operation, and with 1 : 1 every unit still
