@@ -55,8 +55,11 @@ void role_ratio(int policy, int n_prefill_wgs, int n_decode_wgs, int &p, int &d)
     d = std::max(d, 1);
 }
 
-pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n_cus, Plan &plan,
-                      std::string &err)
+// Longest decode unit of the automatic cut: about 1 MB of K/V (see "decode units" below).
+static int longest_unit(int head_dim) { return 2048 * 128 / std::max(128, head_dim); }
+
+static pod_status cut_batch(const pod_attn_params &prm, const int32_t *seq_meta, int n_cus, int unit_cap, Plan &plan,
+                            std::string &err)
 {
     // ---- parameters --------------------------------------------------------------------
     if (prm.n_prefill < 0 || prm.n_decode < 0) { err = "negative request count"; return POD_ERR_INVALID_ARG; }
@@ -297,8 +300,7 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
             // 2592 keys of 256 channels: 464 against 483).  us per call, pieces of a quarter share or 768 keys
             // before: 8 decodes 62.6 -> 59.6, 512 + 16 decodes 140.7 -> 135.9, 256 channels 473 -> 464,
             // 15 / 5 heads 95 -> 86, 84 decodes at 0.5K-1K 66.8 -> 57.7.
-            const int cap = 2048 * 128 / std::max(128, prm.head_dim);
-            chunk = round_up((int)std::min<int64_t>(std::max<int64_t>(share, shortest), cap), kDecodeStep);
+            chunk = round_up((int)std::min<int64_t>(std::max<int64_t>(share, shortest), unit_cap), kDecodeStep);
         }
         plan.decode_chunk = chunk;
         std::vector<int> cuts;
@@ -470,6 +472,22 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
     plan.off_part_ml = off;  off = align256(off + (size_t)plan.n_partial_rows * 2 * sizeof(float));
     plan.ws_bytes = off;
     return POD_OK;
+}
+
+pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n_cus, Plan &plan,
+                      std::string &err)
+{
+    constexpr int kOneCapForAll = 2048;
+    const int cap = longest_unit(prm.head_dim);
+    pod_status st = cut_batch(prm, seq_meta, n_cus, cap, plan, err);
+    // Wide heads are cut at 1024 keys because that streams 4 % faster, but it doubles their partial rows.
+    // Where those are what keeps a batch out of the library's own scratch, it is cut at 2048 keys.
+    if (st == POD_OK && cap < kOneCapForAll && prm.decode_chunk <= 0 && plan.ws_bytes > POD_ATTN_STATIC_SCRATCH_BYTES) {
+        Plan coarse;
+        if (cut_batch(prm, seq_meta, n_cus, kOneCapForAll, coarse, err) == POD_OK && coarse.ws_bytes <= POD_ATTN_STATIC_SCRATCH_BYTES)
+            plan = std::move(coarse);
+    }
+    return st;
 }
 
 }  // namespace pod

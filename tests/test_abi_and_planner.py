@@ -607,6 +607,21 @@ def test_automatic_decode_cuts_cover_every_token(hkv, group, lens):
         assert info.n_combine == 0
 
 
+@pytest.mark.parametrize("n_decode,kv_len,hq,hkv", [(200, 25163, 16, 8), (96, 56519, 16, 8), (240, 53884, 8, 2)])
+def test_wide_heads_are_cut_coarser_where_finer_cuts_miss_the_static_scratch(n_decode, kv_len, hq, hkv):
+    prm, meta = meta_only("wide", [], [kv_len] * n_decode, hq=hq, hkv=hkv, d=256)
+    plan = pod.pod_attn_plan_create(prm, meta)
+    assert plan.info().decode_chunk == 2048
+    assert pod.pod_attn_workspace_size(plan) <= pod.STATIC_SCRATCH_BYTES
+    plan.close()
+    # the finer cut stays where it fits, and where neither does
+    for n in (n_decode // 8, 8 * n_decode):
+        prm, meta = meta_only("wide", [], [kv_len] * n, hq=hq, hkv=hkv, d=256)
+        plan = pod.pod_attn_plan_create(prm, meta)
+        assert plan.info().decode_chunk == 1024
+        plan.close()
+
+
 def test_binder_spreads_a_long_pattern_over_the_units():
     """A unit holds two workgroups, so unit u counts its tickets from 2u: with 4 prefill : 1 decode
     every fifth slot of the chip starts in the decode operation, and with 1 : 1 every unit still
