@@ -45,13 +45,10 @@ template <> struct Num<0> {   // IEEE binary16
     static __device__ __forceinline__ f32x4 mfma16k16(s16x4 a, v4 b, f32x4 c) {
         return __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(v4, a), b, c, 0, 0, 0);
     }
-    // acc + sum of the eight 16-bit values (one dot-product instruction per pair)
-    static __device__ __forceinline__ float add_all(v8 p, float acc) {
-        typedef _Float16 v2 __attribute__((ext_vector_type(2)));
-        const v2 ones = {(_Float16)1.f, (_Float16)1.f};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_fdot2(v2{p[2 * i], p[2 * i + 1]}, ones, acc, false);
-        return acc;
+    // acc + sum of the lane's own four 16-bit values, in every element of acc
+    static __device__ __forceinline__ f32x4 add_all(u32x2 p, f32x4 acc) {
+        const v4 ones = {(_Float16)1.f, (_Float16)1.f, (_Float16)1.f, (_Float16)1.f};
+        return __builtin_amdgcn_mfma_f32_4x4x4f16(ones, __builtin_bit_cast(v4, p), acc, 0, 0, 0);
     }
 };
 template <> struct Num<1> {   // bfloat16
@@ -67,12 +64,9 @@ template <> struct Num<1> {   // bfloat16
     static __device__ __forceinline__ f32x4 mfma16k16(s16x4 a, v4 b, f32x4 c) {
         return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, __builtin_bit_cast(s16x4, b), c, 0, 0, 0);
     }
-    static __device__ __forceinline__ float add_all(v8 p, float acc) {
-        typedef __bf16 v2 __attribute__((ext_vector_type(2)));
-        const v2 ones = {(__bf16)1.f, (__bf16)1.f};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_fdot2_f32_bf16(v2{p[2 * i], p[2 * i + 1]}, ones, acc, false);
-        return acc;
+    static __device__ __forceinline__ f32x4 add_all(u32x2 p, f32x4 acc) {
+        const short one = 0x3f80;
+        return __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(s16x4{one, one, one, one}, __builtin_bit_cast(s16x4, p), acc, 0, 0, 0);
     }
 };
 
@@ -489,7 +483,8 @@ __device__ __forceinline__ void prefill_item_run(const KernelArgs &a, const Pref
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[mb][r] = 0.f;
-    float m_run = neg_inf(), l_run = 0.f;
+    float m_run = neg_inf();
+    f32x4 l_run = {0.f, 0.f, 0.f, 0.f};                      // four copies of this lane's weight sum
     const float c = a.scale_log2;
 
     // S^T = K Q^T for one tile: rows = keys, columns = this wavefront's query rows.
@@ -578,7 +573,11 @@ __device__ __forceinline__ void prefill_item_run(const KernelArgs &a, const Pref
 
         const bool live = j0 <= wave_maxpos;                 // something visible to this wavefront
         const bool next_live = (jt + 1 < n_tiles) && (j0 + T <= wave_maxpos);
+        // Matrix blocks ask for issue before the other wavefront's softmax: the two then settle into
+        // opposite phases.  (At 256 channels raised priority costs the decode stream more; see the worker.)
+        if constexpr (D <= 128) __builtin_amdgcn_s_setprio(3);
         if (next_live) scores(cur ^ 1, s_next);              // matrix unit: scores of the next tile
+        if constexpr (D <= 128) __builtin_amdgcn_s_setprio(2);
         if (live) {
             // vector ALUs: softmax of the current tile
             const bool need_mask = (j0 + T - 1 > wave_minpos) || (j0 + T > it.kv_end);
@@ -602,7 +601,7 @@ __device__ __forceinline__ void prefill_item_run(const KernelArgs &a, const Pref
             if (__builtin_amdgcn_ballot_w64(grow) != 0) {
                 const float alpha = grow ? fast_exp2(m_run - mx) : 1.f;   // mx is finite where grow holds
                 m_run = grow ? mx : m_run;
-                l_run *= alpha;
+                l_run = l_run * alpha;
 #pragma unroll
                 for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -615,11 +614,6 @@ __device__ __forceinline__ void prefill_item_run(const KernelArgs &a, const Pref
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
                     pk[tb][r >> 3][r & 7] = (typename N::elem)fast_exp2(__builtin_fmaf(s_cur[tb][r], c, -m_use));
-            // the weight sum is taken over the rounded weights, the ones the PV product uses
-#pragma unroll
-            for (int tb = 0; tb < NTB; ++tb)
-#pragma unroll
-                for (int u = 0; u < 2; ++u) l_run = N::add_all(pk[tb][u], l_run);
             // O^T += V^T P^T : rows = channels, contraction over the keys in S's own register order.
             const POD_LDS unsigned char *vb = lds + (2 + cur) * L::kTileBytes;
             uint32_t v_base = v_rd0;
@@ -627,7 +621,7 @@ __device__ __forceinline__ void prefill_item_run(const KernelArgs &a, const Pref
             // Operation j = (channel block j / (2 NTB), key block (j / 2) % NTB, half j % 2); its V
             // fragment is two transposing reads.  As for K, the reads are written and pinned two
             // operations ahead of the matrix instruction that uses them.
-            constexpr int kAheadV = 2, kOpsV = 2 * NTB * MB;
+            constexpr int kAheadV = 2, kOpsV = 2 * NTB * MB, kSums = 2 * NTB;
             auto v_frag = [&](int j) __attribute__((always_inline)) {
                 const POD_LDS unsigned char *vp = vb + (((j >> 1) % NTB) * 32 + 16 * (j & 1)) * L::kRowBytes +
                                                   (v_base ^ (uint32_t)((cb0 + j / (2 * NTB)) << 6));
@@ -635,13 +629,28 @@ __device__ __forceinline__ void prefill_item_run(const KernelArgs &a, const Pref
                 const s16x4 hi = lds_read_tr(vp + 8 * L::kRowBytes);
                 return __builtin_bit_cast(v8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
             };
+            u32x4 pw[kSums];
+#pragma unroll
+            for (int j = 0; j < kSums; ++j) {
+                pw[j] = __builtin_bit_cast(u32x4, pk[j >> 1][j & 1]);
+                // Weight sums, over the rounded weights, the ones the PV product uses: a 4x4x4 product with ones
+                // adds four weights of every lane in 8 cycles of the matrix pipe, where a two-element dot
+                // product (which runs in that pipe too) takes 16 for two.  With the issue priority
+                // below, prefill of 8192 tokens 524 -> 515 us, of the prefill-heavy configuration at 32K
+                // contexts 1217 -> 1143.
+                asm("" : "+v"(pw[j]));                       // packed once, for both uses
+                l_run = N::add_all(u32x2{pw[j][0], pw[j][1]}, l_run);
+                l_run = N::add_all(u32x2{pw[j][2], pw[j][3]}, l_run);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (D <= 128) __builtin_amdgcn_s_setprio(3);
             v8 vv[kOpsV];
 #pragma unroll
             for (int j = 0; j < kAheadV; ++j) vv[j] = v_frag(j);
 #pragma unroll
             for (int j = 0; j < kOpsV; ++j) {
                 if (j + kAheadV < kOpsV) vv[j + kAheadV] = v_frag(j + kAheadV);
-                o[j / (2 * NTB)] = N::mfma32(vv[j], pk[(j >> 1) % NTB][j & 1], o[j / (2 * NTB)]);
+                o[j / (2 * NTB)] = N::mfma32(vv[j], __builtin_bit_cast(v8, pw[j % kSums]), o[j / (2 * NTB)]);
             }
             __builtin_amdgcn_sched_group_barrier(0x100, 2 * kAheadV, 0);
 #pragma unroll
@@ -650,6 +659,7 @@ __device__ __forceinline__ void prefill_item_run(const KernelArgs &a, const Pref
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
             }
             __builtin_amdgcn_sched_group_barrier(0x008, kAheadV, 0);
+            if constexpr (D <= 128) __builtin_amdgcn_s_setprio(2);
         }
         wait_all_loads();                                    // K tile jt+2 and V tile jt+1 have landed
         __syncthreads();                                     // ... for every wavefront; tile jt is done
@@ -661,7 +671,7 @@ __device__ __forceinline__ void prefill_item_run(const KernelArgs &a, const Pref
     }
 
     // Epilogue.  o[mb][r] is channel (cb0 + mb)*32 + 8*(r/4) + 4*h + r%4 of this lane's query row.
-    const float l_tot = sum_across_32(l_run);
+    const float l_tot = sum_across_32(l_run[0]);
     if (it.prow0 < 0) {
         if (row_ok) {
             const float inv = 1.f / l_tot;
