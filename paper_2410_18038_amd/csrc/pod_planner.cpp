@@ -264,6 +264,23 @@ static pod_status cut_batch(const pod_attn_params &prm, const int32_t *seq_meta,
             size_t u = 0;
             for (int q = 0; q < kXcdQueues; ++q)
                 while (next[q] < plan.pq_begin[q + 1]) place(unfilled[u++], next[q]++);
+            // Two rounds at once: workgroup b + n_cus joins workgroup b on its compute unit, and two long items
+            // there slow each other down while other units run dry.  Within an XCD the second round is
+            // therefore dealt shortest first.
+            if (n > n_cus && n <= 2 * n_cus) {
+                for (int x = 0; x < kXcdQueues; ++x) {
+                    std::vector<int> items;
+                    for (int b = x; b < n; b += kXcdQueues) items.push_back(plan.pitem_of_wg[(size_t)b]);
+                    std::stable_sort(items.begin(), items.end(), [&](int i, int j) {
+                        const PrefillItem &a = plan.pitems[(size_t)i], &b = plan.pitems[(size_t)j];
+                        return a.kv_end - a.kv_begin > b.kv_end - b.kv_begin;
+                    });
+                    const size_t first_round = std::min(items.size(), (size_t)std::max(0, (n_cus - x + kXcdQueues - 1) / kXcdQueues));
+                    std::reverse(items.begin() + (std::ptrdiff_t)first_round, items.end());
+                    size_t k = 0;
+                    for (int b = x; b < n; b += kXcdQueues) place(b, items[k++]);
+                }
+            }
         }
     }
 
