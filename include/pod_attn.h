@@ -54,7 +54,9 @@ typedef enum { POD_F16 = 0, POD_BF16 = 1 } pod_dtype;
 /* How pod_attn_forward schedules the two operations. */
 typedef enum {
     POD_MODE_FUSED = 0,         /* one launch, roles bound per workgroup at run time (Section 4.1);
-                                   a batch with one operation runs that operation's own kernel      */
+                                   a batch with one operation runs that operation's own kernel, and
+                                   under POD_POLICY_AUTO a batch whose items and decode workers are
+                                   all resident at once may bind by workgroup index instead         */
     POD_MODE_SERIAL = 1,        /* prefill kernel, then decode kernel, one stream (Section 3.1)    */
     POD_MODE_STREAMS = 2,       /* the same two kernels on two streams, joined (Section 3.1)       */
     POD_MODE_PREFILL_ONLY = 3,  /* only the prefill rows of `out` are written                      */
@@ -304,7 +306,9 @@ int32_t pod_attn_role_for_ticket(int32_t ticket, int32_t prefill_ratio, int32_t 
  *                  operation).  Actors 4w .. 4w+3 are its wavefronts while it is a decode worker:
  *                  the fixed first unit 4 * seat + v of the first seats without a claim, then one
  *                  claim per step on the decode queue the wavefront is at (its XCD's queue first,
- *                  then the others; after all eight it is done).  A workgroup switches operation once and then ends.  Entries naming an
+ *                  then the others; after all eight it is done; with units for one round of wavefronts
+ *                  or fewer all units are fixed and nobody claims).  In a plan that binds by workgroup
+ *                  index the leader's one step takes that index's prefill item or decode seat.  A workgroup switches operation once and then ends.  Entries naming an
  *                  actor that has nothing to do at that moment are skipped; when `order` is used
  *                  up, all unfinished actors run on in turn until the launch has drained.
  * Outputs (host, each may be NULL): first_role[w] 0 prefill / 1 decode; seat_of_wg[w] (untouched if

@@ -106,9 +106,12 @@ pod::KernelArgs make_args(const pod::Plan &p, const void *prefill_q, const void 
     // grid is never smaller than the number of seats, so all fixed units are run whatever
     // operation the workgroups start with.
     a.dq_begin = (const int32_t *)(ws + p.off_dq);
-    a.n_static_seats = p.n_static_seats;
+    // Units for one round of wavefronts or fewer are all run as fixed units, also the last up to three, which
+    // the plan keeps in the queues: unit 4 * seat + v on wavefront v, and no wavefront claims anything.
+    a.single_unit = a.n_dunits <= pod::kWavesPerWg * p.n_cus;
+    a.n_static_seats = a.single_unit ? p.n_dwgs : p.n_static_seats;
     a.n_dctas = ((int)p.dunits.size() + pod::kWavesPerWg - 1) / pod::kWavesPerWg;
-    a.single_unit = 0;
+    a.fixed_roles = pod::kRolesByTicket;
     a.n_prefill_rows = (int)p.n_prefill_rows;
     a.p_ratio = p.p_ratio;
     a.d_ratio = p.d_ratio;
@@ -440,6 +443,11 @@ static pod_status forward_impl(const void *prefill_q, const void *decode_q, cons
             // K/V heads 37.6 -> 34.2 us, four prompts of 100-700 tokens 69.7 -> 23.4 us, one of 8192
             // tokens 570 -> 552 us, 128 decodes at 2K-16K 811 -> 804 us.
             go(a.n_dunits == 0 ? pod::kLaunchPrefill : pod::kLaunchDecode, a, s);
+        } else if (p.fixed_roles != pod::kRolesByTicket) {
+            pod::KernelArgs c = a;
+            c.fixed_roles = p.fixed_roles;
+            c.n_dctas = c.fused_grid - c.n_pitems;
+            go(pod::kLaunchFusedCta, c, s);
         } else {
             go(pod::kLaunchFused, a, s);
         }
@@ -545,6 +553,26 @@ int32_t pod_attn_simulate_launch(const pod_attn_plan *plan, const int32_t *unit_
         case kBind: {
             if (v != 0) return false;
             const unsigned cu = (unsigned)unit_of_wg[w] & (pod::kCuSlots - 1);
+            if (p.fixed_roles != pod::kRolesByTicket) {
+                // the workgroup index says it all: one prefill item, or a decode seat
+                const int piece = pod::fixed_piece(p.fixed_roles, w, n_items, p.n_dwgs);
+                g.roles_done = 1;               // no switch of operation
+                g.first = piece < n_items ? pod::kPrefill : pod::kDecode;
+                g.xcd = (int)(cu >> 6);
+                if (first_role) first_role[w] = g.first;
+                if (g.first == pod::kPrefill) {
+                    const int item = p.pitem_of_wg[(size_t)piece];
+                    if (item_owner) { if (item_owner[item] != -1) ++owner_errors; item_owner[item] = w; }
+                    next_phase(g);
+                } else {
+                    const bool seated = piece - n_items < p.n_dwgs;
+                    g.seat = seated ? piece - n_items : -1;
+                    if (seat_of_wg) seat_of_wg[w] = g.seat;
+                    g.phase = seated ? kDecodeWaves : kEnd;
+                    for (Wave &x : g.wave) { x = Wave(); x.cq = g.xcd & (Q - 1); }
+                }
+                return true;
+            }
             const uint32_t ticket = cu_ticket[cu]++;
             g.first = pod::role_for_ticket(ticket, p.p_ratio, p.d_ratio, (int)cu);
             g.xcd = (int)(cu >> 6);
@@ -591,9 +619,11 @@ int32_t pod_attn_simulate_launch(const pod_attn_plan *plan, const int32_t *unit_
             Wave &x = g.wave[v];
             if (x.done) return false;
             auto own = [&](int unit) { if (unit_owner) { if (unit_owner[unit] != -1) ++owner_errors; unit_owner[unit] = actor; } };
-            if (!x.started && g.seat < p.n_static_seats) {
+            const bool one_round = n_units <= W * p.n_cus;
+            if (!x.started && (one_round || g.seat < p.n_static_seats)) {
                 x.started = true;
-                own(g.seat * W + v);            // the fixed first unit: no claim
+                x.done = one_round;             // nothing is left to claim
+                if (g.seat * W + v < n_units) own(g.seat * W + v);   // the fixed first unit: no claim
             } else {
                 x.started = true;
                 // one claim on the queue the wavefront is at; a used-up queue sends it to the next

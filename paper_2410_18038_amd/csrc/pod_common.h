@@ -110,6 +110,18 @@ POD_HD inline int role_for_ticket(uint32_t ticket, int p, int d, int unit = 0)
     return (t % (p + d)) < p ? kPrefill : kDecode;
 }
 
+// How the workgroups of a fused launch get their operation: by ticket (above), or, in a launch whose
+// items and decode workers all fit the chip at once, by their index, prefill items or decode seats first.
+enum RoleRule : int { kRolesByTicket = 0, kPrefillFirst = 1, kDecodeFirst = 2 };
+
+// What workgroup b does under the second rule: prefill item (of the workgroup order) below n_pitems,
+// decode seat + n_pitems from there on (workgroups beyond the last seat have nothing to do).
+POD_HD inline int fixed_piece(int rule, int b, int n_pitems, int n_dwgs)
+{
+    if (rule == kPrefillFirst) return b;
+    return b < n_dwgs ? n_pitems + b : b < n_dwgs + n_pitems ? b - n_dwgs : b;
+}
+
 // Optional execution trace: where each workgroup of an attention kernel ran, which operation it
 // took first, when it switched to the other one and how many work items it processed in each.
 struct TraceRecord {
@@ -166,7 +178,8 @@ struct KernelArgs {
     const int32_t *dq_begin;               // [kXcdQueues + 1]: decode queue q holds units dq_begin[q] .. dq_begin[q+1]-1
     int32_t n_static_seats;                // decode seats that start with four fixed units (units 0 .. 4*seats-1)
     int32_t n_dctas;                       // decode workgroups of the CTA-parallel launch: ceil(n_dunits / 4)
-    int32_t single_unit;                   // CTA-parallel launch: a decode wavefront runs its fixed unit and stops
+    int32_t single_unit;                   // a decode wavefront runs its fixed unit and stops (queues empty, or a CTA-parallel launch)
+    int32_t fixed_roles;                   // CTA-parallel kernel: a RoleRule
     int32_t p_ratio, d_ratio;
     float scale_log2;                      // softmax_scale * log2(e)
 };

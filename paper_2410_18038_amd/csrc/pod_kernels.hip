@@ -1302,7 +1302,7 @@ __global__ __launch_bounds__(kWgThreads, 2) void decode_kernel(KernelArgs a)
         if (threadIdx.x == 0)
             write_trace(a, a.n_pitems + blockIdx.x, __smid() & (kCuSlots - 1), kDecode, n_done, 0, t0, wall_clock64());
     }
-    finish_and_reset(a.hdr, &flag);
+    if (!a.single_unit) finish_and_reset(a.hdr, &flag);      // (nothing was counted)
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1565,7 +1565,7 @@ __global__ __launch_bounds__(kWgThreads) __attribute__((amdgpu_num_vgpr(kLiteVgp
         if (threadIdx.x == 0)
             write_trace(a, a.n_pitems + blockIdx.x, __smid() & (kCuSlots - 1), kDecode, n_done, 0, t_start, wall_clock64());
     }
-    finish_and_reset(a.hdr, &flag);
+    if (!a.single_unit) finish_and_reset(a.hdr, &flag);      // (nothing was counted)
 }
 
 // The prefill kernel of that configuration: the stand-alone prefill kernel, held to 208 registers
@@ -1647,6 +1647,8 @@ __global__ __launch_bounds__(kWgThreads, 2) void fused_kernel(KernelArgs a)
 // a global counter, switches operation if that counter has run past its limit, runs the one item
 // and leaves.  The persistent kernel above is the variant of Section 4.4; this one exists so that
 // the two can be timed against each other on this chip.
+// It is also the kernel of launches whose work is all resident at once (fixed_roles): operation and piece
+// of work then follow from the workgroup index, and only decode units beyond the fixed ones are claimed.
 // ------------------------------------------------------------------------------------------
 template <int DT, int D, int LAYOUT>
 __global__ __launch_bounds__(kWgThreads, 2) void fused_cta_kernel(KernelArgs a)
@@ -1655,7 +1657,15 @@ __global__ __launch_bounds__(kWgThreads, 2) void fused_cta_kernel(KernelArgs a)
     __shared__ int bind[4];                                  // role, work id, unit id, last flag
     WsHeader *hdr = a.hdr;
     const uint64_t t0 = a.trace ? wall_clock64() : 0;
-    if (threadIdx.x == 0) {
+    if (a.fixed_roles) {
+        // Everything fits the chip at once: the roles follow from the workgroup index.
+        if (threadIdx.x == 0) {
+            const int piece = fixed_piece(a.fixed_roles, blockIdx.x, a.n_pitems, a.n_dwgs);
+            bind[0] = piece < a.n_pitems ? kPrefill : kDecode;
+            bind[1] = piece < a.n_pitems ? piece : piece - a.n_pitems;
+            bind[2] = (int)(__smid() & (kCuSlots - 1));
+        }
+    } else if (threadIdx.x == 0) {
         const unsigned cu = __smid() & (kCuSlots - 1);
         const uint32_t ticket = atomicAdd(&hdr->cu_state[cu], 1u);
         int role = role_for_ticket(ticket, a.p_ratio, a.d_ratio, (int)cu);
@@ -1676,17 +1686,19 @@ __global__ __launch_bounds__(kWgThreads, 2) void fused_cta_kernel(KernelArgs a)
     int n_done = 0;
     if (role == kPrefill) {
         PrefillItem it;
-        const POD_CONST int32_t *w = (const POD_CONST int32_t *)a.pitems + 8 * (int64_t)id;
+        const POD_CONST int32_t *w = (const POD_CONST int32_t *)(a.fixed_roles ? a.pitems_by_wg : a.pitems) + 8 * (int64_t)id;
         it.req = w[0]; it.kv_head = w[1]; it.row0 = w[2]; it.n_rows = w[3];
         it.kv_begin = w[4]; it.kv_end = w[5]; it.prow0 = w[6]; it.split = w[7];
+        const uint64_t tb = a.evlog ? wall_clock64() : 0;
         prefill_item_run<DT, D, LAYOUT>(a, it, smem);
+        if (a.evlog && threadIdx.x == 0) log_event(a, kPrefill, a.fixed_roles ? a.pitem_of_wg[id] : id, tb);
         n_done = 1;
-    } else if (role == kDecode) {
+    } else if (role == kDecode && (id < a.n_dwgs || !a.fixed_roles)) {
         n_done = decode_worker_run<DT, D, LAYOUT>(a, smem, id, bind[2] >> 6);
     }
     __syncthreads();
     if (threadIdx.x == 0 && a.trace) write_trace(a, blockIdx.x, bind[2], role, n_done, 0, t0, wall_clock64());
-    finish_and_reset(hdr, &bind[3]);
+    if (!(a.fixed_roles && a.single_unit)) finish_and_reset(hdr, &bind[3]);
 }
 
 // ------------------------------------------------------------------------------------------

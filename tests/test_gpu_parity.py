@@ -306,6 +306,30 @@ def _sample_rows(batch, n_p, n_d, seed):
     return np.concatenate([rows_p[:0] if npr == 0 else rows_p, rows_d[:0] if nd == 0 else rows_d]).astype(np.int32)
 
 
+@pytest.mark.parametrize("d,q_len,decode", [
+    (128, 300, [700, 333, 90]),                  # everything fits one workgroup per unit, all units fixed, a remainder of them
+    (64, 100, [1] * 5),                          # ... and a decode worker with a single wavefront at work
+    (128, 896, [1500] * 9 + [16, 2500]),         # 14 items for 16 units: roles by index, the rest of the units claimed
+    (128, 897, [1500] * 9 + [16, 2500]),         # 16 items: roles by ticket
+    (256, 200, [1500] * 9 + [2500]),             # 256 channels, a worker on every unit: decode seats first
+    (256, 100, [70]),                            # ... and too few for that
+])
+def test_roles_by_workgroup_index_and_by_ticket(d, q_len, decode):
+    """Both sides of the planner's role rule, on a plan made for 16 compute units: the fused launch runs the
+    plan's items and units, so it gives the bits of the two kernels run one after the other, again and again."""
+    batch = wl.make_batch("roles", prefill=[(q_len, q_len + 77)], decode_kv_lens=decode, n_q_heads=4, n_kv_heads=2,
+                          head_dim=d, dtype=wl.BF16, seed=d + q_len, block_size=16, poison=float("nan"))
+    got, info = run_gpu(batch, "fused", n_compute_units=16)
+    assert np.abs(got - oracle_out(batch)).max() <= TOL[batch.dtype]
+    dev_batch = batch.to("cuda:0")
+    attn = pod.HybridAttention(dev_batch, n_compute_units=16)
+    serial = attn.forward(dev_batch, mode=pod.MODES["serial"]).clone()
+    for _ in range(3):
+        fused = attn.forward(dev_batch, out=torch.zeros_like(serial))
+        assert torch.equal(fused.view(torch.int16), serial.view(torch.int16))
+    attn.close()
+
+
 @pytest.mark.parametrize("config,index", [(2, 0), (3, 0), (4, 0)] + [(5, i) for i in range(len(wl.RATIO_SWEEP))])
 def test_full_size_batches_on_sampled_rows(config, index):
     """The configurations the benchmark times, at full size and with the default plan (the launch
