@@ -69,7 +69,8 @@ pod::KernelArgs make_args(const pod::Plan &p, const void *prefill_q, const void 
     a.dunits = (const pod::DecodeUnit *)(ws + p.off_dunits);
     a.crows = (const pod::CombineRow *)(ws + p.off_crows);
     a.n_crows = (int)p.merge_rows.size();
-    a.combine_groups = p.combine_groups;
+    a.n_crows_prefill = p.n_crows_prefill;
+    for (int op : {pod::kPrefill, pod::kDecode}) a.combine_groups[op] = p.combine_groups[op];
     a.part_o = (float *)(ws + p.off_part_o);
     a.part_ml = (float *)(ws + p.off_part_ml);
     a.kv_seq_stride = p.prm.kv_seq_stride;
@@ -385,6 +386,7 @@ static pod_status forward_impl(const void *prefill_q, const void *decode_q, cons
     // holds the rows of prefill groups first, then those of decode groups.
     pod::KernelArgs only_p = a, only_d = a;
     only_p.n_crows = p.n_crows_prefill;
+    only_d.n_crows_prefill = 0;
     only_d.crows = a.crows + p.n_crows_prefill;
     only_d.n_crows = a.n_crows - p.n_crows_prefill;
 

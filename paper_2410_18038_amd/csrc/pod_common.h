@@ -169,8 +169,8 @@ struct KernelArgs {
     int32_t block_size, max_blocks_per_seq;
     int32_t bs_shift;                      // log2(block_size) when it is a power of two, else -1
     uint32_t bs_magic;                     // ceil(2^32 / block_size) for block sizes above 1 (block_of)
-    int32_t n_crows;
-    int32_t combine_groups;                // thread groups of the combine kernel that share a row's splits
+    int32_t n_crows, n_crows_prefill;      // merged rows, and how many of them (the first ones) are prefill rows
+    int32_t combine_groups[2];             // [op]: thread groups of the combine kernel that share a row's splits
     int32_t n_pitems, n_dunits, n_dwgs;      // n_dwgs: decode worker workgroups
     int32_t n_prefill_rows;
     int32_t fused_grid;

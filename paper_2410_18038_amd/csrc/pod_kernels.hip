@@ -246,6 +246,13 @@ __device__ __forceinline__ void dma16_vaddr(uint32_t lds_addr, const void *vaddr
 }
 __device__ __forceinline__ void wait_all_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+// An item, read through the constant address space so that it and what follows from it stay in scalar registers.
+__device__ __forceinline__ PrefillItem load_item(const PrefillItem *items, int index)
+{
+    const POD_CONST int32_t *w = (const POD_CONST int32_t *)(items + index);
+    return PrefillItem{w[0], w[1], w[2], w[3], w[4], w[5], w[6], w[7]};
+}
+
 template <int DT, int D, int LAYOUT>
 __device__ __forceinline__ void prefill_item_run(const KernelArgs &a, const PrefillItem it,
                                                  unsigned char *smem)
@@ -1207,7 +1214,7 @@ __global__ __launch_bounds__(kWgThreads, 2) void prefill_kernel(KernelArgs a)
 {
     __shared__ __attribute__((aligned(16))) unsigned char smem[PrefillLds<D>::kBytes];
     const uint64_t t0 = a.trace || a.evlog ? wall_clock64() : 0;
-    prefill_item_run<DT, D, LAYOUT>(a, a.pitems_by_wg[blockIdx.x], smem);
+    prefill_item_run<DT, D, LAYOUT>(a, load_item(a.pitems_by_wg, blockIdx.x), smem);
     if (a.evlog && threadIdx.x == 0) log_event(a, kPrefill, a.pitem_of_wg[blockIdx.x], t0);
     if (a.trace && threadIdx.x == 0)
         write_trace(a, blockIdx.x, __smid() & (kCuSlots - 1), kPrefill, 1, 0, t0, wall_clock64());
@@ -1244,12 +1251,7 @@ __device__ __forceinline__ int prefill_worker_run(const KernelArgs &a, unsigned 
         q = __builtin_amdgcn_readfirstlane(slot[1]);
         if (item < 0) break;
         const uint64_t tb = a.evlog ? wall_clock64() : 0;
-        PrefillItem it;
-        {
-            const POD_CONST int32_t *w = (const POD_CONST int32_t *)a.pitems + 8 * (int64_t)item;
-            it.req = w[0]; it.kv_head = w[1]; it.row0 = w[2]; it.n_rows = w[3];
-            it.kv_begin = w[4]; it.kv_end = w[5]; it.prow0 = w[6]; it.split = w[7];
-        }
+        const PrefillItem it = load_item(a.pitems, item);
         // Of the two workgroups on a unit the hardware serves the older one's memory operations first.
         // A prefill workgroup that is the younger one beside a decode worker waits behind a stream that
         // always has the next load ready (items of 300-700 us where older ones take 120-230, chunk of 1024
@@ -1576,7 +1578,7 @@ __global__ __launch_bounds__(kWgThreads, 2) __attribute__((amdgpu_num_vgpr(kHeav
 {
     __shared__ __attribute__((aligned(16))) unsigned char smem[PrefillLds<D>::kBytes];
     const uint64_t t0 = a.trace ? wall_clock64() : 0;
-    prefill_item_run<DT, D, LAYOUT>(a, a.pitems_by_wg[blockIdx.x], smem);
+    prefill_item_run<DT, D, LAYOUT>(a, load_item(a.pitems_by_wg, blockIdx.x), smem);
     if (a.trace && threadIdx.x == 0)
         write_trace(a, blockIdx.x, __smid() & (kCuSlots - 1), kPrefill, 1, 0, t0, wall_clock64());
 }
@@ -1685,10 +1687,7 @@ __global__ __launch_bounds__(kWgThreads, 2) void fused_cta_kernel(KernelArgs a)
     const int id = __builtin_amdgcn_readfirstlane(bind[1]);
     int n_done = 0;
     if (role == kPrefill) {
-        PrefillItem it;
-        const POD_CONST int32_t *w = (const POD_CONST int32_t *)(a.fixed_roles ? a.pitems_by_wg : a.pitems) + 8 * (int64_t)id;
-        it.req = w[0]; it.kv_head = w[1]; it.row0 = w[2]; it.n_rows = w[3];
-        it.kv_begin = w[4]; it.kv_end = w[5]; it.prow0 = w[6]; it.split = w[7];
+        const PrefillItem it = load_item(a.fixed_roles ? a.pitems_by_wg : a.pitems, id);
         const uint64_t tb = a.evlog ? wall_clock64() : 0;
         prefill_item_run<DT, D, LAYOUT>(a, it, smem);
         if (a.evlog && threadIdx.x == 0) log_event(a, kPrefill, a.fixed_roles ? a.pitem_of_wg[id] : id, tb);
@@ -1708,6 +1707,8 @@ __global__ __launch_bounds__(kWgThreads, 2) void fused_cta_kernel(KernelArgs a)
 // at a time; what bounds the kernel is its chain of dependent memory round trips (row, partials, and
 // one more for every further fetch), not its bytes, so rows with many splits are shared by more groups.
 // (32 rows of 94 splits: 15.8 us with one group per row, a row list and an entry lookup before it; 5.2 now.)
+// Prefill and decode rows have their own number of groups: 32768 prefill rows of two splits beside 512 decode
+// rows of up to 15 kept half of the groups idle and fetched every partial four times, 12.1 -> 7.4 us.
 // ------------------------------------------------------------------------------------------
 template <int DT, int D>
 __global__ __launch_bounds__(kWgThreads) void combine_kernel(KernelArgs a)
@@ -1715,15 +1716,17 @@ __global__ __launch_bounds__(kWgThreads) void combine_kernel(KernelArgs a)
     using N = Num<DT>;
     constexpr int TPR = D / 4;                      // threads per group, 4 channels each
     constexpr int GPW = kWgThreads / TPR;           // groups of the workgroup
-    constexpr int U = kCombineFetch;
     __shared__ f32x4 part_acc[GPW][TPR];
     __shared__ float part_m[GPW], part_l[GPW];
     const int sub = threadIdx.x % TPR;
     const int grp = threadIdx.x / TPR;
-    const int G = a.combine_groups;                 // a power of two, at most GPW
+    // Workgroups of prefill rows come first; the two kinds of rows have their own numbers of splits.
+    const int p_blocks = (a.n_crows_prefill * a.combine_groups[kPrefill] + GPW - 1) / GPW;
+    const bool prefill = (int)blockIdx.x < p_blocks;
+    const int G = a.combine_groups[prefill ? kPrefill : kDecode];   // a power of two, at most GPW
     const int share = grp & (G - 1);                // this group's part of its row's splits
-    const int crow = (blockIdx.x * GPW + grp) / G;
-    const bool row_ok = crow < a.n_crows;
+    const int crow = prefill ? (blockIdx.x * GPW + grp) / G : a.n_crows_prefill + ((blockIdx.x - p_blocks) * GPW + grp) / G;
+    const bool row_ok = crow < (prefill ? a.n_crows_prefill : a.n_crows);
     float M = neg_inf(), lsum = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     int64_t out_row = 0;
@@ -1731,7 +1734,8 @@ __global__ __launch_bounds__(kWgThreads) void combine_kernel(KernelArgs a)
         const u32x4 w = load16(a.crows + crow);
         const int n_splits = (int)w[1], stride = (int)w[3] < 0 ? a.group : prefill_item_rows(D);
         out_row = (int64_t)((uint64_t)w[2] | (uint64_t)(w[3] & 0x7fffffffu) << 32);
-        for (int s0 = share * U; s0 < n_splits; s0 += G * U) {
+        auto merge = [&](auto count, int s0) __attribute__((always_inline)) {
+            constexpr int U = decltype(count)::value;
             float ms[U], ls[U];
             f32x4 v[U];
 #pragma unroll
@@ -1745,7 +1749,7 @@ __global__ __launch_bounds__(kWgThreads) void combine_kernel(KernelArgs a)
             float Mn = M;
 #pragma unroll
             for (int u = 0; u < U; ++u) Mn = fmaxf(Mn, ms[u]);
-            if (Mn == neg_inf()) continue;          // no split so far saw a key of this row
+            if (Mn == neg_inf()) return;            // no split so far saw a key of this row
             const float keep = fast_exp2(M - Mn);   // 0 while M is still -inf
             lsum *= keep;
             acc = acc * keep;
@@ -1756,6 +1760,14 @@ __global__ __launch_bounds__(kWgThreads) void combine_kernel(KernelArgs a)
                 acc += v[u] * wt;
             }
             M = Mn;
+        };
+        // Prefill rows have two splits as a rule, and fetching eight of two is four requests for one.  (Decode
+        // rows differ from one to the next: two ways through one wavefront would be two round trips.)
+        if (prefill && n_splits <= 2) {
+            if (share == 0) merge(std::integral_constant<int, 2>{}, 0);
+        } else {
+            for (int s0 = share * kCombineFetch; s0 < n_splits; s0 += G * kCombineFetch)
+                merge(std::integral_constant<int, kCombineFetch>{}, s0);
         }
     }
     if (G > 1) {
@@ -1824,8 +1836,11 @@ static hipError_t launch_variant(int which, const KernelArgs &a, hipStream_t str
         break;
     case kLaunchCombine:
         if (a.n_crows > 0) {
-            const int rows_per_wg = kWgThreads / (D / 4) / a.combine_groups;
-            combine_kernel<DT, D><<<dim3((a.n_crows + rows_per_wg - 1) / rows_per_wg), dim3(kWgThreads), 0, stream>>>(a);
+            constexpr int groups = kWgThreads / (D / 4);       // thread groups of a workgroup
+            const int n_decode_rows = a.n_crows - a.n_crows_prefill;
+            const int blocks = (a.n_crows_prefill * a.combine_groups[kPrefill] + groups - 1) / groups +
+                               (n_decode_rows * a.combine_groups[kDecode] + groups - 1) / groups;
+            combine_kernel<DT, D><<<dim3(blocks), dim3(kWgThreads), 0, stream>>>(a);
         }
         break;
     default:

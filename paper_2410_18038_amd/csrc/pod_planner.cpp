@@ -438,9 +438,10 @@ static pod_status cut_batch(const pod_attn_params &prm, const int32_t *seq_meta,
 
     // A group of the combine kernel fetches kCombineFetch splits at a time; as many groups share a row as
     // its splits need to be fetched at once, as far as a workgroup has groups.
-    while (plan.combine_groups < kWgThreads / (prm.head_dim / 4) &&
-           plan.combine_groups * kCombineFetch < std::max(plan.max_psplits, plan.max_dsplits))
-        plan.combine_groups *= 2;
+    for (int op : {kPrefill, kDecode})
+        while (plan.combine_groups[op] < kWgThreads / (prm.head_dim / 4) &&
+               plan.combine_groups[op] * kCombineFetch < (op == kPrefill ? plan.max_psplits : plan.max_dsplits))
+            plan.combine_groups[op] *= 2;
 
     // The ratio compares workgroup counts as the paper does (Section 4.1): decode work counts as the
     // workgroups it would fill at one wavefront per unit, up to one resident round.

@@ -27,7 +27,7 @@ struct Plan {
     std::vector<CombineEntry> centries;
     std::vector<int32_t> crows;             // (entry, row) pairs, prefill entries first
     std::vector<CombineRow> merge_rows;     // the same rows as the combine kernel reads them
-    int combine_groups = 1;                 // thread groups that share a row's splits
+    int combine_groups[2] = {1, 1};         // [op]: thread groups that share a row's splits
     int n_crows_prefill = 0;
     int64_t n_prefill_rows = 0;
     int64_t n_partial_rows = 0;
