@@ -178,7 +178,7 @@ struct KernelArgs {
     const int32_t *dq_begin;               // [kXcdQueues + 1]: decode queue q holds units dq_begin[q] .. dq_begin[q+1]-1
     int32_t n_static_seats;                // decode seats that start with four fixed units (units 0 .. 4*seats-1)
     int32_t n_dctas;                       // decode workgroups of the CTA-parallel launch: ceil(n_dunits / 4)
-    int32_t single_unit;                   // a decode wavefront runs its fixed unit and stops (queues empty, or a CTA-parallel launch)
+    int32_t single_unit;                   // a decode wavefront runs its fixed unit and claims none, whatever the queues hold
     int32_t fixed_roles;                   // CTA-parallel kernel: a RoleRule
     int32_t p_ratio, d_ratio;
     float scale_log2;                      // softmax_scale * log2(e)

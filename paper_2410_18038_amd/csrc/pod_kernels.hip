@@ -1374,7 +1374,9 @@ __global__ __launch_bounds__(kWgThreads) __attribute__((amdgpu_num_vgpr(kLiteVgp
     const uint32_t k_src0 = (uint32_t)(n16 * tok_bytes + b4 * 16);
 
     // ---- unit claims (the protocol of the decode worker: fixed first units, then the queues) ----
-    int cq = __builtin_amdgcn_readfirstlane((int)(__smid() >> 6)) & (kXcdQueues - 1), tried = 0;
+    // With single_unit the queues count as used up: units that the plan keeps there run as fixed units.
+    int cq = __builtin_amdgcn_readfirstlane((int)(__smid() >> 6)) & (kXcdQueues - 1);
+    int tried = a.single_unit ? kXcdQueues : 0;
     auto claim_unit = [&]() __attribute__((always_inline)) -> int {
         while (tried < kXcdQueues) {
             const int q0 = dq[cq], q1 = dq[cq + 1];

@@ -605,6 +605,29 @@ def test_prefill_heavy_configuration_places_three_workgroups_on_every_unit():
     attn.close()
 
 
+@pytest.mark.parametrize("mode", ["fused_heavy", "decode_only_lite", "fused", "fused_cta", "serial", "decode_only"])
+@pytest.mark.parametrize("hkv,lens", [(1, [70] * 13), (3, [900, 50, 1000, 64, 3]), (5, [40]), (1, [6000])])
+def test_one_round_of_units_is_run_once_and_leaves_the_counters_zero(mode, hkv, lens):
+    """A plan with units for one round of wavefronts whose number is no multiple of four keeps the last ones in
+    the queues, and every decode kernel runs them as fixed units: each unit is logged once per launch, and the
+    counters at the head of the workspace (1024 tickets, then 20 counters on 128-byte lines) stay zero."""
+    batch = wl.make_batch(f"one-round-{hkv}", prefill=[(70, 200)], decode_kv_lens=lens, n_q_heads=4 * hkv, n_kv_heads=hkv,
+                          head_dim=128, dtype=wl.BF16, seed=55 + hkv, block_size=16)
+    dev_batch = batch.to("cuda:0")
+    attn = pod.HybridAttention(dev_batch)
+    assert attn.info.n_decode_units % 4 != 0 and attn.info.n_decode_units <= 4 * attn.info.n_compute_units
+    first = attn.ws_ptr - attn.workspace.data_ptr()
+    attn.enable_event_log()
+    for _ in range(3):
+        out = attn.forward(dev_batch, mode=pod.MODES[mode])
+        ev = attn.read_event_log()
+        assert np.sort(ev["item"][ev["kind"] == 1]).tolist() == list(range(attn.info.n_decode_units))
+        assert not attn.workspace[first:first + 4 * 1024 + 20 * 128].any()
+    rows = slice(batch.n_prefill_rows, None)
+    assert np.abs(out.to(torch.float64).cpu().numpy()[rows] - oracle_out(batch)[rows]).max() <= TOL[batch.dtype]
+    attn.close()
+
+
 def test_prefill_heavy_configuration_with_many_short_units_and_long_contexts():
     """The light decode kernel's own claim path: hundreds of units of 1..3 steps beside a few long
     ones on a plan made for two compute units (every wavefront runs through many units, empties its
