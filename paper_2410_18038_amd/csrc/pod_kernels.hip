@@ -749,9 +749,13 @@ template <int D, int LAYOUT> struct DecodeRing {
     // (6.1 -> 6.3 TB/s going from 5 slots to 2 on 64 requests x 32 heads x 4096 keys with eight
     // streaming wavefronts per unit; with the four there are now, 2, 3 and 4 slots measure the
     // same) and for the prefill role running beside it (its tile loads wait in the same queues).
-    // The price: a wavefront alone on the chip streams 10.7 instead of 12.8 GB/s.  The any-block-size layout looks up block ids with vector loads before each
-    // step and gets one more slot to cover them; D = 64 slots are half the size.
-    static constexpr int kDepth = D >= 128 ? (LAYOUT == kLayoutPagedAny ? 3 : 2) : 4;
+    // The price: a wavefront alone on the chip streams 10.7 instead of 12.8 GB/s.  The any-block-size
+    // layout looks up block ids with vector loads before each step and gets one more slot to cover them;
+    // D = 64 slots are half the size.  At D = 256 that slot does not fit the registers beside a unit's
+    // epilogue: with it 38-65 registers were spilled in bf16 and 64 decodes at 2K-8K (16 / 8 heads, blocks
+    // of one key) took 1909 us, 1032 without; beside a chunk of 1024 1936 and 1075; 4 decodes 65 and 35.
+    // (fp16, where three slots just fit: 997 and 994; 1056 and 1053; 38.9 and 34.6.)
+    static constexpr int kDepth = D >= 128 ? (LAYOUT == kLayoutPagedAny && D == 128 ? 3 : 2) : 4;
 };
 
 // Placed right after a branch on a per-lane condition inside code that keeps wavefront-uniform
