@@ -25,6 +25,65 @@ std::string fmt(const char *f, long long a = 0, long long b = 0, long long c = 0
 // Up to this many keys per wavefront the decode work is cut into one round of equal units.
 constexpr int kOneRoundShare = 320;
 
+// Keys of the longest decode unit of the automatic cut: about 1 MB of K/V (see "decode units" below).
+int longest_unit(int head_dim) { return 2048 * 128 / std::max(128, head_dim); }
+constexpr int kLongestUnit = 2048;           // over all head_dims
+
+// Where the tables lie in the workspace, given their lengths; returns the bytes it takes.
+size_t lay_out(Plan &plan, size_t n_pitems, size_t n_dunits, size_t n_merge_rows, int64_t n_partial_rows)
+{
+    size_t off = align256(sizeof(WsHeader));
+    plan.off_pitems = off;   off = align256(off + n_pitems * sizeof(PrefillItem));
+    plan.off_pitems_by_wg = off; off = align256(off + n_pitems * sizeof(PrefillItem));
+    plan.off_pitem_of_wg = off; off = align256(off + n_pitems * sizeof(int32_t));
+    plan.off_dunits = off;   off = align256(off + n_dunits * sizeof(DecodeUnit));
+    plan.off_crows = off;    off = align256(off + n_merge_rows * sizeof(CombineRow));
+    plan.off_dq = off;       off = align256(off + sizeof plan.dq_begin);
+    plan.off_part_o = off;   off = align256(off + (size_t)n_partial_rows * plan.prm.head_dim * sizeof(float));
+    plan.off_part_ml = off;  off = align256(off + (size_t)n_partial_rows * 2 * sizeof(float));
+    return off;
+}
+
+// First keys of the pieces a request of kv_len keys is cut into, and kv_len behind them.  One round of units:
+// equal pieces of at most `chunk` keys.  A length given by the caller: the same, except that the last piece is
+// cut again into a half and two quarters when those are still at least 128 keys (a request that fits one piece
+// stays whole and needs no merge).  Otherwise a taper: pieces of at most `chunk` keys over the first half of the
+// request, and a second half in pieces that halve down to max(chunk / 4, shortest).  Units are claimed
+// longest first, so the short pieces are what is left at the end of a launch, when the wavefronts that
+// are still busy decide when it ends.
+enum class Cut { kEqual, kGiven, kTaper };
+void cut_request(int kv_len, int chunk, int shortest, Cut how, std::vector<int> &cuts)
+{
+    cuts.clear();
+    const int last = round_up(std::max(chunk / 4, shortest), kDecodeStep);     // shortest piece of a taper
+    if (how == Cut::kTaper && kv_len > chunk + last / 2) {
+        const int tail = kv_len / 2 >= 2 * last ? kv_len / 2 : 0;
+        const int big = kv_len - tail, piece = round_up(ceil_div(big, ceil_div(big, chunk)), kDecodeStep);
+        int t = 0;
+        for (; t < big; t += piece) cuts.push_back(t);
+        for (t = std::min(t, kv_len); t < kv_len;) {
+            cuts.push_back(t);
+            const int left = kv_len - t, half = std::min(chunk, left / 2 / kDecodeStep * kDecodeStep);
+            t += half >= last ? half : left >= 2 * last ? last : left;
+        }
+    } else if (how == Cut::kTaper) {
+        cuts.push_back(0);
+    } else {
+        const int tps = round_up(ceil_div(kv_len, ceil_div(kv_len, chunk)), kDecodeStep);
+        for (int t = 0; t < kv_len; t += tps) cuts.push_back(t);
+    }
+    if (how == Cut::kGiven) {
+        const int t_last = cuts.back(), len = kv_len - t_last;
+        const int quarter = round_up(len / 4, kDecodeStep);
+        const int half = (len - 2 * quarter) / kDecodeStep * kDecodeStep;    // cuts stay multiples of a step
+        if (cuts.size() >= 2 && quarter >= 128 && half > 0 && half + quarter < len) {
+            cuts.push_back(t_last + half);
+            cuts.push_back(t_last + half + quarter);
+        }
+    }
+    cuts.push_back(kv_len);
+}
+
 // Decode units when every request is cut into pieces of `chunk` keys.
 int64_t units_of_length(const pod_attn_params &prm, const int32_t *seq_meta, int chunk)
 {
@@ -55,11 +114,8 @@ void role_ratio(int policy, int n_prefill_wgs, int n_decode_wgs, int &p, int &d)
     d = std::max(d, 1);
 }
 
-// Longest decode unit of the automatic cut: about 1 MB of K/V (see "decode units" below).
-static int longest_unit(int head_dim) { return 2048 * 128 / std::max(128, head_dim); }
-
-static pod_status cut_batch(const pod_attn_params &prm, const int32_t *seq_meta, int n_cus, int unit_cap, Plan &plan,
-                            std::string &err)
+pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n_cus, Plan &plan,
+                      std::string &err)
 {
     // ---- parameters --------------------------------------------------------------------
     if (prm.n_prefill < 0 || prm.n_decode < 0) { err = "negative request count"; return POD_ERR_INVALID_ARG; }
@@ -290,6 +346,7 @@ static pod_status cut_batch(const pod_attn_params &prm, const int32_t *seq_meta,
         for (const PrefillItem &it : plan.pitems) longest_item = std::max(longest_item, it.kv_end - it.kv_begin);
         const bool one_round = prm.decode_chunk <= 0 && share <= kOneRoundShare;
         const int shortest = std::max(64, 8 * group);    // a unit's partial rows stay below 1/8 of its K/V bytes
+        std::vector<int> cuts;
         int chunk;
         if (given_chunk > 0) {
             chunk = given_chunk;
@@ -317,10 +374,31 @@ static pod_status cut_batch(const pod_attn_params &prm, const int32_t *seq_meta,
             // 2592 keys of 256 channels: 464 against 483).  us per call, pieces of a quarter share or 768 keys
             // before: 8 decodes 62.6 -> 59.6, 512 + 16 decodes 140.7 -> 135.9, 256 channels 473 -> 464,
             // 15 / 5 heads 95 -> 86, 84 decodes at 0.5K-1K 66.8 -> 57.7.
-            chunk = round_up((int)std::min<int64_t>(std::max<int64_t>(share, shortest), unit_cap), kDecodeStep);
+            auto chunk_of = [&](int cap) { return round_up((int)std::min<int64_t>(std::max<int64_t>(share, shortest), cap), kDecodeStep); };
+            const int coarse = chunk_of(kLongestUnit);
+            chunk = chunk_of(longest_unit(prm.head_dim));
+            // Shorter units stream faster there but make more partial rows.  Where those are what keeps a
+            // batch out of the library's own scratch, it is cut at 2048 keys.
+            if (chunk < coarse) {
+                size_t merged = 0;
+                for (const CombineEntry &c : plan.centries) merged += (size_t)c.n_rows;
+                auto bytes_at = [&](int length) {
+                    size_t n_units = 0, n_rows = merged;
+                    int64_t n_partials = next_prow;
+                    for (int r = prm.n_prefill; r < n_req; ++r) {
+                        cut_request(seq_meta[4 * r + 2], length, shortest, Cut::kTaper, cuts);
+                        const size_t s = cuts.size() - 1;
+                        n_units += s * (size_t)prm.n_kv_heads;
+                        if (s > 1) { n_rows += (size_t)prm.n_q_heads; n_partials += (int64_t)s * prm.n_q_heads; }
+                    }
+                    return lay_out(plan, plan.pitems.size(), n_units, n_rows, n_partials);
+                };
+                if (bytes_at(chunk) > POD_ATTN_STATIC_SCRATCH_BYTES && bytes_at(coarse) <= POD_ATTN_STATIC_SCRATCH_BYTES)
+                    chunk = coarse;
+            }
         }
         plan.decode_chunk = chunk;
-        std::vector<int> cuts;
+        const Cut how = given_chunk > 0 ? Cut::kGiven : one_round ? Cut::kEqual : Cut::kTaper;
         {
             size_t n_est = 0;
             for (int r = prm.n_prefill; r < n_req; ++r)
@@ -329,42 +407,7 @@ static pod_status cut_batch(const pod_attn_params &prm, const int32_t *seq_meta,
             plan.centries.reserve(plan.centries.size() + (size_t)prm.n_decode * prm.n_kv_heads);
         }
         for (int r = prm.n_prefill; r < n_req; ++r) {
-            const int kv_len = seq_meta[4 * r + 2];
-            const int s = ceil_div(kv_len, chunk);
-            const int tps = round_up(ceil_div(kv_len, s), kDecodeStep);
-            // Token ranges of the request.  With a length given by the caller: equal pieces of tps keys,
-            // except that the last piece is cut again into a half and two quarters when those are
-            // still at least 128 keys (a request that fits one piece stays whole and needs no merge).
-            // Units are claimed longest first, so the short pieces are what is left at the end of
-            // a launch, when the wavefronts that are still busy decide when it ends.
-            cuts.clear();
-            const bool taper = prm.decode_chunk <= 0 && !one_round;
-            const int last = round_up(std::max(chunk / 4, shortest), kDecodeStep);     // shortest piece of a taper
-            if (taper && kv_len > chunk + last / 2) {
-                const int tail = kv_len / 2 >= 2 * last ? kv_len / 2 : 0;
-                const int big = kv_len - tail, piece = round_up(ceil_div(big, ceil_div(big, chunk)), kDecodeStep);
-                int t = 0;
-                for (; t < big; t += piece) cuts.push_back(t);
-                for (t = std::min(t, kv_len); t < kv_len;) {
-                    cuts.push_back(t);
-                    const int left = kv_len - t, half = std::min(chunk, left / 2 / kDecodeStep * kDecodeStep);
-                    t += half >= last ? half : left >= 2 * last ? last : left;
-                }
-            } else if (taper) {
-                cuts.push_back(0);
-            } else {
-                for (int t = 0; t < kv_len; t += tps) cuts.push_back(t);
-            }
-            if (prm.decode_chunk > 0) {
-                const int t_last = cuts.back(), len = kv_len - t_last;
-                const int quarter = round_up(len / 4, kDecodeStep);
-                const int half = (len - 2 * quarter) / kDecodeStep * kDecodeStep;    // cuts stay multiples of a step
-                if (cuts.size() >= 2 && quarter >= 128 && half > 0 && half + quarter < len) {
-                    cuts.push_back(t_last + half);
-                    cuts.push_back(t_last + half + quarter);
-                }
-            }
-            cuts.push_back(kv_len);
+            cut_request(seq_meta[4 * r + 2], chunk, shortest, how, cuts);
             const int s_eff = (int)cuts.size() - 1;
             for (int kvh = 0; kvh < prm.n_kv_heads; ++kvh) {
                 int64_t prow_base = -1;
@@ -495,33 +538,8 @@ static pod_status cut_batch(const pod_attn_params &prm, const int32_t *seq_meta,
     }
 
     // ---- workspace layout --------------------------------------------------------------
-    size_t off = align256(sizeof(WsHeader));
-    plan.off_pitems = off;   off = align256(off + plan.pitems.size() * sizeof(PrefillItem));
-    plan.off_pitems_by_wg = off; off = align256(off + plan.pitems_by_wg.size() * sizeof(PrefillItem));
-    plan.off_pitem_of_wg = off; off = align256(off + plan.pitem_of_wg.size() * sizeof(int32_t));
-    plan.off_dunits = off;   off = align256(off + plan.dunits.size() * sizeof(DecodeUnit));
-    plan.off_crows = off;    off = align256(off + plan.merge_rows.size() * sizeof(CombineRow));
-    plan.off_dq = off;       off = align256(off + sizeof plan.dq_begin);
-    plan.off_part_o = off;   off = align256(off + (size_t)plan.n_partial_rows * prm.head_dim * sizeof(float));
-    plan.off_part_ml = off;  off = align256(off + (size_t)plan.n_partial_rows * 2 * sizeof(float));
-    plan.ws_bytes = off;
+    plan.ws_bytes = lay_out(plan, plan.pitems.size(), plan.dunits.size(), plan.merge_rows.size(), plan.n_partial_rows);
     return POD_OK;
-}
-
-pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n_cus, Plan &plan,
-                      std::string &err)
-{
-    constexpr int kOneCapForAll = 2048;
-    const int cap = longest_unit(prm.head_dim);
-    pod_status st = cut_batch(prm, seq_meta, n_cus, cap, plan, err);
-    // Wide heads are cut at 1024 keys because that streams 4 % faster, but it doubles their partial rows.
-    // Where those are what keeps a batch out of the library's own scratch, it is cut at 2048 keys.
-    if (st == POD_OK && cap < kOneCapForAll && prm.decode_chunk <= 0 && plan.ws_bytes > POD_ATTN_STATIC_SCRATCH_BYTES) {
-        Plan coarse;
-        if (cut_batch(prm, seq_meta, n_cus, kOneCapForAll, coarse, err) == POD_OK && coarse.ws_bytes <= POD_ATTN_STATIC_SCRATCH_BYTES)
-            plan = std::move(coarse);
-    }
-    return st;
 }
 
 }  // namespace pod
