@@ -388,7 +388,7 @@ static pod_status forward_impl(const void *prefill_q, const void *decode_q, cons
     hipError_t e = hipSuccess;
     auto go = [&](int which, const pod::KernelArgs &args, hipStream_t on) {
         if (which == pod::kLaunchCombine && no_combine) return;
-        if (e == hipSuccess) e = pod::launch(which, args, dt, hd, paged, on);
+        if (e == hipSuccess) e = pod::launch(which, args, dt, hd, on);
     };
 
     // The combine pass only touches rows whose partials were produced in this call; the row list

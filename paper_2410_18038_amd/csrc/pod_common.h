@@ -41,6 +41,14 @@ enum Role : int { kPrefill = 0, kDecode = 1, kNone = -1 };
 // per load); paged, any (a block id per lane, looked up with vector loads that the K/V loads wait for).
 // Blocks of 24 keys, 15 / 5 heads, 2 chunks + 40 decodes at 0.5K-7K: 199 us by lane, 94 by row.
 enum Layout : int { kLayoutContiguous = 0, kLayoutPaged16 = 1, kLayoutPagedRows = 2, kLayoutPagedAny = 3 };
+inline Layout cache_layout(int block_size, int head_dim, int n_kv_heads)
+{
+    if (block_size <= 0) return kLayoutContiguous;
+    // (byte offsets inside a block are 32 bits wide there)
+    const bool small = (int64_t)block_size * n_kv_heads * head_dim * 2 < (int64_t)1 << 32;
+    if (block_size >= 16 && (block_size & (block_size - 1)) == 0 && small) return kLayoutPaged16;
+    return block_size % (kWaveSize / (head_dim / 8)) == 0 ? kLayoutPagedRows : kLayoutPagedAny;
+}
 
 // One prefill work item: a block of packed query rows of one K/V head over a key range.
 // Packed row R of a request stands for token R / group, query head kv_head * group + R % group,

@@ -1887,13 +1887,9 @@ __global__ void clear_header_kernel(WsHeader *hdr)
         p[i] = 0u;
 }
 
-hipError_t launch(int which, const KernelArgs &a, int dtype, int head_dim, bool paged, hipStream_t stream)
+hipError_t launch(int which, const KernelArgs &a, int dtype, int head_dim, hipStream_t stream)
 {
-    // The block-wise path wants power-of-two blocks of at least 16 keys whose byte size fits 32 bits;
-    // the row-wise one, blocks that every load instruction stays inside of.
-    const bool block_wise = a.bs_shift >= 4 && a.block_elems * 2 < (1ll << 32);
-    const bool row_wise = a.block_size > 1 && a.block_size % (kWaveSize / (head_dim / 8)) == 0;
-    const int layout = !paged ? kLayoutContiguous : block_wise ? kLayoutPaged16 : row_wise ? kLayoutPagedRows : kLayoutPagedAny;
+    const int layout = cache_layout(a.block_size, head_dim, a.n_kv_heads);
     if (dtype == 0 && head_dim == 128) return launch_layout<0, 128>(which, a, layout, stream);
     if (dtype == 0 && head_dim == 64) return launch_layout<0, 64>(which, a, layout, stream);
     if (dtype == 1 && head_dim == 128) return launch_layout<1, 128>(which, a, layout, stream);

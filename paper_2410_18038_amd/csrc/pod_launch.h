@@ -9,8 +9,8 @@ namespace pod {
 enum LaunchKind : int { kLaunchPrefill = 0, kLaunchDecode = 1, kLaunchFused = 2, kLaunchCombine = 3, kLaunchFusedCta = 4,
                         kLaunchPrefillHeavy = 5, kLaunchDecodeLite = 6 };
 
-// Enqueue one kernel of the given kind for (dtype, head_dim, layout) on `stream`.
-hipError_t launch(int which, const KernelArgs &a, int dtype, int head_dim, bool paged, hipStream_t stream);
+// Enqueue one kernel of the given kind for (dtype, head_dim, the cache's layout) on `stream`.
+hipError_t launch(int which, const KernelArgs &a, int dtype, int head_dim, hipStream_t stream);
 // Zero the counters at the head of a workspace.
 hipError_t clear_header(WsHeader *hdr, hipStream_t stream);
 

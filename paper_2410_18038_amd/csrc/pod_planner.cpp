@@ -25,9 +25,18 @@ std::string fmt(const char *f, long long a = 0, long long b = 0, long long c = 0
 // Up to this many keys per wavefront the decode work is cut into one round of equal units.
 constexpr int kOneRoundShare = 320;
 
-// Keys of the longest decode unit of the automatic cut: about 1 MB of K/V (see "decode units" below).
-int longest_unit(int head_dim) { return 2048 * 128 / std::max(128, head_dim); }
-constexpr int kLongestUnit = 2048;           // over all head_dims
+// Keys of the longest decode unit of the automatic cut: about 1 MB of K/V (see "decode units" below).  Where
+// block ids are looked up per lane a unit takes two to four times as long (the lookups are a second memory round
+// trip in every step, and what they cost differs between wavefronts), so units are shorter to even that out.  us per
+// call at 512 / 768 / 1024 / 2048 keys, blocks of one key: 32 decodes at 1K-4K of 32 / 32 heads 442 / 439 / 447 /
+// 480; 64 at 2K-8K, 32 / 8 heads 479 / 485 / 493 / 514, of 64 channels 236 / 238 / 241 / 245; 16 at 4K-16K beside
+// 512 tokens 302 / 304 / 352 / 319; 256 channels beside 1024 tokens 1029 / 1042 / 1063 / 1114.  768 makes half of
+// the partial rows of 512.  (With blocks of 16 and 24 keys the same sizes are best between 1024 and 2048.)
+int longest_unit(Layout layout, int head_dim)
+{
+    return layout == kLayoutPagedAny ? 768 : 2048 * 128 / std::max(128, head_dim);
+}
+constexpr int kLongestUnit = 2048;           // over all of them
 
 // Where the tables lie in the workspace, given their lengths; returns the bytes it takes.
 size_t lay_out(Plan &plan, size_t n_pitems, size_t n_dunits, size_t n_merge_rows, int64_t n_partial_rows)
@@ -376,7 +385,7 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
             // 15 / 5 heads 95 -> 86, 84 decodes at 0.5K-1K 66.8 -> 57.7.
             auto chunk_of = [&](int cap) { return round_up((int)std::min<int64_t>(std::max<int64_t>(share, shortest), cap), kDecodeStep); };
             const int coarse = chunk_of(kLongestUnit);
-            chunk = chunk_of(longest_unit(prm.head_dim));
+            chunk = chunk_of(longest_unit(cache_layout(prm.block_size, prm.head_dim, prm.n_kv_heads), prm.head_dim));
             // Shorter units stream faster there but make more partial rows.  Where those are what keeps a
             // batch out of the library's own scratch, it is cut at 2048 keys.
             if (chunk < coarse) {

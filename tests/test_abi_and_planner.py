@@ -607,6 +607,18 @@ def test_automatic_decode_cuts_cover_every_token(hkv, group, lens):
         assert info.n_combine == 0
 
 
+@pytest.mark.parametrize("d,block_size,longest", [
+    (128, 0, 2048), (128, 16, 2048), (128, 24, 2048), (128, 4, 2048), (128, 1, 768), (128, 3, 768), (128, 6, 768),
+    (64, 8, 2048), (64, 4, 768), (64, 12, 768), (256, 2, 1024), (256, 16, 1024), (256, 1, 768), (256, 5, 768)])
+def test_longest_decode_unit_follows_the_cache_layout(d, block_size, longest):
+    """Blocks that are no multiple of the rows of a load (8, 4, 2 at 64, 128, 256 channels) are cut finer."""
+    prm, meta = meta_only("layouts", [], [16384] * 32, hq=16, hkv=8, d=d, block_size=block_size)
+    prm.max_blocks_per_seq = 16384
+    assert coverage_check(prm, meta).decode_chunk == longest
+    prm.decode_chunk = 4096                      # a given length is taken as it is
+    assert coverage_check(prm, meta).decode_chunk == 4096
+
+
 @pytest.mark.parametrize("n_decode,kv_len,hq,hkv", [(200, 25163, 16, 8), (96, 56519, 16, 8), (240, 53884, 8, 2)])
 def test_wide_heads_are_cut_coarser_where_finer_cuts_miss_the_static_scratch(n_decode, kv_len, hq, hkv):
     prm, meta = meta_only("wide", [], [kv_len] * n_decode, hq=hq, hkv=hkv, d=256)
