@@ -1755,13 +1755,15 @@ __global__ __launch_bounds__(kWgThreads) void combine_kernel(KernelArgs a)
             float Mn = M;
 #pragma unroll
             for (int u = 0; u < U; ++u) Mn = fmaxf(Mn, ms[u]);
-            if (Mn == neg_inf()) return;            // no split so far saw a key of this row
-            const float keep = fast_exp2(M - Mn);   // 0 while M is still -inf
+            // As long as no split saw a key of this row all weights are 0.  (Splits whose scores are all NaN have
+            // a maximum of -inf as well, and their NaN sums have to reach the result.)
+            const float base = Mn == neg_inf() ? 0.f : Mn;
+            const float keep = fast_exp2(M - base); // 0 while M is still -inf
             lsum *= keep;
             acc = acc * keep;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const float wt = fast_exp2(ms[u] - Mn);  // 0 for a split that saw no key
+                const float wt = fast_exp2(ms[u] - base);  // 0 for a split that saw no key
                 lsum += ls[u] * wt;
                 acc += v[u] * wt;
             }

@@ -133,6 +133,24 @@ def test_split_kv_paths(mode, block_size, d):
     assert info.max_prefill_splits > 1 and info.max_decode_splits > 1
 
 
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("keys", [(0, 512), (512, 1024), (640, 700), (1000, 1010), (1990, 2000), (0, 2000)])
+def test_nan_scores_of_whole_splits_reach_the_result(d, keys):
+    """Every row that sees a key whose scores are NaN is NaN, and no other row, whichever of its splits (64 to 128
+    keys each, merged eight at a time by several thread groups) hold such keys and nothing else: the running
+    maximum of such a split is -inf, like that of a split that saw no key."""
+    batch = wl.make_batch(f"nan-d{d}", prefill=[(1, 1990), (60, 1030)], decode_kv_lens=[2000, 300], n_q_heads=4, n_kv_heads=2,
+                          head_dim=d, dtype=wl.F16, seed=17, block_size=0)
+    rows = [int(batch.seq_meta[r][3]) for r in (0, 1, 2)]                        # the long requests
+    batch.k_cache[rows, keys[0]:keys[1]] = float("nan")
+    want = oracle_out(batch)
+    got, info = run_gpu(batch, decode_chunk=64, prefill_split_len=64, max_prefill_waves=1000)
+    assert info.max_decode_splits > 24 and info.max_prefill_splits > 8
+    assert (np.isnan(got) == np.isnan(want)).all()
+    seen = ~np.isnan(want)
+    assert np.abs(got[seen] - want[seen]).max() <= TOL[batch.dtype]
+
+
 @pytest.mark.parametrize("block_size", [0, 16])
 def test_many_requests_of_both_kinds(block_size):
     """Forty prefill chunks (1..300 new tokens over 0..900 cached ones) and 1500 decodes (1..700
