@@ -142,7 +142,8 @@ typedef struct {
     int32_t decode_chunk;       /* tokens per decode unit actually chosen                        */
     int32_t prefill_ratio;      /* roles per compute unit, prefill : decode                      */
     int32_t decode_ratio;
-    int32_t fused_grid;         /* workgroups of the fused launch (persistent, <= 2 per unit)    */
+    int32_t fused_grid;         /* workgroups of the fused launch (persistent, <= 2 per unit); with
+                                   prefill requests alone the launch has n_prefill_items instead  */
     int32_t n_compute_units;
     int64_t n_prefill_rows;     /* sum of q_len over prefill requests                            */
     int64_t n_partial_rows;     /* rows of fp32 partial output held in the workspace             */
@@ -185,7 +186,8 @@ pod_status pod_attn_plan_info_get(const pod_attn_plan *plan, pod_attn_plan_info 
  * 1 decode), work items done in the first operation, work items done after switching} followed by
  * three uint64 device timestamps (100 MHz): begin, switch of operation, end, and 8 bytes of
  * padding.  Prefill items are counted per workgroup, decode units per leading wavefront.  The
- * stand-alone kernels write one record per prefill item, then one per decode workgroup.
+ * stand-alone kernels (also in the fused mode, when the batch has one operation) write one record
+ * per prefill item, then one per decode workgroup.
  */
 pod_status pod_attn_plan_set_trace(pod_attn_plan *plan, void *trace, size_t trace_bytes);
 

@@ -398,8 +398,11 @@ class HybridAttention:
         pod_attn_plan_set_trace(self.plan, self.trace.data_ptr(), self.trace.numel())
 
     def read_trace(self) -> np.ndarray:
+        """Records of the last fused launch: one per workgroup.  A batch of prompts alone runs the prefill
+        kernel there, which has a workgroup per item."""
         self.torch.cuda.synchronize()
-        return self.trace.cpu().numpy().view(TRACE_DTYPE)[: self.info.fused_grid].copy()
+        n = self.info.fused_grid if self.info.n_decode_units > 0 else self.info.n_prefill_items
+        return self.trace.cpu().numpy().view(TRACE_DTYPE)[:n].copy()
 
     def disable_trace(self):
         pod_attn_plan_set_trace(self.plan, 0, 0)

@@ -315,6 +315,25 @@ def test_batches_with_one_operation(prefill, decode):
     attn.close()
 
 
+@pytest.mark.parametrize("prefill,decode", [([(700, 900), (300, 300)], []), ([], [500] * 40 + [33, 1]), ([(700, 900)], [500, 33])])
+def test_trace_has_a_record_of_every_workgroup_of_the_fused_mode(prefill, decode):
+    """Whatever kernel the fused mode runs: no workgroup without a record, and all items in the records."""
+    batch = wl.make_batch("trace", prefill=prefill, decode_kv_lens=decode, n_q_heads=8, n_kv_heads=2, head_dim=128,
+                          dtype=wl.BF16, seed=103, block_size=16, device="cuda:0")
+    attn = pod.HybridAttention(batch, n_compute_units=4)
+    attn.enable_trace()
+    attn.enable_event_log()
+    attn.forward(batch)
+    trace, ev = attn.read_trace(), attn.read_event_log()
+    assert (trace["t_end"] > trace["t_begin"]).all() and (trace["t_begin"] > 0).all()
+    first_p = trace["first_role"] == 0
+    n_items = trace["n_first"][first_p].sum() + trace["n_second"][~first_p].sum()
+    assert n_items == attn.info.n_prefill_items and len(ev) == n_items + attn.info.n_decode_units
+    if not decode:
+        assert len(trace) > attn.info.fused_grid
+    attn.close()
+
+
 def _sample_rows(batch, n_p, n_d, seed):
     rng = np.random.Generator(np.random.PCG64(seed))
     npr, nd = batch.n_prefill_rows, batch.n_decode
