@@ -295,16 +295,19 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
             const int stream = x.req * prm.n_kv_heads + x.kv_head;
             return (stream * per + (x.row0 / kPrefillRows) % per) % kXcdQueues;
         };
-        std::stable_sort(plan.pitems.begin(), plan.pitems.end(), [&](const PrefillItem &x, const PrefillItem &y) {
-            const int qx = queue_of(x), qy = queue_of(y);
-            if (qx != qy) return qx < qy;
-            return (x.kv_end - x.kv_begin) > (y.kv_end - y.kv_begin);
-        });
-        int at = 0;
-        for (int q = 0; q <= kXcdQueues; ++q) {
-            while (at < (int)plan.pitems.size() && queue_of(plan.pitems[(size_t)at]) < q) ++at;
-            plan.pq_begin[q] = q == kXcdQueues ? (int)plan.pitems.size() : at;
+        std::vector<PrefillItem> dealt(plan.pitems.size());
+        std::vector<int32_t> queue(plan.pitems.size());
+        for (size_t i = 0; i < plan.pitems.size(); ++i) ++plan.pq_begin[(queue[i] = queue_of(plan.pitems[i])) + 1];
+        for (int q = 0; q < kXcdQueues; ++q) plan.pq_begin[q + 1] += plan.pq_begin[q];
+        {
+            int at[kXcdQueues];
+            std::copy(plan.pq_begin, plan.pq_begin + kXcdQueues, at);
+            for (size_t i = 0; i < plan.pitems.size(); ++i) dealt[(size_t)at[queue[i]]++] = plan.pitems[i];
         }
+        for (int q = 0; q < kXcdQueues; ++q)
+            std::stable_sort(dealt.begin() + plan.pq_begin[q], dealt.begin() + plan.pq_begin[q + 1],
+                             [](const PrefillItem &x, const PrefillItem &y) { return x.kv_end - x.kv_begin > y.kv_end - y.kv_begin; });
+        plan.pitems = std::move(dealt);
         // Order for the kernels that take items by workgroup index (one workgroup per item, no
         // claims): workgroup b runs on XCD b % 8 (measured: the dispatcher deals them round-robin
         // without exception), so it gets the next item of queue b % 8 and a K/V head's tiles stay in
@@ -312,40 +315,40 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
         // to the workgroups whose own queue has run out.
         {
             const int n = (int)plan.pitems.size();
-            plan.pitems_by_wg.assign((size_t)n, PrefillItem{});
-            plan.pitem_of_wg.assign((size_t)n, 0);
-            auto place = [&](int b, int item) {
-                plan.pitems_by_wg[(size_t)b] = plan.pitems[(size_t)item];
-                plan.pitem_of_wg[(size_t)b] = item;
-            };
+            std::vector<int32_t> &item = plan.pitem_of_wg;
+            item.assign((size_t)n, 0);
             int next[kXcdQueues];
             for (int q = 0; q < kXcdQueues; ++q) next[q] = plan.pq_begin[q];
             std::vector<int> unfilled;
             for (int b = 0; b < n; ++b) {
                 const int q = b % kXcdQueues;
-                if (next[q] < plan.pq_begin[q + 1]) place(b, next[q]++);
+                if (next[q] < plan.pq_begin[q + 1]) item[(size_t)b] = next[q]++;
                 else unfilled.push_back(b);
             }
             size_t u = 0;
             for (int q = 0; q < kXcdQueues; ++q)
-                while (next[q] < plan.pq_begin[q + 1]) place(unfilled[u++], next[q]++);
+                while (next[q] < plan.pq_begin[q + 1]) item[(size_t)unfilled[u++]] = next[q]++;
             // Two rounds at once: workgroup b + n_cus joins workgroup b on its compute unit, and two long items
             // there slow each other down while other units run dry.  Within an XCD the second round is
-            // therefore dealt shortest first.
+            // therefore dealt shortest first.  (An XCD's own items come longest first; only items that were
+            // left over from other queues are out of place, and are moved up.)
             if (n > n_cus && n <= 2 * n_cus) {
+                auto keys = [&](int i) { return plan.pitems[(size_t)i].kv_end - plan.pitems[(size_t)i].kv_begin; };
                 for (int x = 0; x < kXcdQueues; ++x) {
-                    std::vector<int> items;
-                    for (int b = x; b < n; b += kXcdQueues) items.push_back(plan.pitem_of_wg[(size_t)b]);
-                    std::stable_sort(items.begin(), items.end(), [&](int i, int j) {
-                        const PrefillItem &a = plan.pitems[(size_t)i], &b = plan.pitems[(size_t)j];
-                        return a.kv_end - a.kv_begin > b.kv_end - b.kv_begin;
-                    });
-                    const size_t first_round = std::min(items.size(), (size_t)std::max(0, (n_cus - x + kXcdQueues - 1) / kXcdQueues));
-                    std::reverse(items.begin() + (std::ptrdiff_t)first_round, items.end());
-                    size_t k = 0;
-                    for (int b = x; b < n; b += kXcdQueues) place(b, items[k++]);
+                    const int count = (n - x + kXcdQueues - 1) / kXcdQueues;
+                    auto at = [&](int k) -> int32_t & { return item[(size_t)(x + k * kXcdQueues)]; };
+                    for (int k = 1; k < count; ++k) {
+                        const int32_t moved = at(k);
+                        int j = k;
+                        for (; j > 0 && keys(at(j - 1)) < keys(moved); --j) at(j) = at(j - 1);
+                        at(j) = moved;
+                    }
+                    int lo = std::min(count, std::max(0, (n_cus - x + kXcdQueues - 1) / kXcdQueues)), hi = count - 1;
+                    for (; lo < hi; ++lo, --hi) std::swap(at(lo), at(hi));
                 }
             }
+            plan.pitems_by_wg.reserve((size_t)n);
+            for (int b = 0; b < n; ++b) plan.pitems_by_wg.push_back(plan.pitems[(size_t)item[(size_t)b]]);
         }
     }
 
