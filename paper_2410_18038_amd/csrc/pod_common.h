@@ -70,13 +70,12 @@ struct DecodeUnit {
     int32_t q_start, cache_row;            // copied from the request: a unit starts with one lookup
 };
 
-// One group of output rows merged from split partials.
+// One group of output rows merged from split partials (host only; the kernel reads CombineRows).
 struct CombineEntry {
     int32_t kind;                          // kPrefill or kDecode
-    int32_t req, kv_head, row0, n_rows;
+    int32_t kv_head, row0, n_rows;
     int32_t n_splits, prow0, split_stride; // partial row of split s, row r: prow0 + s*split_stride + r
-    int32_t q_start, q_len;                // copied from the request, so the merge needs no second lookup
-    int32_t pad0, pad1;
+    int32_t q_start;                       // of the request
 };
 
 // One merged output row as the combine kernel reads it: everything in one 16-byte lookup.

@@ -267,9 +267,8 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
                     if (s > 1) {
                         prow_base = next_prow;
                         next_prow += (int64_t)s * kPrefillRows;
-                        plan.centries.push_back(CombineEntry{kPrefill, r, kvh, row0, n_rows, s,
-                                                             (int32_t)prow_base, kPrefillRows,
-                                                             seq_meta[4 * r], q_len, 0, 0});
+                        plan.centries.push_back(CombineEntry{kPrefill, kvh, row0, n_rows, s, (int32_t)prow_base,
+                                                             kPrefillRows, seq_meta[4 * r]});
                     }
                     for (int i = 0; i < s; ++i) {
                         PrefillItem it;
@@ -426,8 +425,7 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
                 if (s_eff > 1) {
                     prow_base = next_prow;
                     next_prow += (int64_t)s_eff * group;
-                    plan.centries.push_back(CombineEntry{kDecode, r, kvh, 0, group, s_eff, (int32_t)prow_base, group,
-                                                         seq_meta[4 * r], 1, 0, 0});
+                    plan.centries.push_back(CombineEntry{kDecode, kvh, 0, group, s_eff, (int32_t)prow_base, group, seq_meta[4 * r]});
                 }
                 for (int i = 0; i < s_eff; ++i) {
                     DecodeUnit u;
@@ -470,25 +468,22 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
     if (next_prow > (int64_t)1 << 30) { err = "too many partial rows"; return POD_ERR_INVALID_ARG; }
     plan.n_partial_rows = next_prow;
 
-    // One (entry, row) pair per output row that is merged from partials, prefill entries first.
+    // The output rows that are merged from partials, prefill rows first.
     {
-        size_t n_pairs = 0;
-        for (const CombineEntry &c : plan.centries) n_pairs += (size_t)c.n_rows;
-        plan.crows.reserve(2 * n_pairs);
-        plan.merge_rows.reserve(n_pairs);
+        size_t n_rows = 0;
+        for (const CombineEntry &c : plan.centries) n_rows += (size_t)c.n_rows;
+        plan.merge_rows.reserve(n_rows);
     }
-    for (size_t e = 0; e < plan.centries.size(); ++e) {
-        const CombineEntry &c = plan.centries[e];
+    for (const CombineEntry &c : plan.centries) {
+        const uint64_t decode_bit = (uint64_t)(c.kind == kDecode) << 63;
+        int64_t token_row = c.kind == kPrefill ? c.q_start + c.row0 / group : n_prefill_rows + c.q_start;
+        int head = c.kind == kPrefill ? c.row0 % group : 0;               // inside the group
         for (int r = 0; r < c.n_rows; ++r) {
-            if (c.kind == kPrefill && (c.row0 + r) / group >= c.q_len) continue;
-            plan.crows.push_back((int32_t)e);
-            plan.crows.push_back(r);
-            const int64_t token_row = c.kind == kPrefill ? c.q_start + (c.row0 + r) / group : n_prefill_rows + c.q_start;
-            const int head = c.kv_head * group + (c.kind == kPrefill ? (c.row0 + r) % group : r);
-            const uint64_t out_row = (uint64_t)(token_row * prm.n_q_heads + head) | (uint64_t)(c.kind == kDecode) << 63;
+            const uint64_t out_row = (uint64_t)(token_row * prm.n_q_heads + c.kv_head * group + head) | decode_bit;
             plan.merge_rows.push_back(CombineRow{c.prow0 + r, c.n_splits, (uint32_t)out_row, (uint32_t)(out_row >> 32)});
+            if (++head == group) { head = 0; ++token_row; }
         }
-        if (c.kind == kPrefill) plan.n_crows_prefill = (int)(plan.crows.size() / 2);
+        if (c.kind == kPrefill) plan.n_crows_prefill = (int)plan.merge_rows.size();
     }
 
     // A group of the combine kernel fetches kCombineFetch splits at a time; as many groups share a row as

@@ -24,11 +24,10 @@ struct Plan {
     std::vector<PrefillItem> pitems_by_wg;
     std::vector<int32_t> pitem_of_wg;       // index in pitems of each of them
     std::vector<DecodeUnit> dunits;
-    std::vector<CombineEntry> centries;
-    std::vector<int32_t> crows;             // (entry, row) pairs, prefill entries first
-    std::vector<CombineRow> merge_rows;     // the same rows as the combine kernel reads them
+    std::vector<CombineEntry> centries;     // output groups merged from partials
+    std::vector<CombineRow> merge_rows;     // their rows as the combine kernel reads them, prefill rows first
     int combine_groups[2] = {1, 1};         // [op]: thread groups that share a row's splits
-    int n_crows_prefill = 0;
+    int n_crows_prefill = 0;                // rows of merge_rows that are prefill rows
     int64_t n_prefill_rows = 0;
     int64_t n_partial_rows = 0;
     int p_ratio = 1, d_ratio = 1;

@@ -6,6 +6,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 #include <map>
 #include <string>
 #include <utility>
@@ -90,18 +91,79 @@ bool check_plan(const pod_attn_params &prm, const std::vector<int32_t> &meta, co
     for (int q = 0; q < pod::kXcdQueues; ++q)
         CHECK(p.dq_begin[q] <= p.dq_begin[q + 1] && p.dq_begin[q + 1] <= (int)p.dunits.size(), "decode queue %d", q);
     CHECK(p.dq_begin[pod::kXcdQueues] == (int)p.dunits.size(), "last queue %d", p.dq_begin[pod::kXcdQueues]);
-    // combine entries and the row list
+    // combine entries
     for (const pod::CombineEntry &c : p.centries) {
         CHECK(c.n_splits >= 2, "splits %d", c.n_splits);
         CHECK(c.prow0 >= 0 && (int64_t)c.prow0 + (int64_t)(c.n_splits - 1) * c.split_stride + c.n_rows <= p.n_partial_rows,
               "entry partial rows %d", c.prow0);
     }
-    CHECK(p.crows.size() % 2 == 0, "row list");
-    for (size_t i = 0; i < p.crows.size(); i += 2) {
-        CHECK(p.crows[i] >= 0 && p.crows[i] < (int)p.centries.size(), "row list entry %d", p.crows[i]);
-        CHECK(p.crows[i + 1] >= 0 && p.crows[i + 1] < p.centries[(size_t)p.crows[i]].n_rows, "row list row %d", p.crows[i + 1]);
+    // the rows the merge runs from, against what the split items and units write: the partial rows of split s lie
+    // s items' (or groups') rows behind those of split 0, and every output row of a split is merged once
+    struct Group { int64_t base = -1, n = 0, sum = 0; };                 // split 0's partial row, splits, sum of their numbers
+    const int block = pod::prefill_item_rows(prm.head_dim);
+    std::vector<Group> groups;
+    std::vector<size_t> group0((size_t)n_req + 1, 0);                    // first group of each request
+    for (int r = 0; r < n_req; ++r)
+        group0[(size_t)r + 1] = group0[(size_t)r] + (size_t)prm.n_kv_heads * (size_t)(r < prm.n_prefill ? (meta[4 * r + 1] * group + block - 1) / block : 1);
+    groups.resize(group0[(size_t)n_req]);
+    auto add = [&](size_t g, int split, int prow0, int stride) {
+        Group &x = groups[g];
+        const int64_t base = (int64_t)prow0 - (int64_t)split * stride;
+        if (x.n++ == 0) x.base = base;
+        x.sum += split;
+        return x.base == base && base >= 0;
+    };
+    auto group_of = [&](int req, int kv_head, int row0) {
+        const size_t per_head = (group0[(size_t)req + 1] - group0[(size_t)req]) / (size_t)prm.n_kv_heads;
+        return group0[(size_t)req] + (size_t)kv_head * per_head + (size_t)(row0 / block);
+    };
+    for (const pod::PrefillItem &it : p.pitems)
+        if (it.prow0 >= 0) CHECK(add(group_of(it.req, it.kv_head, it.row0), it.split, it.prow0, block), "partial row %d", it.prow0);
+    for (const pod::DecodeUnit &u : p.dunits)
+        if (u.prow0 >= 0) CHECK(add(group_of(u.req, u.kv_head, 0), u.split, u.prow0, group), "partial row %d", u.prow0);
+    const size_t n_out = (size_t)((p.n_prefill_rows + prm.n_decode) * prm.n_q_heads);
+    std::vector<int> first_partial(n_out, -1), splits(n_out, 0);         // of each output row
+    size_t n_expected = 0;
+    for (int r = 0; r < n_req; ++r)
+        for (size_t g = group0[(size_t)r]; g < group0[(size_t)r + 1]; ++g) {
+            const Group &x = groups[g];
+            if (x.n == 0) continue;
+            CHECK(x.sum == x.n * (x.n - 1) / 2, "splits of request %d", r);
+            const bool is_p = r < prm.n_prefill;
+            const int per_head = (int)((group0[(size_t)r + 1] - group0[(size_t)r]) / (size_t)prm.n_kv_heads);
+            const int kv_head = (int)(g - group0[(size_t)r]) / per_head, row0 = (int)(g - group0[(size_t)r]) % per_head * block;
+            const int n_rows = is_p ? std::min(block, meta[4 * r + 1] * group - row0) : group;
+            for (int i = 0; i < n_rows; ++i) {
+                const int64_t token = is_p ? meta[4 * r] + (row0 + i) / group : p.n_prefill_rows + meta[4 * r];
+                const int64_t out_row = token * prm.n_q_heads + kv_head * group + (row0 + i) % group;
+                first_partial[(size_t)out_row] = (int)x.base + i;
+                splits[(size_t)out_row] = (int)x.n;
+            }
+            n_expected += (size_t)n_rows;
+        }
+    CHECK(p.merge_rows.size() == n_expected, "merged rows %d of %d", (int)p.merge_rows.size(), (int)n_expected);
+    CHECK(p.n_crows_prefill >= 0 && (size_t)p.n_crows_prefill <= p.merge_rows.size(), "prefill rows %d", p.n_crows_prefill);
+    for (size_t i = 0; i < p.merge_rows.size(); ++i) {
+        const pod::CombineRow &c = p.merge_rows[i];
+        CHECK((c.out_row_hi >> 31) == (i >= (size_t)p.n_crows_prefill), "kind of merged row %d", (int)i);
+        const uint64_t out_row = (uint64_t)(c.out_row_hi & 0x7fffffffu) << 32 | c.out_row_lo;
+        CHECK(out_row < n_out, "merged row %d", (int)i);
+        CHECK(first_partial[out_row] == c.prow && splits[out_row] == c.n_splits, "merged row %d: partial row %d", (int)i, c.prow);
+        first_partial[out_row] = -1;                 // a second row for it would not match
     }
-    CHECK(p.n_crows_prefill >= 0 && (size_t)p.n_crows_prefill * 2 <= p.crows.size(), "prefill rows %d", p.n_crows_prefill);
+    for (int op : {pod::kPrefill, pod::kDecode}) {
+        const int g = p.combine_groups[op];
+        CHECK(g >= 1 && (g & (g - 1)) == 0 && g <= pod::kWgThreads / (prm.head_dim / 4), "thread groups %d", g);
+    }
+    // the workgroup order: the same items, each once
+    CHECK(p.pitem_of_wg.size() == p.pitems.size() && p.pitems_by_wg.size() == p.pitems.size(), "workgroup order");
+    std::vector<char> taken(p.pitems.size(), 0);
+    for (size_t b = 0; b < p.pitem_of_wg.size(); ++b) {
+        const int32_t i = p.pitem_of_wg[b];
+        CHECK(i >= 0 && i < (int)p.pitems.size() && !taken[(size_t)i], "workgroup %d takes item %d", (int)b, i);
+        taken[(size_t)i] = 1;
+        CHECK(std::memcmp(&p.pitems_by_wg[b], &p.pitems[(size_t)i], sizeof(pod::PrefillItem)) == 0, "item of workgroup %d", (int)b);
+    }
     CHECK(p.fused_grid >= 0 && p.fused_grid <= 2 * p.n_cus, "grid %d", p.fused_grid);
     CHECK(p.fused_grid >= p.n_dwgs, "grid %d below the seats %d", p.fused_grid, p.n_dwgs);
     CHECK(p.off_part_ml + (size_t)p.n_partial_rows * 2 * sizeof(float) <= p.ws_bytes, "workspace");
@@ -118,7 +180,7 @@ int main(int argc, char **argv)
     for (g_case = 0; g_case < n_cases; ++g_case) {
         pod_attn_params prm{};
         const int hkv = one_of({1, 2, 3, 4, 5, 8, 32});
-        const int group = one_of({1, 2, 4, 8, 16});
+        const int group = one_of({1, 2, 3, 4, 6, 8, 16});
         prm.n_kv_heads = hkv;
         prm.n_q_heads = hkv * group;
         prm.head_dim = group <= 8 ? one_of({64, 128, 256}) : one_of({64, 128});   // 256 channels: at most 8 heads per K/V head
