@@ -100,6 +100,7 @@ struct WsHeader {
     uint32_t next_pitem_xcd[kXcdQueues][32];
     // Next decode unit of each per-XCD queue (offset inside the queue), claimed by wavefronts.
     uint32_t next_dunit_xcd[kXcdQueues][32];
+    uint32_t reserved[512][32];            // zero
 };
 
 // Which operation the workgroup holding `ticket` on hardware unit `unit` starts with: the ticket
