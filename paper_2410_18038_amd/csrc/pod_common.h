@@ -100,7 +100,7 @@ struct WsHeader {
     uint32_t next_pitem_xcd[kXcdQueues][32];
     // Next decode unit of each per-XCD queue (offset inside the queue), claimed by wavefronts.
     uint32_t next_dunit_xcd[kXcdQueues][32];
-    uint32_t reserved[512][32];            // zero
+    uint32_t reserved[512][32];            // zero; not used (the block of counters at the head of a workspace keeps its size)
 };
 
 // Which operation the workgroup holding `ticket` on hardware unit `unit` starts with: the ticket

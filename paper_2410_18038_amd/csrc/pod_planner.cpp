@@ -73,7 +73,7 @@ void cut_request(int kv_len, int chunk, int shortest, Cut how, std::vector<int> 
         for (t = std::min(t, kv_len); t < kv_len;) {
             cuts.push_back(t);
             const int left = kv_len - t, half = std::min(chunk, left / 2 / kDecodeStep * kDecodeStep);
-            t += half >= last ? half : left >= 2 * last ? last : left;
+            t += half >= last ? half : left;
         }
     } else if (how == Cut::kTaper) {
         cuts.push_back(0);
