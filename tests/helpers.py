@@ -2,6 +2,7 @@
 import numpy as np
 
 from oracle import reference
+from paper_2410_18038_amd import pod
 from paper_2410_18038_amd import workloads as wl
 
 
@@ -16,6 +17,23 @@ def oracle_out(batch: wl.HybridBatch, rows=None) -> np.ndarray:
         softmax_scale=batch.softmax_scale, block_size=batch.block_size,
         max_blocks_per_seq=batch.max_blocks_per_seq, kv_seq_stride=batch.kv_seq_stride,
         head_major=batch.head_major, rows=rows)
+
+
+def role_rule(plan) -> str:
+    """How the fused launch of a plan with both operations gives its workgroups their operation, read off the host
+    model of the launch: "ticket", or by workgroup index with "prefill" or "decode" first."""
+    info = plan.info()
+    n, n_items = info.fused_grid, info.n_prefill_items
+    n_workers = min(info.n_compute_units, (info.n_decode_units + 3) // 4)
+    want = {"prefill": [0] * n_items + [1] * (n - n_items),
+            "decode": [1] * n_workers + [0] * n_items + [1] * (n - n_items - n_workers)}
+    fits = {"ticket", "prefill", "decode"}
+    for unit in range(info.prefill_ratio + info.decode_ratio):               # all workgroups on one unit, in turn
+        first = pod.pod_attn_simulate_launch(plan, [unit] * n, list(range(0, 4 * n, 4)))[1].tolist()
+        by_ticket = [pod.pod_attn_role_for_ticket(t, info.prefill_ratio, info.decode_ratio, unit) for t in range(n)]
+        fits -= {rule for rule in fits if first != (by_ticket if rule == "ticket" else want[rule])}
+    assert len(fits) == 1, f"the launch fits {fits or 'no rule'}"
+    return fits.pop()
 
 
 def logical_kv(batch: wl.HybridBatch, req: int):

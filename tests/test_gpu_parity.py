@@ -9,7 +9,7 @@ import torch
 
 from paper_2410_18038_amd import pod
 from paper_2410_18038_amd import workloads as wl
-from tests.helpers import oracle_out
+from tests.helpers import oracle_out, role_rule
 
 pytestmark = pytest.mark.gpu
 
@@ -343,15 +343,20 @@ def _sample_rows(batch, n_p, n_d, seed):
     return np.concatenate([rows_p[:0] if npr == 0 else rows_p, rows_d[:0] if nd == 0 else rows_d]).astype(np.int32)
 
 
-@pytest.mark.parametrize("d,q_len,decode", [
-    (128, 300, [700, 333, 90]),                  # everything fits one workgroup per unit, all units fixed, a remainder of them
-    (64, 100, [1] * 5),                          # ... and a decode worker with a single wavefront at work
-    (128, 896, [1500] * 9 + [16, 2500]),         # 14 items for 16 units: roles by index, the rest of the units claimed
-    (128, 897, [1500] * 9 + [16, 2500]),         # 16 items: roles by ticket
-    (256, 200, [1500] * 9 + [2500]),             # 256 channels, a worker on every unit: decode seats first
-    (256, 100, [70]),                            # ... and too few for that
+# (items for 16 compute units; whether decode units beyond the fixed ones are claimed)
+@pytest.mark.parametrize("d,q_len,decode,rule,n_items,claims", [
+    (128, 300, [700, 333, 90], "prefill", 10, False),           # everything fits one workgroup per unit, all units fixed
+    (64, 100, [1] * 5, "prefill", 4, False),                    # ... and a decode worker with two wavefronts at work
+    (128, 448, [5000] * 9 + [16, 2500], "prefill", 14, True),   # 7/8 of the units: by index, the rest of the units claimed
+    (64, 448, [5000] * 9 + [16, 2500], "prefill", 14, True),
+    (128, 449, [5000] * 9 + [16, 2500], "ticket", 16, True),    # more items than that
+    (128, 449, [150] * 4, "ticket", 16, False),
+    (256, 200, [1500] * 9 + [2500], "decode", 14, True),        # 256 channels, a worker on every unit: decode seats first
+    (256, 256, [1500] * 9 + [2500], "decode", 16, True),        # ... up to an item for every unit
+    (256, 257, [1500] * 9 + [2500], "ticket", 18, True),
+    (256, 100, [70], "prefill", 8, False),                      # ... and too few decodes for that
 ])
-def test_roles_by_workgroup_index_and_by_ticket(d, q_len, decode):
+def test_roles_by_workgroup_index_and_by_ticket(d, q_len, decode, rule, n_items, claims):
     """Both sides of the planner's role rule, on a plan made for 16 compute units: the fused launch runs the
     plan's items and units, so it gives the bits of the two kernels run one after the other, again and again."""
     batch = wl.make_batch("roles", prefill=[(q_len, q_len + 77)], decode_kv_lens=decode, n_q_heads=4, n_kv_heads=2,
@@ -360,6 +365,7 @@ def test_roles_by_workgroup_index_and_by_ticket(d, q_len, decode):
     assert np.abs(got - oracle_out(batch)).max() <= TOL[batch.dtype]
     dev_batch = batch.to("cuda:0")
     attn = pod.HybridAttention(dev_batch, n_compute_units=16)
+    assert (role_rule(attn.plan), info.n_prefill_items, info.n_decode_units > 64) == (rule, n_items, claims)
     serial = attn.forward(dev_batch, mode=pod.MODES["serial"]).clone()
     for _ in range(3):
         fused = attn.forward(dev_batch, out=torch.zeros_like(serial))
