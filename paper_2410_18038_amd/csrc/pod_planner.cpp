@@ -355,6 +355,7 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
     {
         int longest_item = 0;                    // keys of the longest prefill item
         for (const PrefillItem &it : plan.pitems) longest_item = std::max(longest_item, it.kv_end - it.kv_begin);
+        const Layout layout = cache_layout(prm.block_size, prm.head_dim, prm.n_kv_heads);
         const bool one_round = prm.decode_chunk <= 0 && share <= kOneRoundShare;
         const int shortest = std::max(64, 8 * group);    // a unit's partial rows stay below 1/8 of its K/V bytes
         std::vector<int> cuts;
@@ -364,11 +365,11 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
         } else if (one_round) {
             // Little work: what counts is the length of the one unit a wavefront runs (16 keys take about
             // 0.7 us), so requests are cut into equal pieces as short as one round of the chip allows.
+            // us per call, units of at least 512 keys before: one decode of 6007 keys 31.9 -> 14.4,
+            // three at 4K (8 heads per K/V head) 31.8 -> 18.1, 128 short ones 21.1 -> 15.0.
             // Cutting costs a merge pass, about as long as a hundred keys: it is not worth it when
             // the whole requests are short, nor when the prefill items beside them take longer anyway (a
             // tile of 64 keys takes about 1.1 us) and need no merge themselves.
-            // us per call, units of at least 512 keys before: one decode of 6007 keys 31.9 -> 14.4,
-            // three at 4K (8 heads per K/V head) 31.8 -> 18.1, 128 short ones 21.1 -> 15.0.
             chunk = shortest;
             if (longest_decode <= shortest + 112 || (longest_item > 0 && plan.centries.empty() && longest_decode <= longest_item / 8 + 150))
                 chunk = round_up(std::max(longest_decode, kDecodeStep), kDecodeStep);
@@ -387,7 +388,27 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
             // 15 / 5 heads 95 -> 86, 84 decodes at 0.5K-1K 66.8 -> 57.7.
             auto chunk_of = [&](int cap) { return round_up((int)std::min<int64_t>(std::max<int64_t>(share, shortest), cap), kDecodeStep); };
             const int coarse = chunk_of(kLongestUnit);
-            chunk = chunk_of(longest_unit(cache_layout(prm.block_size, prm.head_dim, prm.n_kv_heads), prm.head_dim));
+            const int cap = longest_unit(layout, prm.head_dim);
+            chunk = chunk_of(cap);
+            // Requests shorter than a piece stay whole.  Where they are most of the work and 1 to 1.4 (or 2 to 2.1; with one
+            // or two heads per K/V head, whose partial rows are small, 1 to 1.6, 2 to 2.4 or 3 to 3.2) per wavefront, the last round keeps few wavefronts busy, and pieces of half the longest request (the taper
+            // makes three or four of each) are faster.  (A wavefront streams up to 1.7 times as fast when others are
+            // idle, so that fuller last rounds cost nothing.)  us whole / half, 32 / 8 heads of 2000 keys: 130
+            // requests (1.02 per wavefront) 234 / 181, 160 (1.25) 248 / 217, 200 (1.56) 268 / 268, 250 (1.95) 323 / 331,
+            // 300 (2.34) 402 / 395; of 1000 keys 123 / 100, 128 / 118, 139 / 145, 162 / 178, 204 / 211; 32 / 32 heads
+            // of 2000 keys at 1.25, 1.56, 1.94, 2.34 249 / 213, 275 / 264, 327 / 321, 400 / 387; 8 / 1 heads at 1.25,
+            // 1.56 246 / 227, 263 / 278.  Short pieces gain less: 160 of 500 keys 71 / 73, 64 channels 44 / 48, but
+            // 256 channels 141 / 123.
+            {
+                const int whole = chunk + round_up(std::max(chunk / 4, shortest), kDecodeStep) / 2;
+                int64_t whole_token_heads = 0;
+                for (int r = prm.n_prefill; r < n_req; ++r)
+                    if (seq_meta[4 * r + 2] <= whole) whole_token_heads += (int64_t)seq_meta[4 * r + 2] * prm.n_kv_heads;
+                const int64_t n_units = units_of_length(prm, seq_meta, whole), rounds = (n_units + n_waves - 1) / n_waves;
+                if (2 * whole_token_heads > token_heads && 10 * n_units < (group <= 2 ? 8 : 7) * rounds * n_waves &&
+                    (int64_t)longest_decode * std::max(128, prm.head_dim) >= 96 * 1024)
+                    chunk = chunk_of(std::min(cap, longest_decode / 2));
+            }
             // Shorter units stream faster there but make more partial rows.  Where those are what keeps a
             // batch out of the library's own scratch, it is cut at 2048 keys.
             if (chunk < coarse) {

@@ -619,6 +619,25 @@ def test_longest_decode_unit_follows_the_cache_layout(d, block_size, longest):
     assert coverage_check(prm, meta).decode_chunk == 4096
 
 
+# (query heads, K/V heads, channels, block size, prefill (new, visible), decodes) -> longest piece, most units or None
+@pytest.mark.parametrize("hq,hkv,d,bs,prefill,lens,chunk,units", [
+    # whole requests: just over one per wavefront is halved, a fuller second round and short requests are not
+    (32, 8, 128, 16, [], [2000] * 130, 1008, None), (32, 8, 128, 16, [], [2000] * 178, 1008, None),
+    (32, 8, 128, 16, [], [2000] * 180, 2048, 1440), (32, 8, 128, 16, [], [2000] * 128, 2000, 1024),
+    (32, 8, 128, 16, [], [500] * 130, 512, 1040), (16, 8, 256, 16, [], [500] * 130, 256, None),
+    (32, 32, 128, 0, [], [2000] * 51, 1008, None), (32, 32, 128, 0, [], [2000] * 52, 2048, 1664)])
+def test_automatic_cut_on_both_sides_of_its_rules(hq, hkv, d, bs, prefill, lens, chunk, units):
+    prm, meta = meta_only("rules", prefill, lens, hq=hq, hkv=hkv, d=d, block_size=bs)
+    if bs:
+        prm.max_blocks_per_seq = 8192
+    info = coverage_check(prm, meta)
+    assert info.decode_chunk == chunk
+    if units is not None:
+        assert info.n_decode_units <= units
+    else:
+        assert info.n_decode_units > info.n_compute_units * 4
+
+
 @pytest.mark.parametrize("n_decode,kv_len,hq,hkv", [(200, 25163, 16, 8), (96, 56519, 16, 8), (240, 53884, 8, 2)])
 def test_wide_heads_are_cut_coarser_where_finer_cuts_miss_the_static_scratch(n_decode, kv_len, hq, hkv):
     prm, meta = meta_only("wide", [], [kv_len] * n_decode, hq=hq, hkv=hkv, d=256)
