@@ -355,7 +355,9 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
     {
         int longest_item = 0;                    // keys of the longest prefill item
         for (const PrefillItem &it : plan.pitems) longest_item = std::max(longest_item, it.kv_end - it.kv_begin);
+        const int n_items = (int)plan.pitems.size();
         const Layout layout = cache_layout(prm.block_size, prm.head_dim, prm.n_kv_heads);
+        const bool few_items = 2 * n_items <= n_cus && layout != kLayoutPagedAny;
         const bool one_round = prm.decode_chunk <= 0 && share <= kOneRoundShare;
         const int shortest = std::max(64, 8 * group);    // a unit's partial rows stay below 1/8 of its K/V bytes
         std::vector<int> cuts;
@@ -367,6 +369,14 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
             // 0.7 us), so requests are cut into equal pieces as short as one round of the chip allows.
             // us per call, units of at least 512 keys before: one decode of 6007 keys 31.9 -> 14.4,
             // three at 4K (8 heads per K/V head) 31.8 -> 18.1, 128 short ones 21.1 -> 15.0.
+            //
+            // Beside few prefill items (longer than a share) the round is that of the compute units without one: every workgroup then has
+            // a unit to itself (see the roles by index), where an item that shares its unit with a worker takes up to
+            // 40 % longer.  All units / those without an item: 300 + 1000 tokens beside 8 x 4000, 32 / 8 heads 47.4 /
+            // 35.5; 128 + 1000 beside 8 x 4000, 256 channels 78 / 48; 96 items beside 12 x 8000, 8 / 1 heads 43.5 / 39.0.
+            // Above half of the units (176 items, 8 x 1000: 25.9 / 26.2; 256 channels, 8 x 4000: 62 / 102) the workers need them all.
+            const int64_t waves = few_items && longest_item > share ? (int64_t)kWavesPerWg * (n_cus - n_items) : n_waves;
+            const int64_t own_share = (token_heads + waves - 1) / waves;
             // Cutting costs a merge pass, about as long as a hundred keys: it is not worth it when
             // the whole requests are short, nor when the prefill items beside them take longer anyway (a
             // tile of 64 keys takes about 1.1 us) and need no merge themselves.
@@ -374,7 +384,7 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
             if (longest_decode <= shortest + 112 || (longest_item > 0 && plan.centries.empty() && longest_decode <= longest_item / 8 + 150))
                 chunk = round_up(std::max(longest_decode, kDecodeStep), kDecodeStep);
             else
-                while (chunk < std::min<int64_t>(longest_decode, 2 * share) && units_of_length(prm, seq_meta, chunk) > n_waves)
+                while (chunk < std::min<int64_t>(longest_decode, 2 * own_share) && units_of_length(prm, seq_meta, chunk) > waves)
                     chunk += kDecodeStep;
         } else {
             // Enough work for every wavefront: pieces of at most one wavefront's share, and the second
