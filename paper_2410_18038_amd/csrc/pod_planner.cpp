@@ -22,8 +22,14 @@ std::string fmt(const char *f, long long a = 0, long long b = 0, long long c = 0
     return buf;
 }
 
-// Up to this many keys per wavefront the decode work is cut into one round of equal units.
-constexpr int kOneRoundShare = 320;
+// Up to this many keys per wavefront the decode work is cut into one round of equal units, else into a wavefront's
+// share with a taper.  us per call, taper / one round (8192-key requests): 128 channels (32 / 8 heads) at 260 keys per
+// wavefront 37 / 27, at 400 46 / 39, at 640 67 / 60; 64 channels at 640 42 / 37; 256 channels at 260 57 / 49, at 400 75 /
+// 71, at 640 between 128 / 110 and, beside a prefill chunk, 131 / 156: the line is the same number of bytes there.
+// It is 320 keys beside prefill items on more than half of the compute units (384 items: 12000 keys of 32 heads 92 /
+// 97; 256 channels at 310 keys 135 / 120), and where block ids are looked up per lane (24 decodes at 1K-6K
+// beside 400 tokens 153 / 255; 256 channels, 43 at 0.4K-6K, 287 keys, 154 / 137).
+int64_t one_round_share(int head_dim, bool few_items) { return few_items ? 640 * 128 / std::max(128, head_dim) : 320; }
 
 // Keys of the longest decode unit of the automatic cut: about 1 MB of K/V (see "decode units" below).  Where
 // block ids are looked up per lane a unit takes two to four times as long (the lookups are a second memory round
@@ -358,7 +364,7 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
         const int n_items = (int)plan.pitems.size();
         const Layout layout = cache_layout(prm.block_size, prm.head_dim, prm.n_kv_heads);
         const bool few_items = 2 * n_items <= n_cus && layout != kLayoutPagedAny;
-        const bool one_round = prm.decode_chunk <= 0 && share <= kOneRoundShare;
+        const bool one_round = prm.decode_chunk <= 0 && share <= one_round_share(prm.head_dim, few_items);
         const int shortest = std::max(64, 8 * group);    // a unit's partial rows stay below 1/8 of its K/V bytes
         std::vector<int> cuts;
         int chunk;

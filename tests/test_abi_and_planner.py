@@ -626,6 +626,11 @@ def test_longest_decode_unit_follows_the_cache_layout(d, block_size, longest):
     (32, 8, 128, 16, [], [2000] * 180, 2048, 1440), (32, 8, 128, 16, [], [2000] * 128, 2000, 1024),
     (32, 8, 128, 16, [], [500] * 130, 512, 1040), (16, 8, 256, 16, [], [500] * 130, 256, None),
     (32, 32, 128, 0, [], [2000] * 51, 1008, None), (32, 32, 128, 0, [], [2000] * 52, 2048, 1664),
+    # one round of equal pieces up to 640 keys per wavefront, 320 of 256 channels, by lane and beside many items
+    (32, 8, 128, 16, [], [8192] * 10, 688, 1024), (32, 8, 128, 16, [], [8192] * 10 + [20], 656, None),
+    (16, 8, 256, 16, [], [8192] * 5, 336, 1024), (16, 8, 256, 16, [], [8192] * 5 + [20], 336, None),
+    (32, 8, 128, 3, [], [8192] * 5, 336, 1024), (32, 8, 128, 3, [], [8192] * 5 + [20], 336, None),
+    (32, 8, 128, 16, [(513, 4000)], [8192] * 5, 336, 1024), (32, 8, 128, 16, [(513, 4000)], [8192] * 5 + [20], 336, None),
     # beside few items: the wavefronts of the units without one (80 items of 1300 keys; 80 short ones)
     (32, 8, 128, 16, [(300, 1300)], [4000] * 8, 368, 704), (32, 8, 128, 16, [(300, 300)], [5000] * 8, 320, 1024)])
 def test_automatic_cut_on_both_sides_of_its_rules(hq, hkv, d, bs, prefill, lens, chunk, units):
