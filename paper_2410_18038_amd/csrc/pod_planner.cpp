@@ -383,11 +383,21 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
             // Above half of the units (176 items, 8 x 1000: 25.9 / 26.2; 256 channels, 8 x 4000: 62 / 102) the workers need them all.
             const int64_t waves = few_items && longest_item > share ? (int64_t)kWavesPerWg * (n_cus - n_items) : n_waves;
             const int64_t own_share = (token_heads + waves - 1) / waves;
-            // Cutting costs a merge pass, about as long as a hundred keys: it is not worth it when
-            // the whole requests are short, nor when the prefill items beside them take longer anyway (a
-            // tile of 64 keys takes about 1.1 us) and need no merge themselves.
+            // Cutting costs a merge pass, which takes as long as about a hundred more keys in the unit (twenty at 256
+            // channels).  It is not worth it when the requests are short: us whole / cut at 160 keys 10.2 / 10.9, at
+            // 176 11.4 / 10.8, at 250 14.6 / 10.8 (64 channels 8.3 / 11.5, 8.4 / 11.5, 10.3 / 11.4; 256 channels at
+            // 100 keys 17.0 / 14.6, at 250 34 / 15).  Nor when the prefill items beside them take longer than the
+            // whole requests anyway (64 keys of an item take about 1.1 us, 16 of a unit 0.7, at 256 channels 2)
+            // and need no merge themselves: items of 1128 keys beside 16 x 500 27.8 / 33.5, x 700 36 / 34;
+            // of 2028 beside 16 x 700 44.6 / 50.7, 2 x 1000 50.1 / 48.1; of 128 beside 16 x 200 14.0 / 12.2; 256
+            // channels, 1128 keys beside 16 x 300 41.2 / 44.0, x 400 53 / 44, 2028 beside 2 x 500 67.5 / 70.4, x 700
+            // 86 / 71.  (Units whose block ids are looked up per lane take longer: cut from an eighth.)
+            const int worth_merging = shortest + (prm.head_dim > 128 ? 16 : 112);
+            const int beside_items = layout == kLayoutPagedAny ? longest_item / 8 + 150
+                                                               : (prm.head_dim > 128 ? longest_item / 5 : longest_item / 5 * 2) + 100;
             chunk = shortest;
-            if (longest_decode <= shortest + 112 || (longest_item > 0 && plan.centries.empty() && longest_decode <= longest_item / 8 + 150))
+            if (longest_decode <= worth_merging ||
+                (longest_item > 0 && plan.centries.empty() && longest_decode <= beside_items && units_of_length(prm, seq_meta, longest_decode) <= waves))
                 chunk = round_up(std::max(longest_decode, kDecodeStep), kDecodeStep);
             else
                 while (chunk < std::min<int64_t>(longest_decode, 2 * own_share) && units_of_length(prm, seq_meta, chunk) > waves)

@@ -632,7 +632,12 @@ def test_longest_decode_unit_follows_the_cache_layout(d, block_size, longest):
     (32, 8, 128, 3, [], [8192] * 5, 336, 1024), (32, 8, 128, 3, [], [8192] * 5 + [20], 336, None),
     (32, 8, 128, 16, [(513, 4000)], [8192] * 5, 336, 1024), (32, 8, 128, 16, [(513, 4000)], [8192] * 5 + [20], 336, None),
     # beside few items: the wavefronts of the units without one (80 items of 1300 keys; 80 short ones)
-    (32, 8, 128, 16, [(300, 1300)], [4000] * 8, 368, 704), (32, 8, 128, 16, [(300, 300)], [5000] * 8, 320, 1024)])
+    (32, 8, 128, 16, [(300, 1300)], [4000] * 8, 368, 704), (32, 8, 128, 16, [(300, 300)], [5000] * 8, 320, 1024),
+    # whole where the items beside them take longer, and where they are short
+    (32, 8, 128, 16, [(128, 1128)], [550] * 16, 560, 128), (32, 8, 128, 16, [(128, 1128)], [551] * 16, 80, 896),
+    (16, 8, 256, 16, [(128, 1128)], [325] * 16, 336, 128), (16, 8, 256, 16, [(128, 1128)], [326] * 16, 64, 896),
+    (32, 8, 128, 16, [], [176] * 8, 176, 64), (32, 8, 128, 16, [], [177] * 8, 64, 1024),
+    (16, 8, 256, 16, [], [80] * 8, 80, 64), (16, 8, 256, 16, [], [81] * 8, 64, 1024)])
 def test_automatic_cut_on_both_sides_of_its_rules(hq, hkv, d, bs, prefill, lens, chunk, units):
     prm, meta = meta_only("rules", prefill, lens, hq=hq, hkv=hkv, d=d, block_size=bs)
     if bs:
