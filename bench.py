@@ -35,15 +35,15 @@ PEAK_HBM = 8.0e12               # bytes/s, MI355X HBM3E
 MEASURED_TRAFFIC_BYTES = {
     # (config, batch_index): {kernel: FETCH_SIZE KiB x 2.0 (copy calibration: the counter reads half of a
     # plain copy's bytes) + WRITE_SIZE KiB x 1.0, per launch}  (files under profiles/)
-    (2, 0): {"fused_kernel": 4416896205, "fused_cta_kernel": 4623039283},
-    #   fused_kernel: 2145859.8 KiB fetched, 21655.6 KiB written
-    #   fused_cta_kernel: 2246222.3 KiB fetched, 22242.2 KiB written
-    (3, 0): {"fused_kernel": 4994009498, "fused_cta_kernel": 5153556582},
-    #   fused_kernel: 2417927.3 KiB fetched, 41107.8 KiB written
-    #   fused_cta_kernel: 2495912.2 KiB fetched, 40945.7 KiB written
-    (4, 0): {"fused_kernel": 2582235443, "fused_cta_kernel": 2749092147},
-    #   fused_kernel: 1240935.5 KiB fetched, 39843.3 KiB written
-    #   fused_cta_kernel: 1322148.0 KiB fetched, 40364.3 KiB written
+    (2, 0): {"fused_kernel": 4388586189, "fused_cta_kernel": 4573902541},
+    #   fused_kernel: 2136292.1 KiB fetched, 13144.5 KiB written
+    #   fused_cta_kernel: 2226925.4 KiB fetched, 12850.9 KiB written
+    (3, 0): {"fused_kernel": 4979373978, "fused_cta_kernel": 5138292736},
+    #   fused_kernel: 2416193.4 KiB fetched, 30283.1 KiB written
+    #   fused_cta_kernel: 2493943.4 KiB fetched, 29977.2 KiB written
+    (4, 0): {"fused_kernel": 2468465459, "fused_cta_kernel": 2736429978},
+    #   fused_kernel: 1192242.0 KiB fetched, 26126.8 KiB written
+    #   fused_cta_kernel: 1323216.9 KiB fetched, 25861.1 KiB written
 }
 
 
