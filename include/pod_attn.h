@@ -72,8 +72,9 @@ typedef enum {
  * (one workgroup per prefill item or per four decode units; each takes its unit's ticket, picks
  * its operation, claims one work id, runs it and leaves), instead of as one resident round of
  * persistent workgroups (Section 4.4's variant, the default).  Same result bit for bit; exists so
- * that the two launch styles can be timed against each other (once the chip's clocks are up the
- * persistent one is level on the MFMA-bound benchmark batch and 6-17 % faster on all others). */
+ * that the two launch styles can be timed against each other (once the chip's clocks are up this one
+ * is 5 % faster on the MFMA-bound benchmark batch, level on 1024 tokens beside 16 decodes, and the
+ * persistent one 2-13 % faster on all others). */
 #define POD_MODE_FLAG_CTA_PARALLEL 0x200
 
 /* May be OR-ed into POD_MODE_FUSED: the prefill-heavy occupancy configuration (Section 4.2.2 ships
@@ -86,8 +87,8 @@ typedef enum {
  * rounding (the decode kernel adds its weights in another order).  Built for head_dim 128 and for
  * contiguous caches or paged ones with power-of-two blocks of at least 16 tokens; otherwise
  * POD_ERR_UNSUPPORTED.  Not chosen automatically: on this chip it ends a prefill-heavy batch
- * 3-8 % sooner when launches are spaced out and 1-3 % sooner in a sustained loop, where the chip
- * clocks down under the power the two kernels draw together, and is slower on decode-bound batches.
+ * 8-10 % sooner in a sustained loop (2048 tokens at 32K beside 32 decodes at 32K: 1119 us against
+ * 1233), 4-11 % sooner when launches are spaced out, and is 6-35 % slower on decode-bound batches.
  * Also accepted with POD_MODE_PREFILL_ONLY and POD_MODE_DECODE_ONLY, which then run that
  * configuration's prefill or decode kernel alone.  Like POD_MODE_STREAMS it creates streams and
  * events on first use, is not meant for graph capture, and is rejected by pod_attn_forward_static. */
@@ -345,7 +346,9 @@ pod_status pod_attn_plan_decode_unit(const pod_attn_plan *plan, int32_t index, i
  * nothing for it.  Every other unit sits in one of 8 queues, one per XCD; queue q holds units
  * [*begin, *end), and a wavefront claims from the queue of the XCD it runs on before it tries the
  * others (the virtual decode CTAs of Section 4.2.3 are these units; which multiprocessor runs
- * which of them is decided at run time as in Section 4.1).  Units are sorted longest first inside
+ * which of them is decided at run time as in Section 4.1).  With units for at most one round of
+ * wavefronts (4 per compute unit) nobody claims: the up to three units that the queues then hold are
+ * run as fixed units of the last worker as well.  Units are sorted longest first inside
  * the fixed range and inside each queue.  Returns POD_ERR_INVALID_ARG when q is not in 0..7.
  */
 pod_status pod_attn_plan_decode_queue(const pod_attn_plan *plan, int32_t q, int32_t *begin, int32_t *end);

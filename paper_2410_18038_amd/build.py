@@ -17,8 +17,8 @@ UNITS = ([("pod_kernels.hip", (f"-DPOD_INSTANCE_DT={dt}", f"-DPOD_INSTANCE_D={d}
 HEADERS = ["pod_common.h", "pod_launch.h", "pod_planner.h", os.path.join("..", "..", "include", "pod_attn.h")]
 # Packed-fp32 instructions are switched off for the device pass (the host pass does not know
 # the feature and says so; that message is harmless).  The compiler's rewriting of atomics is
-# switched off too: every counter update here is already issued by one lane, and the rewrite
-# reads the result back at once, which makes a claim issued ahead of its use wait on the spot.
+# switched off too: every counter update here is already issued by one lane, so the rewrite would only add
+# a lane count and a read-back around each of them.
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
                "-mllvm", "-amdgpu-atomic-optimizer-strategy=None",

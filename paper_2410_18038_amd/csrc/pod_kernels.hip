@@ -643,7 +643,7 @@ __device__ __forceinline__ void prefill_item_run(const KernelArgs &a, const Pref
                 // Weight sums, over the rounded weights, the ones the PV product uses: a 4x4x4 product with ones
                 // adds four weights of every lane in 8 cycles of the matrix pipe, where a two-element dot
                 // product (which runs in that pipe too) takes 16 for two.  With the issue priority
-                // below, prefill of 8192 tokens 524 -> 515 us, of the prefill-heavy configuration at 32K
+                // below, prefill of 8192 tokens 544 -> 528 us, the prefill-heavy configuration at 32K
                 // contexts 1217 -> 1143.
                 asm("" : "+v"(pw[j]));                       // packed once, for both uses
                 l_run = N::add_all(u32x2{pw[j][0], pw[j][1]}, l_run);
@@ -1329,7 +1329,7 @@ __global__ __launch_bounds__(kWgThreads, 2) void decode_kernel(KernelArgs a)
 // of 8 channels) into 16 registers that are consumed by four matrix instructions as soon as they
 // arrive and re-requested at once for the next step.  One step is in flight per wavefront while
 // the previous one is computed: ~8 KB per wavefront, 32 KB per unit.  Alone on the chip that
-// streams within 3-10 % of the full decode worker; beside two prefill workgroups per unit at
+// streams within 2-8 % of the full decode worker; beside two prefill workgroups per unit at
 // about two thirds of it.
 // ------------------------------------------------------------------------------------------
 // Register budgets of the two kernels (the attribute below counts half of the unified file):
@@ -1577,8 +1577,9 @@ __global__ __launch_bounds__(kWgThreads) __attribute__((amdgpu_num_vgpr(kLiteVgp
 }
 
 // The prefill kernel of that configuration: the stand-alone prefill kernel, held to 208 registers
-// (seven values go to scratch memory at head_dim 128; the kernel measures 1-3 % faster, not
-// slower) so that two of its workgroups and one light decode workgroup fill a unit's register file.
+// (eleven values go to scratch memory at head_dim 128; alone it takes 911-973 us against 948-956 for 2048
+// tokens at 32K, 110 against 114 for 2048 at 4K, and 78 against 78 for 1024 at 4K with a K/V head per
+// head) so that two of its workgroups and one light decode workgroup fill a unit's register file.
 template <int DT, int D, int LAYOUT>
 __global__ __launch_bounds__(kWgThreads, 2) __attribute__((amdgpu_num_vgpr(kHeavyPrefillVgprs / 2))) void prefill_heavy_kernel(KernelArgs a)
 {

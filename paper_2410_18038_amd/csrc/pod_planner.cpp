@@ -365,7 +365,7 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
         const Layout layout = cache_layout(prm.block_size, prm.head_dim, prm.n_kv_heads);
         const bool few_items = 2 * n_items <= n_cus && layout != kLayoutPagedAny;
         const bool one_round = prm.decode_chunk <= 0 && share <= one_round_share(prm.head_dim, few_items);
-        const int shortest = std::max(64, 8 * group);    // a unit's partial rows stay below 1/8 of its K/V bytes
+        const int shortest = std::max(64, 8 * group);    // at 8 * group keys a unit's partial rows are 1/8 of its K/V bytes
         std::vector<int> cuts;
         int chunk;
         if (given_chunk > 0) {
@@ -580,6 +580,13 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
     // workgroup of each is a prefill one, and the stream pays more than that: 240 items 677 / 686, 256 items
     // 136.7 / 141.  At 256 channels decode workers go first, for the same reason: 256 items 472 / 465,
     // 192 items 456 / 448 (prefill first 461).
+    // By ticket / items first / workers first over 2048 cached keys, 32 / 8 heads of 128 channels, 16 decodes at 8192,
+    // 64 at 4096, 120 at 2000: 192 items 131 / 117 / 130, 201 / 192 / 200, 189 / 180 / 189; 224 items 130 / 116 / 121,
+    // 201 / 195 / 200, 188 / 184 / 191; 256 items 129 / 121 / 121, 201 / 207 / 204, 186 / 196 / 193: above 7/8 of
+    // the units it depends on the decodes, and workers first is the better of the two for none.  32 / 32 heads are within
+    // 1 % either way.  64 channels gain by index up to 256 items as well (119 / 112 / 112 with 64 decodes): the
+    // line is drawn for 128.  256 channels, 128 to 256 items: workers first 2 to 12 % ahead of tickets,
+    // items first within 4 %.
     if (prm.policy == POD_POLICY_AUTO && !plan.pitems.empty() && plan.n_dwgs > 0) {
         const int n_items = (int)plan.pitems.size();
         int rule = kRolesByTicket;
