@@ -424,15 +424,16 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
             // 300 (2.34) 402 / 395; of 1000 keys 123 / 100, 128 / 118, 139 / 145, 162 / 178, 204 / 211; 32 / 32 heads
             // of 2000 keys at 1.25, 1.56, 1.94, 2.34 249 / 213, 275 / 264, 327 / 321, 400 / 387; 8 / 1 heads at 1.25,
             // 1.56 246 / 227, 263 / 278.  Short pieces gain less: 160 of 500 keys 71 / 73, 64 channels 44 / 48, but
-            // 256 channels 141 / 123.
+            // 256 channels 141 / 123 (200 of them, at 1.56, 144 / 150).
             {
                 const int whole = chunk + round_up(std::max(chunk / 4, shortest), kDecodeStep) / 2;
                 int64_t whole_token_heads = 0;
                 for (int r = prm.n_prefill; r < n_req; ++r)
                     if (seq_meta[4 * r + 2] <= whole) whole_token_heads += (int64_t)seq_meta[4 * r + 2] * prm.n_kv_heads;
                 const int64_t n_units = units_of_length(prm, seq_meta, whole), rounds = (n_units + n_waves - 1) / n_waves;
-                if (2 * whole_token_heads > token_heads && 10 * n_units < (group <= 2 ? 8 : 7) * rounds * n_waves &&
-                    (int64_t)longest_decode * std::max(128, prm.head_dim) >= 96 * 1024)
+                const int64_t length = (int64_t)longest_decode * std::max(128, prm.head_dim);
+                const int tenths = group <= 2 && length > 128 * 1024 ? 8 : 7;
+                if (2 * whole_token_heads > token_heads && 10 * n_units < tenths * rounds * n_waves && length >= 96 * 1024)
                     chunk = chunk_of(std::min(cap, longest_decode / 2));
             }
             // Shorter units stream faster there but make more partial rows.  Where those are what keeps a

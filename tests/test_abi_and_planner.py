@@ -625,6 +625,7 @@ def test_longest_decode_unit_follows_the_cache_layout(d, block_size, longest):
     (32, 8, 128, 16, [], [2000] * 130, 1008, None), (32, 8, 128, 16, [], [2000] * 178, 1008, None),
     (32, 8, 128, 16, [], [2000] * 180, 2048, 1440), (32, 8, 128, 16, [], [2000] * 128, 2000, 1024),
     (32, 8, 128, 16, [], [500] * 130, 512, 1040), (16, 8, 256, 16, [], [500] * 130, 256, None),
+    (16, 8, 256, 16, [], [500] * 200, 784, 1600),
     (32, 32, 128, 0, [], [2000] * 51, 1008, None), (32, 32, 128, 0, [], [2000] * 52, 2048, 1664),
     # one round of equal pieces up to 640 keys per wavefront, 320 of 256 channels, by lane and beside many items
     (32, 8, 128, 16, [], [8192] * 10, 688, 1024), (32, 8, 128, 16, [], [8192] * 10 + [20], 656, None),
