@@ -395,13 +395,20 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
             const int worth_merging = shortest + (prm.head_dim > 128 ? 16 : 112);
             const int beside_items = layout == kLayoutPagedAny ? longest_item / 8 + 150
                                                                : (prm.head_dim > 128 ? longest_item / 5 : longest_item / 5 * 2) + 100;
-            chunk = shortest;
             if (longest_decode <= worth_merging ||
                 (longest_item > 0 && plan.centries.empty() && longest_decode <= beside_items && units_of_length(prm, seq_meta, longest_decode) <= waves))
                 chunk = round_up(std::max(longest_decode, kDecodeStep), kDecodeStep);
-            else
-                while (chunk < std::min<int64_t>(longest_decode, 2 * own_share) && units_of_length(prm, seq_meta, chunk) > waves)
-                    chunk += kDecodeStep;
+            else {
+                // the shortest length, in steps from `shortest`, that makes units for one round; two shares at the most
+                const int64_t limit = std::min<int64_t>(longest_decode, 2 * own_share);
+                int lo = 0, hi = limit > shortest ? (int)((limit - shortest + kDecodeStep - 1) / kDecodeStep) : 0;
+                while (lo < hi) {
+                    const int mid = (lo + hi) / 2;
+                    if (units_of_length(prm, seq_meta, shortest + mid * kDecodeStep) <= waves) hi = mid;
+                    else lo = mid + 1;
+                }
+                chunk = shortest + lo * kDecodeStep;
+            }
         } else {
             // Enough work for every wavefront: pieces of at most one wavefront's share, and the second
             // half of every request in pieces that halve down to a quarter of that.  Wavefronts do not
