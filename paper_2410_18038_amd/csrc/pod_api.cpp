@@ -401,6 +401,12 @@ static pod_status forward_impl(const void *prefill_q, const void *decode_q, cons
     only_d.crows = a.crows + p.n_crows_prefill;
     only_d.n_crows = a.n_crows - p.n_crows_prefill;
 
+    // The counters are cleared by the combine kernel of the call where it has one.
+    if (!no_combine) {
+        only_d.combine_resets = only_d.n_crows > 0;
+        a.combine_resets = mode == POD_MODE_DECODE_ONLY ? only_d.combine_resets : a.n_crows > 0;
+    }
+
     // Prefill kernel and decode kernel on the library's two side streams, forked from and joined
     // back into the caller's stream; the merge follows on the caller's stream.
     auto two_streams = [&](int prefill_kind, int decode_kind) -> pod_status {
@@ -487,7 +493,10 @@ static pod_status forward_impl(const void *prefill_q, const void *decode_q, cons
     default:
         break;
     }
-    if (e != hipSuccess) return fail_hip(e, "launching attention kernels");
+    if (e != hipSuccess) {
+        if (a.combine_resets) (void)pod::clear_header(a.hdr, s);       // the combine kernel may be what failed
+        return fail_hip(e, "launching attention kernels");
+    }
     return POD_OK;
 }
 
@@ -535,7 +544,7 @@ int32_t pod_attn_simulate_launch(const pod_attn_plan *plan, const int32_t *unit_
     uint32_t next_seat = 0, next_pitem[Q] = {0}, next_dunit[Q] = {0};
 
     enum Phase { kBind, kPrefillClaims, kSeat, kDecodeWaves, kEnd };
-    struct Wave { int cq = 0, tried = 0; bool started = false, done = false; };
+    struct Wave { int cq = 0; bool started = false, done = false; };
     struct Wg {
         Phase phase = kBind;
         int first = pod::kNone, roles_done = 0, xcd = 0, seat = -1;
@@ -640,16 +649,20 @@ int32_t pod_attn_simulate_launch(const pod_attn_plan *plan, const int32_t *unit_
             } else {
                 x.started = true;
                 // one claim on the queue the wavefront is at; a used-up queue sends it to the next
-                // non-empty one, and after all eight it is done
+                // one with units, and back at its XCD's own queue it is done, as it is once another
+                // wavefront of the XCD has come that far
                 const int q0 = p.dq_begin[x.cq], q1 = p.dq_begin[x.cq + 1];
                 const int k = (int)next_dunit[x.cq]++;
-                if (k < q1 - q0) own(q0 + k);
+                if (k & pod::kAllQueuesEmpty) x.done = true;
+                else if (k < q1 - q0) own(q0 + k);
                 else {
-                    do {
-                        x.cq = (x.cq + 1) & (Q - 1);
-                        ++x.tried;
-                    } while (x.tried < Q && p.dq_begin[x.cq + 1] == p.dq_begin[x.cq]);
-                    if (x.tried >= Q) x.done = true;
+                    const int home = g.xcd & (Q - 1);
+                    do x.cq = (x.cq + 1) & (Q - 1);
+                    while (x.cq != home && p.dq_begin[x.cq + 1] == p.dq_begin[x.cq]);
+                    if (x.cq == home) {
+                        next_dunit[home] |= pod::kAllQueuesEmpty;    // for the others of that XCD
+                        x.done = true;
+                    }
                 }
             }
             bool all = true;

@@ -86,8 +86,8 @@ struct CombineRow {
                                            // the top bit is set for a decode row
 };
 
-// Counters at the head of the device workspace.  All zero between launches: the last
-// workgroup of a fused launch clears them.  Counters that many workgroups add to have a 128-byte
+// Counters at the head of the device workspace.  All zero between calls: the combine kernel, or in calls
+// without one the last workgroup of the attention kernel, clears them.  Counters that many workgroups add to have a 128-byte
 // line each: the memory system serves one atomic per line every 11 ns, whichever word it names
 // (measured: 512 workgroups adding to eight words of one line take 7.4 us, on eight lines 2.7).
 struct WsHeader {
@@ -102,6 +102,9 @@ struct WsHeader {
     uint32_t next_dunit_xcd[kXcdQueues][32];
     uint32_t reserved[512][32];            // zero; not used (the block of counters at the head of a workspace keeps its size)
 };
+
+// Set in the counter of an XCD's decode queue once a wavefront of that XCD has found every queue used up.
+constexpr int kAllQueuesEmpty = 1 << 30;
 
 // Which operation the workgroup holding `ticket` on hardware unit `unit` starts with: the ticket
 // rule of Section 4.1 (ticket mod (p + d) < p means prefill).  A unit holds only kSlotsPerUnit
@@ -185,6 +188,7 @@ struct KernelArgs {
     const int32_t *dq_begin;               // [kXcdQueues + 1]: decode queue q holds units dq_begin[q] .. dq_begin[q+1]-1
     int32_t n_static_seats;                // decode seats that start with four fixed units (units 0 .. 4*seats-1)
     int32_t n_dctas;                       // decode workgroups of the CTA-parallel launch: ceil(n_dunits / 4)
+    int32_t combine_resets;                // the combine kernel of this call clears the counters, not the attention kernel
     int32_t single_unit;                   // a decode wavefront runs its fixed unit and claims none, whatever the queues hold
     int32_t fixed_roles;                   // CTA-parallel kernel: a RoleRule
     int32_t p_ratio, d_ratio;

@@ -853,6 +853,17 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
         return d;
     };
 
+    // State bits (one word: separate flags end up addressed through a common pointer and then
+    // live in scratch memory).
+    constexpr uint32_t kHeadInTail = 1u;           // head and tail are in the same unit
+    constexpr uint32_t kNextValid = 2u;            // `nx` holds a fetched unit, its query heads are in (or on their way to) LDS
+    constexpr uint32_t kQueueEmpty = 4u;           // the queue the wavefront is at has been found empty
+    constexpr uint32_t kExhausted = 8u;            // every queue has been found empty
+    constexpr uint32_t kDone = 16u;                // the tail has finished the last unit
+    // In the CTA-parallel launch a wavefront runs the one unit it was given: the queues count as
+    // used up from the start, so no claim is ever issued and the worker ends with its unit.
+    uint32_t st = kHeadInTail | (a.single_unit ? kExhausted : 0u);
+
     // ---- claims ------------------------------------------------------------------------
     // The compiler keeps exact counts of the loads in flight only as long as every path through
     // the ring's loop issues the same memory operations it knows of.  A claim is therefore one opaque
@@ -860,21 +871,37 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
     // every turn of the ring, adding zero to a word of the workgroup in the turns that wanted no unit;
     // 430 such atomics per us on the chip cost the stream 5 % of its rate, 7.1 against 7.5 TB/s in the
     // steady state of 2048 units of 4096 keys, more than waiting for one claim per unit does.)
-    int cq = __builtin_amdgcn_readfirstlane(xcd) & (kXcdQueues - 1), tried = 0;
-    auto claim_now = [&]() __attribute__((always_inline)) -> int { return decode_claim(a, cq, lane); };
-    // Turns a claimed counter value into a unit index.  When the queue is used up it claims from
-    // the next queues (and waits for those claims); -1 when no unit is left anywhere.
-    auto claim_resolve = [&](int k) __attribute__((always_inline)) -> int {
-        for (;;) {
-            const int q0 = dq[cq], q1 = dq[cq + 1];
-            if (k < q1 - q0) return q0 + k;
-            do {
-                cq = (cq + 1) & (kXcdQueues - 1);
-                ++tried;
-            } while (tried < kXcdQueues && dq[cq + 1] == dq[cq]);
-            if (tried >= kXcdQueues) return -1;
-            k = claim_now();
+    int cq = __builtin_amdgcn_readfirstlane(xcd) & (kXcdQueues - 1);
+    // One claim from the queue the wavefront is at: a unit index, or -1 when the queue is used up.
+    auto claim_here = [&]() __attribute__((always_inline)) -> int {
+        const int q0 = dq[cq], q1 = dq[cq + 1], k = decode_claim(a, cq, lane);
+        if (k & kAllQueuesEmpty) st |= kExhausted;
+        return k < q1 - q0 ? q0 + k : -1;
+    };
+    // That queue is used up: claims from the next ones, round trip by round trip; -1 when no unit is left
+    // anywhere.  The queues of a launch run out within a few microseconds of each other, and seven round trips
+    // are 5 us that every wavefront would spend at the very end.  So whoever has come round to the queue of its
+    // XCD, where it started, says so in that queue's counter: the others of the XCD see it with the claim that fails.
+    // Decode alone, us before / after, with the walk moved behind the unit's last step: 16 requests 118.0 / 115.9, 48 of
+    // 64 channels 78.0 / 74.7, 128 requests 773 / 770.  (A look at all eight counters with one load each took
+    // longer than the walk: 622 / 643 with 8192 units, 77 / 82 with 64 channels; it slows the claims on them.)
+    auto claim_elsewhere = [&]() __attribute__((always_inline)) -> int {
+        const int home = (int)(__smid() >> 6) & (kXcdQueues - 1);
+        int idx = -1;
+        while (idx < 0 && !(st & kExhausted)) {
+            cq = (cq + 1) & (kXcdQueues - 1);
+            if (cq == home) {
+                if (lane == 0) {
+                    uint32_t *ctr = &a.hdr->next_dunit_xcd[home][0];
+                    asm volatile("global_atomic_or %0, %1, off" ::"v"(ctr), "v"(kAllQueuesEmpty) : "memory");
+                }
+                lane_test_done();
+                st |= kExhausted;
+            } else if (dq[cq + 1] > dq[cq]) {
+                idx = claim_here();
+            }
         }
+        return idx;
     };
 
     // ---- the next unit's query heads: global memory -> LDS, asynchronously ----------------
@@ -930,15 +957,6 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
     uint32_t voff[NLD];                            // per-lane byte offsets from those
     const elem *kc = nullptr, *vc = nullptr;
     const POD_CONST int32_t *table = nullptr;
-    // State bits (one word: separate flags end up addressed through a common pointer and then
-    // live in scratch memory).
-    constexpr uint32_t kHeadInTail = 1u;           // head and tail are in the same unit
-    constexpr uint32_t kNextValid = 2u;            // `nx` holds a fetched unit, its query heads are in (or on their way to) LDS
-    constexpr uint32_t kExhausted = 8u;            // every queue has been found empty
-    constexpr uint32_t kDone = 16u;                // the tail has finished the last unit
-    // In the CTA-parallel launch a wavefront runs the one unit it was given: the queues count as
-    // used up from the start, so no claim is ever issued and the worker ends with its unit.
-    uint32_t st = kHeadInTail | (a.single_unit ? kExhausted : 0u);
     int n_iss = 0, q_mark = 0;                     // steps issued so far; their count when the last Q copy was issued
 
     // Rows past the end of a unit's last step re-read its last row (the keys are masked out of the
@@ -1017,14 +1035,22 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
             }
         }
     };
-    // Claim result -> descriptor -> query copy.  Waits for the claim and for the descriptor.
-    auto fetch_next = [&]() __attribute__((always_inline)) {
+    // Claim -> descriptor -> query copy.  Waits for the claim and for the descriptor.  Ahead of time only the queue
+    // the wavefront is at is asked; the others are, where that one is used up, when the tail has finished its unit and
+    // the wavefront has nothing else to do.
+    auto fetch_next = [&](bool ahead) __attribute__((always_inline)) {
         int idx = -1;
-        if (!(st & kExhausted)) idx = claim_resolve(claim_now());
-        nx = load_desc(max(idx, 0));
-        q_mark = idx >= 0 ? n_iss : q_mark;
-        st |= idx >= 0 ? kNextValid : kExhausted;
-        if (idx >= 0) q_dma(nx, q_cur ^ 1);
+        if (!(st & (kExhausted | kQueueEmpty))) idx = claim_here();
+        if (idx < 0 && !ahead && !(st & kExhausted)) idx = claim_elsewhere();
+        st &= ~kQueueEmpty;
+        if (idx >= 0) {
+            nx = load_desc(idx);
+            q_mark = n_iss;
+            st |= kNextValid;
+            q_dma(nx, q_cur ^ 1);
+        } else {
+            st |= kQueueEmpty;                     // (or kExhausted, set above)
+        }
     };
 
     // ---- tail: the step being computed ------------------------------------------------------------
@@ -1130,7 +1156,7 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
     {
         int idx0;
         if (seat < a.n_static_seats) idx0 = __builtin_amdgcn_readfirstlane(seat) * kWavesPerWg + wave;
-        else idx0 = claim_resolve(claim_now());
+        else idx0 = claim_here();
         if (idx0 < 0 || idx0 >= a.n_dunits) return 0;
         set_head(load_desc(idx0));
         cu = hu;
@@ -1159,7 +1185,7 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
         for (int r = 0; r < R; ++r) {
             // Claim ahead, once the head is close to the end of its unit.  The claim is waited for, which
             // at this point waits for the slot that is consumed next anyway.
-            if (r == 0 && st == kHeadInTail && hu.t1 - h_t <= kClaimAhead * STEP) fetch_next();
+            if (r == 0 && st == kHeadInTail && hu.t1 - h_t <= kClaimAhead * STEP) fetch_next(true);
             // The head moves on once it has run out of its unit, the next unit is known and the
             // tail has reached the head's unit (the ring holds at most one unit boundary).
             if (h_t >= hu.t1 && (st & (kNextValid | kHeadInTail)) == (kNextValid | kHeadInTail)) {
@@ -1182,7 +1208,7 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
                 ++n_done;
                 if (st & kHeadInTail) {
                     // the head has run out of this unit and has nowhere to go yet
-                    if (!(st & kNextValid)) fetch_next();
+                    if (!(st & kNextValid)) fetch_next(false);
                     // Nothing left: the turn is finished with empty slots (leaving the loop from
                     // inside a turn makes the compiler lose its exact load counts), then the
                     // worker returns.
@@ -1272,9 +1298,29 @@ __device__ __forceinline__ int prefill_worker_run(const KernelArgs &a, unsigned 
     return n_done;
 }
 
-// Last workgroup of a launch that used the counters leaves them at zero for the next launch.
-__device__ __forceinline__ void finish_and_reset(WsHeader *hdr, int *flag)
+// Leaves the counters at zero for the next launch (one workgroup does this).
+__device__ __forceinline__ void reset_counters(WsHeader *hdr)
 {
+    for (int i = threadIdx.x; i < kCuSlots; i += kWgThreads) hdr->cu_state[i] = 0u;
+    if (threadIdx.x < kXcdQueues) {
+        hdr->next_dunit_xcd[threadIdx.x][0] = 0u;
+        hdr->next_pitem_xcd[threadIdx.x][0] = 0u;
+    }
+    if (threadIdx.x == 0) {
+        hdr->next_id[0][0] = 0u;
+        hdr->next_id[1][0] = 0u;
+        hdr->done[0][0] = 0u;
+    }
+}
+
+// End of a launch that used the counters.  The combine kernel clears them where one follows.  Otherwise the
+// last workgroup does, which takes all of them an atomic on one counter and the wait for it: 256 decode workgroups that end
+// together are 3 us of that counter (11 ns each), after the last unit.  Decode alone, us before / after: 48 requests of 64
+// channels 74.7 / 73.1, 64 of 256 channels 430 / 426, 40 with 15 heads 72.1 / 71.4.
+__device__ __forceinline__ void finish_and_reset(const KernelArgs &a, int *flag)
+{
+    WsHeader *hdr = a.hdr;
+    if (a.combine_resets) return;
     __syncthreads();
     if (threadIdx.x == 0) {
         // (every claim of this workgroup has returned: their values have been used)
@@ -1282,16 +1328,7 @@ __device__ __forceinline__ void finish_and_reset(WsHeader *hdr, int *flag)
         *flag = (done == gridDim.x - 1) ? 1 : 0;
     }
     __syncthreads();
-    if (*flag) {
-        for (int i = threadIdx.x; i < kCuSlots; i += kWgThreads) hdr->cu_state[i] = 0u;
-        if (threadIdx.x == 0) {
-            hdr->next_id[0][0] = 0u;
-            hdr->next_id[1][0] = 0u;
-            for (int q = 0; q < kXcdQueues; ++q) hdr->next_dunit_xcd[q][0] = 0u;
-            hdr->done[0][0] = 0u;
-            for (int q = 0; q < kXcdQueues; ++q) hdr->next_pitem_xcd[q][0] = 0u;
-        }
-    }
+    if (*flag) reset_counters(hdr);
 }
 
 template <int DT, int D, int LAYOUT>
@@ -1308,7 +1345,7 @@ __global__ __launch_bounds__(kWgThreads, 2) void decode_kernel(KernelArgs a)
         if (threadIdx.x == 0)
             write_trace(a, a.n_pitems + blockIdx.x, __smid() & (kCuSlots - 1), kDecode, n_done, 0, t0, wall_clock64());
     }
-    if (!a.single_unit) finish_and_reset(a.hdr, &flag);      // (nothing was counted)
+    if (!a.single_unit) finish_and_reset(a, &flag);      // (nothing was counted)
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1573,7 +1610,7 @@ __global__ __launch_bounds__(kWgThreads) __attribute__((amdgpu_num_vgpr(kLiteVgp
         if (threadIdx.x == 0)
             write_trace(a, a.n_pitems + blockIdx.x, __smid() & (kCuSlots - 1), kDecode, n_done, 0, t_start, wall_clock64());
     }
-    if (!a.single_unit) finish_and_reset(a.hdr, &flag);      // (nothing was counted)
+    if (!a.single_unit) finish_and_reset(a, &flag);      // (nothing was counted)
 }
 
 // The prefill kernel of that configuration: the stand-alone prefill kernel, held to 208 registers
@@ -1645,7 +1682,7 @@ __global__ __launch_bounds__(kWgThreads, 2) void fused_kernel(KernelArgs a)
     }
     __syncthreads();
     if (threadIdx.x == 0 && a.trace) write_trace(a, blockIdx.x, bind[2], first, n_first, n_second, t0, t_switch);
-    finish_and_reset(hdr, &bind[3]);
+    finish_and_reset(a, &bind[3]);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1704,7 +1741,7 @@ __global__ __launch_bounds__(kWgThreads, 2) void fused_cta_kernel(KernelArgs a)
     }
     __syncthreads();
     if (threadIdx.x == 0 && a.trace) write_trace(a, blockIdx.x, bind[2], role, n_done, 0, t0, wall_clock64());
-    if (!(a.fixed_roles && a.single_unit)) finish_and_reset(hdr, &bind[3]);
+    if (!(a.fixed_roles && a.single_unit)) finish_and_reset(a, &bind[3]);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1725,6 +1762,7 @@ __global__ __launch_bounds__(kWgThreads) void combine_kernel(KernelArgs a)
     constexpr int GPW = kWgThreads / TPR;           // groups of the workgroup
     __shared__ f32x4 part_acc[GPW][TPR];
     __shared__ float part_m[GPW], part_l[GPW];
+    if (a.combine_resets && blockIdx.x == 0) reset_counters(a.hdr);
     const int sub = threadIdx.x % TPR;
     const int grp = threadIdx.x / TPR;
     // Workgroups of prefill rows come first; the two kinds of rows have their own numbers of splits.

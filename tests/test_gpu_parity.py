@@ -271,6 +271,28 @@ def test_decode_stream_crosses_many_short_units():
         assert info.fused_grid > 1000        # one decode worker per planned unit plus the prefill items
 
 
+@pytest.mark.parametrize("mode", ["fused", "serial", "fused_cta", "decode_only"])
+@pytest.mark.parametrize("lens,chunk", [([40] * 70 + [9], 512), ([700] * 9 + [33] * 30, 128)], ids=["whole", "split"])
+def test_counters_are_zero_after_every_call(mode, lens, chunk):
+    """The combine kernel clears the counters in calls that have one, the last workgroup of the attention kernel in
+    the others (nothing to merge, or merging switched off): every unit is run once in each of several calls."""
+    batch = wl.make_batch(f"counters-{len(lens)}", prefill=[(70, 200)], decode_kv_lens=lens, n_q_heads=8, n_kv_heads=4,
+                          head_dim=64, dtype=wl.F16, seed=12, block_size=16)
+    dev_batch = batch.to("cuda:0")
+    attn = pod.HybridAttention(dev_batch, n_compute_units=2, decode_chunk=chunk)
+    assert (attn.info.n_combine > 0) == (chunk == 128) and attn.info.n_decode_units > 8
+    rows = slice(batch.n_prefill_rows, None) if mode == "decode_only" else slice(None)
+    first = attn.ws_ptr - attn.workspace.data_ptr()
+    attn.enable_event_log()
+    for flag in (0, pod.MODE_FLAG_NO_COMBINE, 0):
+        out = attn.forward(dev_batch, mode=pod.MODES[mode] | flag)
+        ev = attn.read_event_log()
+        assert np.sort(ev["item"][ev["kind"] == 1]).tolist() == list(range(attn.info.n_decode_units))
+        assert not attn.workspace[first:first + 4 * 1024 + 20 * 128].any()
+    assert np.abs(out.to(torch.float64).cpu().numpy()[rows] - oracle_out(batch)[rows]).max() <= TOL[batch.dtype]
+    attn.close()
+
+
 def test_event_log_holds_every_item_and_unit_once():
     """The event log (begin and end of every prefill item and decode unit of one launch) names each
     work id exactly once, with sane times, and logging does not change the result."""
