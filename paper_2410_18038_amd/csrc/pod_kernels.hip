@@ -549,6 +549,11 @@ __device__ __forceinline__ void prefill_item_run(const KernelArgs &a, const Pref
     }
     TileBlocks blocks_ahead = tile_blocks(2);                // for the K loads of the first iteration
     wait_all_loads();
+    // The compiler has to see the queries arrive here: left to their first use in the loop, its wait for them is a
+    // wait for everything in every turn, and each tile's matrix instructions then start when the tile loads
+    // issued just before them have landed.
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(q[ks]));
     __syncthreads();
     // Two score buffers swap roles from one tile to the next; the loop body exists twice (even
     // and odd tiles) so that the swap is a matter of names, not of 32 register moves per tile, and
