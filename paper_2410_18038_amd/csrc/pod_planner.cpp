@@ -395,8 +395,14 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
             const int worth_merging = shortest + (prm.head_dim > 128 ? 16 : 112);
             const int beside_items = layout == kLayoutPagedAny ? longest_item / 8 + 150
                                                                : (prm.head_dim > 128 ? longest_item / 5 : longest_item / 5 * 2) + 100;
+            // All of that holds where the workers have slots of their own.  With an item for every slot, the one
+            // that a worker's slot gets starts when the worker is done and ends that much later: 512 items of 32K
+            // keys beside 4 x 4096 of 4 heads 1128 us whole, 979 cut,
+            // beside 16 x 4096 1146 / 976; 64 channels, 2048 + 6144 beside 1 x 3000 216 / 171.
+            const int64_t whole_units = units_of_length(prm, seq_meta, longest_decode);
+            const bool own_slots = n_items + (whole_units + kWavesPerWg - 1) / kWavesPerWg <= (int64_t)kSlotsPerUnit * n_cus;
             if (longest_decode <= worth_merging ||
-                (longest_item > 0 && plan.centries.empty() && longest_decode <= beside_items && units_of_length(prm, seq_meta, longest_decode) <= waves))
+                (longest_item > 0 && plan.centries.empty() && longest_decode <= beside_items && whole_units <= waves && own_slots))
                 chunk = round_up(std::max(longest_decode, kDecodeStep), kDecodeStep);
             else {
                 // the shortest length, in steps from `shortest`, that makes units for one round; two shares at the most

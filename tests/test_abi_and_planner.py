@@ -693,3 +693,18 @@ def test_event_log_and_queue_arguments_are_checked():
             pod.pod_attn_plan_decode_queue(plan, q)
     assert len(plan.decode_queues()) == 8
     plan.close()
+
+
+def test_requests_stay_whole_beside_items_only_where_workers_have_their_own_slots():
+    """A decode worker that a prefill item waits for is cut short: with an item for every slot of the chip requests
+    that the items outlast are cut, with slots left for the workers they stay whole."""
+    for heads, q_len, whole in [((32, 4), 2048, False), ((32, 4), 2032, True), ((8, 2), 512, True)]:
+        prm, meta = meta_only("own-slots", [(q_len, 30000 + q_len)], [3000] * 2, hq=heads[0], hkv=heads[1])
+        prm.prefill_split_len = 1 << 20                 # (no split, nothing else to merge)
+        plan = pod.pod_attn_plan_create(prm, meta)
+        info = plan.info()
+        workers = (2 * heads[1] + 3) // 4               # with whole requests
+        assert info.max_prefill_splits == 1 and info.n_prefill_items > 0
+        assert (info.n_prefill_items + workers <= 512) == whole
+        assert (info.max_decode_splits == 1) == whole
+        plan.close()
