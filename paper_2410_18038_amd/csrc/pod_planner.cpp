@@ -589,22 +589,19 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
     // the hardware's own order puts one of each on a unit (it deals workgroups to the units in turn),
     // and binding by index saves the chain of ticket, seat and claim at the start (3-4 us, 256 seats being
     // handed out one per 11 ns) and the claims and seats after the last item.  us per call, by ticket / by index:
-    // 4 items + 41 workers 18.0 / 13.8; 200 items (64 channels) 88.9 / 82.3; 140 (15 heads) 87.9 / 80.3;
-    // 224 (512 -> 448 tokens + 16 decodes) 136.8 / 135.3; but with an item for nearly every unit the older
-    // workgroup of each is a prefill one, and the stream pays more than that: 240 items 677 / 686, 256 items
-    // 136.7 / 141.  At 256 channels decode workers go first, for the same reason: 256 items 472 / 465,
-    // 192 items 456 / 448 (prefill first 461).
-    // By ticket / items first / workers first over 2048 cached keys, 32 / 8 heads of 128 channels, 16 decodes at 8192,
-    // 64 at 4096, 120 at 2000: 192 items 131 / 117 / 130, 201 / 192 / 200, 189 / 180 / 189; 224 items 130 / 116 / 121,
-    // 201 / 195 / 200, 188 / 184 / 191; 256 items 129 / 121 / 121, 201 / 207 / 204, 186 / 196 / 193: above 7/8 of
-    // the units it depends on the decodes, and workers first is the better of the two for none.  32 / 32 heads are within
-    // 1 % either way.  64 channels gain by index up to 256 items as well (119 / 112 / 112 with 64 decodes): the
-    // line is drawn for 128.  256 channels, 128 to 256 items: workers first 2 to 12 % ahead of tickets,
-    // items first within 4 %.
+    // 4 items + 41 workers 17.1 / 13.5; 200 items (64 channels) 89.1 / 79.9; 140 (15 heads) 82.3 / 75.4; 224 (448
+    // tokens + 16 decodes, 32 / 8 heads) 163.2 / 161.2.  With an item for every unit (225 to 256 items, 512 to 2048
+    // tokens beside 16 to 120 decodes; ranges over 16 to 32 batches each): 64 channels 0.92 to 1.00 of the time by
+    // ticket, 128 channels with 8 query heads per K/V head 0.93 to 0.99, with 4 0.97 to 1.00, with 2 0.98 to 1.05,
+    // with one 0.99 to 1.02: the line is at 7/8 of the units there (few heads per K/V head mean much to stream, and
+    // the older workgroup of a unit is a prefill one).  At 256 channels decode workers go first, for the
+    // same reason: 256 items 471 / 452 (items first 471), 192 items 456 / 448 (461).  Workers first at up to 128
+    // channels is within 2 % of items first but for 8 query heads per K/V head, 0.96 to 1.10 of the time by ticket.
     if (prm.policy == POD_POLICY_AUTO && !plan.pitems.empty() && plan.n_dwgs > 0) {
         const int n_items = (int)plan.pitems.size();
         int rule = kRolesByTicket;
-        if (n_items + plan.n_dwgs <= n_cus || (prm.head_dim <= 128 && n_items <= n_cus / 8 * 7)) rule = kPrefillFirst;
+        const int most_items = prm.head_dim < 128 || group >= 3 ? n_cus : n_cus / 8 * 7;
+        if (n_items + plan.n_dwgs <= n_cus || (prm.head_dim <= 128 && n_items <= most_items)) rule = kPrefillFirst;
         else if (prm.head_dim > 128 && n_items <= n_cus && plan.n_dwgs == n_cus) rule = kDecodeFirst;
         plan.fixed_roles = rule;
     }

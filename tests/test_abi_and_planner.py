@@ -708,3 +708,17 @@ def test_requests_stay_whole_beside_items_only_where_workers_have_their_own_slot
         assert (info.n_prefill_items + workers <= 512) == whole
         assert (info.max_decode_splits == 1) == whole
         plan.close()
+
+
+def test_roles_go_by_index_up_to_an_item_for_every_unit_where_heads_are_shared_or_short():
+    """At 64 channels and with three or more query heads per K/V head items go first by index up to one per compute
+    unit, with fewer heads at 128 channels up to 7/8 of the units (16 units; 14, 16 and 18 items)."""
+    from tests.helpers import role_rule
+    for d, hq, hkv, n_items, want in [(64, 4, 2, 16, "prefill"), (64, 4, 2, 18, "ticket"), (128, 6, 2, 16, "prefill"),
+                                      (128, 8, 2, 18, "ticket"), (128, 4, 2, 14, "prefill"), (128, 4, 2, 16, "ticket")]:
+        q_len = n_items // hkv * 128 // (hq // hkv)
+        prm, meta = meta_only("roles", [(q_len, q_len + 77)], [5000] * 9, hq=hq, hkv=hkv, d=d)
+        prm.n_compute_units = 16
+        plan = pod.pod_attn_plan_create(prm, meta)
+        assert (plan.info().n_prefill_items, role_rule(plan)) == (n_items, want)
+        plan.close()
