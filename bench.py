@@ -359,6 +359,8 @@ def run_config(config, batch_index, steps, warmup, want_cpu, main_mode, torch, p
     else:
         achieved, peak, unit = flops / (kernel_us * 1e-6) / 1e12, PEAK_MFMA_16BIT / 1e12, "TFLOP/s"
     launched = {"fused": "fused_kernel", "fused_cta": "fused_cta_kernel"}.get(main_mode)
+    if main_mode == "fused" and info.prefill_heavy_chosen:
+        launched = KERNEL_OF_MODE["fused_heavy"]
     traffic = MEASURED_TRAFFIC_BYTES.get((config, batch_index), {}).get(launched)
     head = {
         "metric": "hybrid-batch attention us per batch (fused prefill+decode)",

@@ -86,9 +86,11 @@ typedef enum {
  * that nothing else fits; the trace records show where each workgroup ran).  Same result within
  * rounding (the decode kernel adds its weights in another order).  Built for head_dim 128 and for
  * contiguous caches or paged ones with power-of-two blocks of at least 16 tokens; otherwise
- * POD_ERR_UNSUPPORTED.  Not chosen automatically: on this chip it ends a prefill-heavy batch
- * 8-10 % sooner in a sustained loop (2048 tokens at 32K beside 32 decodes at 32K: 1119 us against
- * 1233), 4-11 % sooner when launches are spaced out, and is 6-35 % slower on decode-bound batches.
+ * POD_ERR_UNSUPPORTED.  POD_MODE_FUSED takes it by itself under the automatic policy where it is
+ * ahead (an item for every workgroup slot, 200 us or more of matrix time, 0.8 to 3.3 times the byte
+ * time of the decode stream: 2048 tokens at 32K beside 32 decodes at 32K 1114 us against 1198), in calls
+ * that are not recorded into a graph and write no trace or event log; it is 6-35 % slower on
+ * decode-bound batches.
  * Also accepted with POD_MODE_PREFILL_ONLY and POD_MODE_DECODE_ONLY, which then run that
  * configuration's prefill or decode kernel alone.  Like POD_MODE_STREAMS it creates streams and
  * events on first use, is not meant for graph capture, and is rejected by pod_attn_forward_static. */
@@ -153,7 +155,7 @@ typedef struct {
                                    for and its prefill work outweighs its decode stream (FLOP time
                                    at the matrix peak above 1.2 x byte time at the HBM peak): the
                                    caller may OR POD_MODE_FLAG_PREFILL_HEAVY into POD_MODE_FUSED  */
-    int32_t reserved0;
+    int32_t prefill_heavy_chosen;  /* 1 when POD_MODE_FUSED takes that configuration by itself (see there) */
 } pod_attn_plan_info;
 
 typedef struct pod_attn_plan pod_attn_plan;   /* opaque, host memory, owned by the caller */
@@ -246,8 +248,9 @@ pod_status pod_attn_plan_upload(const pod_attn_plan *plan, void *workspace, size
  * The call only launches kernels on `stream` (no allocation, no memset, no wait on the host), so
  * in the FUSED, SERIAL and single-operation modes it may be recorded into a HIP graph; the
  * STREAMS mode (and the prefill-heavy configuration) creates two side streams per GPU, kept until the
- * process ends, and three events per plan, destroyed with it, on first use (that first call must not
- * run beside another call on the same plan from a second host thread) and is not meant for capture.
+ * process ends, and three events per plan, destroyed with it, on first use and is not meant for capture.
+ * For plans whose FUSED calls take the prefill-heavy configuration by themselves pod_attn_plan_upload
+ * creates them; such a call forks from `stream` and joins it again, and behaves in stream order like any other.
  * Two forward calls that use the same workspace must not overlap in time.
  */
 pod_status pod_attn_forward(const void *prefill_q, const void *decode_q,

@@ -147,6 +147,39 @@ pod_status side_streams(hipStream_t *s0, hipStream_t *s1)
     return POD_OK;
 }
 
+// Held while a call of a two-kernel mode enqueues: a wait refers to what its event was last recorded for, and
+// the streams, and the events of a plan, are shared by all host threads.
+std::mutex g_two_streams_mu;
+
+// The events of a plan, on the current device (under the lock above).
+pod_status ensure_events(pod::Plan &p)
+{
+    for (void *&ev : p.events)
+        if (!ev) {
+            hipEvent_t ne;
+            const hipError_t e = hipEventCreateWithFlags(&ne, hipEventDisableTiming);
+            if (e != hipSuccess) return fail_hip(e, "creating event");
+            ev = ne;
+            if (hipGetDevice(&p.events_device) != hipSuccess) p.events_device = -1;
+        }
+    return POD_OK;
+}
+
+// May this fused call take the prefill-heavy configuration?  Not where a launch is being recorded (graph
+// capture), where the records of the fused kernel are asked for, or where streams or events would have to be
+// created first.
+bool heavy_is_ready(const pod::Plan &p, hipStream_t s)
+{
+    if (!p.heavy_pays || p.trace || p.evlog || !p.events[2]) return false;
+    int dev = -1;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusActive;
+    if (hipGetDevice(&dev) != hipSuccess || dev != p.events_device || hipStreamIsCapturing(s, &capture) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return capture == hipStreamCaptureStatusNone;
+}
+
 // Clear the counters at the head of `workspace` (with a kernel, not a memset) and copy the plan's
 // work tables behind them; returns when the copies have completed.
 pod_status upload_tables(const pod::Plan &p, void *workspace, hipStream_t s)
@@ -240,7 +273,7 @@ pod_status pod_attn_plan_info_get(const pod_attn_plan *plan, pod_attn_plan_info 
     info->n_partial_rows = p.n_partial_rows;
     info->workspace_bytes = (int64_t)p.ws_bytes;
     info->prefill_heavy_advised = p.heavy_advised ? 1 : 0;
-    info->reserved0 = 0;
+    info->prefill_heavy_chosen = p.heavy_pays ? 1 : 0;
     return POD_OK;
 }
 
@@ -315,7 +348,15 @@ pod_status pod_attn_plan_upload(const pod_attn_plan *plan, void *workspace, size
     const pod::Plan &p = plan->p;
     if (!workspace || workspace_bytes < p.ws_bytes) return fail(POD_ERR_WORKSPACE, "workspace missing or too small");
     if (((uintptr_t)workspace & 255u) != 0) return fail(POD_ERR_WORKSPACE, "workspace must be 256-byte aligned");
-    return upload_tables(p, workspace, (hipStream_t)stream);
+    const pod_status st = upload_tables(p, workspace, (hipStream_t)stream);
+    if (st == POD_OK && p.heavy_pays) {
+        // What a fused call of this plan needs to take the prefill-heavy configuration is made here, so that the
+        // call itself creates nothing.  Without it the fused kernel runs.
+        std::lock_guard<std::mutex> lock(g_two_streams_mu);
+        hipStream_t s0 = nullptr, s1 = nullptr;
+        if (side_streams(&s0, &s1) != POD_OK || ensure_events(const_cast<pod_attn_plan *>(plan)->p) != POD_OK) (void)hipGetLastError();
+    }
+    return st;
 }
 
 static pod_status forward_impl(const void *prefill_q, const void *decode_q, const void *k_cache,
@@ -411,17 +452,10 @@ static pod_status forward_impl(const void *prefill_q, const void *decode_q, cons
     // back into the caller's stream; the merge follows on the caller's stream.
     auto two_streams = [&](int prefill_kind, int decode_kind) -> pod_status {
         hipStream_t s0 = nullptr, s1 = nullptr;
-        {
-            const pod_status ss = side_streams(&s0, &s1);
-            if (ss != POD_OK) return ss;
-        }
-        for (void *&ev : p.events)
-            if (!ev) {
-                hipEvent_t ne;
-                hipError_t ce = hipEventCreateWithFlags(&ne, hipEventDisableTiming);
-                if (ce != hipSuccess) return fail_hip(ce, "creating event");
-                ev = ne;
-            }
+        std::lock_guard<std::mutex> lock(g_two_streams_mu);
+        pod_status st = side_streams(&s0, &s1);
+        if (st == POD_OK) st = ensure_events(p);
+        if (st != POD_OK) return st;
         hipEvent_t fork = (hipEvent_t)p.events[0], j0 = (hipEvent_t)p.events[1], j1 = (hipEvent_t)p.events[2];
         auto chk = [&](hipError_t x) { if (e == hipSuccess) e = x; };
         chk(hipEventRecord(fork, s));
@@ -439,7 +473,7 @@ static pod_status forward_impl(const void *prefill_q, const void *decode_q, cons
 
     switch (mode) {
     case POD_MODE_FUSED:
-        if (heavy) {
+        if (heavy || (!cta_parallel && !use_static && heavy_is_ready(p, s))) {
             // two prefill workgroups and one light decode workgroup per compute unit, from two kernels
             if (p.prm.n_prefill == 0 || p.prm.n_decode == 0) {
                 go(p.prm.n_decode == 0 ? pod::kLaunchPrefillHeavy : pod::kLaunchDecodeLite, a, s);

@@ -622,6 +622,21 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
         const bool block_wise = prm.block_size == 0 || (prm.block_size >= 16 && (prm.block_size & (prm.block_size - 1)) == 0);
         plan.heavy_advised = prm.head_dim == 128 && block_wise && prm.n_prefill > 0 && prm.n_decode > 0 &&
                              flop_time > 1.2 * byte_time;
+        // The automatic policy takes that configuration where it was ahead by more than its two streams and three
+        // events cost (20 us a call): an item for every slot, so that decode workers of the fused launch hold up items,
+        // enough prefill to make up for the light decode kernel, and enough decode to be worth hiding.
+        // fused / prefill-heavy, us, by matrix time at the peak (us) and its ratio to the byte time of the decode
+        // stream: 32 / 4 heads 2048 tokens at 32K beside 32 x 32K (426, 2.1) 1198 / 1114, 8192 tokens beside 32 x 32K
+        // (220, 1.1) 743 / 659; 32 / 8 heads 4096 at 16K beside 32 x 32K (385, 0.95) 1181 / 1105, 8192 beside 32 x 8K (220,
+        // 2.2) 620 / 580; 32 / 32 heads 2048 at 32K beside 16 x 4K (426, 3.2) 1089 / 1036.  Outside: ratio 0.54 (220)
+        // 903 / 868, 0.24 (96) 579 / 692; 3.8 (385) 920 / 906, 6.6 (220) 539 / 549; 96 us of matrix time, ratio 1.9 268 /
+        // 279; an item for every second slot (210, 1.04) 737 / 735.
+        double decode_tokens = 0.0;
+        for (int r = prm.n_prefill; r < n_req; ++r) decode_tokens += seq_meta[4 * r + 2];
+        const double decode_time = decode_tokens * prm.n_kv_heads * prm.head_dim * 4.0 / 8.0e12;
+        plan.heavy_pays = prm.policy == POD_POLICY_AUTO && prm.head_dim == 128 && block_wise && prm.n_decode > 0 &&
+                          (int)plan.pitems.size() >= kSlotsPerUnit * n_cus && flop_time >= 200e-6 &&
+                          flop_time >= 0.8 * decode_time && flop_time <= 3.3 * decode_time;
     }
 
     // ---- workspace layout --------------------------------------------------------------

@@ -18,6 +18,7 @@ struct Plan {
     int group = 1;
     std::vector<int32_t> meta;              // host copy of seq_meta
     bool heavy_advised = false;             // see pod_attn_plan_info.prefill_heavy_advised
+    bool heavy_pays = false;                // POD_MODE_FUSED takes the prefill-heavy configuration where it can
     std::vector<PrefillItem> pitems;
     // The same items in the order the stand-alone prefill kernels take them by workgroup index: the
     // hardware deals workgroups to the XCDs round-robin, so workgroup b gets an item of queue b % 8.
@@ -42,8 +43,10 @@ struct Plan {
     // byte offsets inside the workspace (each 256-byte aligned)
     size_t off_pitems = 0, off_pitems_by_wg = 0, off_pitem_of_wg = 0, off_dunits = 0, off_crows = 0, off_dq = 0, off_part_o = 0, off_part_ml = 0;
     size_t ws_bytes = 0;
-    // events of the two-kernel modes (fork, two joins), created on first use
+    // events of the two-kernel modes (fork, two joins), created on first use, or with the upload of a plan that
+    // takes the prefill-heavy configuration by itself
     void *events[3] = {nullptr, nullptr, nullptr};
+    int events_device = -1;                 // the GPU they were created on
     void *trace = nullptr;                  // device buffer for TraceRecords, or null
     size_t trace_bytes = 0;
     void *evlog = nullptr;                  // device buffer for the event log, or null

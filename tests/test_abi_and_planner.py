@@ -722,3 +722,18 @@ def test_roles_go_by_index_up_to_an_item_for_every_unit_where_heads_are_shared_o
         plan = pod.pod_attn_plan_create(prm, meta)
         assert (plan.info().n_prefill_items, role_rule(plan)) == (n_items, want)
         plan.close()
+
+
+def test_fused_calls_take_the_prefill_heavy_configuration_where_every_slot_has_an_item():
+    """2048 tokens at 32K beside 32 decodes at 32K take it under the automatic policy; not with another policy, less matrix
+    time, items for half of the slots, a decode stream that is short or long beside it, or a shape it is not built for."""
+    base = dict(prefill=[(2048, 32768)], decodes=[32768] * 32, hq=32, hkv=4)
+    cases = [({}, {}, 1), ({}, {"policy": pod.POLICY_ALTERNATE}, 0), ({}, {"policy": pod.POLICY_PROPORTIONAL}, 0),
+             ({"prefill": [(2048, 8192)]}, {}, 0), ({"prefill": [(1024, 32768)]}, {}, 0), ({"decodes": [4096] * 16}, {}, 0),
+             ({"decodes": [32768] * 100}, {}, 0), ({"decodes": []}, {}, 0), ({"d": 64}, {}, 0), ({"block_size": 48}, {}, 0)]
+    for change, tuning, want in cases:
+        prm, meta = meta_only("heavy", **{**base, **change})
+        prm.policy = tuning.get("policy", pod.POLICY_AUTO)
+        plan = pod.pod_attn_plan_create(prm, meta)
+        assert plan.info().prefill_heavy_chosen == want, (change, tuning)
+        plan.close()

@@ -725,3 +725,60 @@ def test_prefill_heavy_configuration_with_many_short_units_and_long_contexts():
     assert bool(torch.isfinite(out.to(torch.float32)).all())
     assert np.abs(got - want).max() <= TOL[big.dtype]
     attn.close()
+
+
+def test_fused_calls_that_take_the_prefill_heavy_configuration_keep_stream_order_threads_and_capture():
+    """A plan whose fused calls fork to the library's side streams (the MFMA-bound benchmark batch): the call reads what
+    its stream has just written and is read by what follows on it, two host threads may share the plan, each with its
+    stream and workspace, and a recorded call runs the one fused kernel, with the same bits."""
+    import threading
+    batch = wl.config_batch(4, device="cuda:0")
+    attn = pod.HybridAttention(batch)
+    want = attn.forward(batch, mode=pod.MODES["serial"]).clone()
+    queries = batch.prefill_q.clone(), batch.decode_q.clone()
+
+    def run(stream, ws_ptr, out, results):
+        with torch.cuda.stream(stream):
+            copies = []
+            for i in range(3):
+                q_p, q_d = torch.zeros_like(queries[0]), torch.zeros_like(queries[1])
+                q_p.copy_(queries[0])
+                q_d.copy_(queries[1])
+                out.fill_(float("nan"))
+                pod.pod_attn_forward(q_p.data_ptr(), q_d.data_ptr(), batch.k_cache.data_ptr(), batch.v_cache.data_ptr(),
+                                     attn.seq_meta_dev.data_ptr(), batch.block_table.data_ptr(), out.data_ptr(), attn.plan,
+                                     ws_ptr, attn.ws_bytes, pod.MODE_FUSED, stream.cuda_stream)
+                copies.append(out.clone())
+                out.zero_()
+            results.extend(copies)
+
+    results, threads, spaces = [], [], []
+    for _ in range(2):
+        stream = torch.cuda.Stream()
+        space = torch.empty(attn.ws_bytes + 256, dtype=torch.uint8, device="cuda:0")
+        ws_ptr = (space.data_ptr() + 255) & ~255
+        pod.pod_attn_plan_upload(attn.plan, ws_ptr, attn.ws_bytes, stream.cuda_stream)
+        spaces.append(space)
+        threads.append(threading.Thread(target=run, args=(stream, ws_ptr, torch.empty_like(want), results)))
+    torch.cuda.synchronize()
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert len(results) == 6
+    for got in results:
+        assert (got.float() - want.float()).abs().max().item() <= TOL[batch.dtype]
+
+    out = torch.empty_like(want)
+    eager = attn.forward(batch).clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        attn.forward(batch, out=out)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16), want.view(torch.int16))
+        assert (attn.forward(batch).float() - eager.float()).abs().max().item() == 0
+    attn.close()
