@@ -752,14 +752,17 @@ def test_fused_calls_that_take_the_prefill_heavy_configuration_keep_stream_order
                 out.zero_()
             results.extend(copies)
 
-    results, threads, spaces = [], [], []
-    for _ in range(2):
+    # Memory that goes to other streams is allocated first and waited for: until then kernels of this stream may
+    # still be writing to what the allocator hands out again (the first call's output).
+    spaces = [torch.empty(attn.ws_bytes + 256, dtype=torch.uint8, device="cuda:0") for _ in range(2)]
+    outs = [torch.empty_like(want) for _ in range(2)]
+    torch.cuda.synchronize()
+    results, threads = [], []
+    for space, out in zip(spaces, outs):
         stream = torch.cuda.Stream()
-        space = torch.empty(attn.ws_bytes + 256, dtype=torch.uint8, device="cuda:0")
         ws_ptr = (space.data_ptr() + 255) & ~255
         pod.pod_attn_plan_upload(attn.plan, ws_ptr, attn.ws_bytes, stream.cuda_stream)
-        spaces.append(space)
-        threads.append(threading.Thread(target=run, args=(stream, ws_ptr, torch.empty_like(want), results)))
+        threads.append(threading.Thread(target=run, args=(stream, ws_ptr, out, results)))
     torch.cuda.synchronize()
     for t in threads:
         t.start()
