@@ -115,6 +115,7 @@ pod::KernelArgs make_args(const pod::Plan &p, const void *prefill_q, const void 
     a.n_dctas = ((int)p.dunits.size() + pod::kWavesPerWg - 1) / pod::kWavesPerWg;
     a.fixed_roles = pod::kRolesByTicket;
     a.n_prefill_rows = (int)p.n_prefill_rows;
+    a.decode_prow0 = (int)p.decode_prow0;
     a.p_ratio = p.p_ratio;
     a.d_ratio = p.d_ratio;
     a.scale_log2 = p.prm.softmax_scale * 1.4426950408889634f;
@@ -208,6 +209,8 @@ pod_status upload_tables(const pod::Plan &p, void *workspace, hipStream_t s)
         end = begin + part.bytes;
     }
     std::memset(tables.get() + end, 0, bytes - end);
+    pod::DecodeUnit *units = (pod::DecodeUnit *)(tables.get() + (p.off_dunits - p.off_pitems));
+    for (size_t i = 0; i < p.unit_splits.size(); ++i) units[i].split |= p.unit_splits[i] << pod::kSplitBits;
     e = hipMemcpyAsync(ws + p.off_pitems, tables.get(), bytes, hipMemcpyHostToDevice, s);
     if (e != hipSuccess) { (void)hipStreamSynchronize(s); return fail_hip(e, "copying plan tables"); }
     e = hipStreamSynchronize(s);
@@ -442,6 +445,14 @@ static pod_status forward_impl(const void *prefill_q, const void *decode_q, cons
     only_d.crows = a.crows + p.n_crows_prefill;
     only_d.n_crows = a.n_crows - p.n_crows_prefill;
 
+    // Where the decode units merge their groups the combine kernel is left with the prefill rows.  (The light decode
+    // kernel does not merge.)
+    const bool two_kernels = heavy || (mode == POD_MODE_FUSED && !cta_parallel && !use_static && heavy_is_ready(p, s));
+    if (p.units_merge && !no_combine && !two_kernels) {
+        a.arrived = a.hdr->arrived;
+        a.n_crows = p.n_crows_prefill;
+        only_d.n_crows = 0;
+    }
     // The counters are cleared by the combine kernel of the call where it has one.
     if (!no_combine) {
         only_d.combine_resets = only_d.n_crows > 0;
@@ -473,7 +484,7 @@ static pod_status forward_impl(const void *prefill_q, const void *decode_q, cons
 
     switch (mode) {
     case POD_MODE_FUSED:
-        if (heavy || (!cta_parallel && !use_static && heavy_is_ready(p, s))) {
+        if (two_kernels) {
             // two prefill workgroups and one light decode workgroup per compute unit, from two kernels
             if (p.prm.n_prefill == 0 || p.prm.n_decode == 0) {
                 go(p.prm.n_decode == 0 ? pod::kLaunchPrefillHeavy : pod::kLaunchDecodeLite, a, s);

@@ -66,9 +66,12 @@ struct PrefillItem {
 struct DecodeUnit {
     int32_t req, kv_head, t0, t1;
     int32_t prow0;                         // first partial row (group rows), or -1
-    int32_t split;
+    int32_t split;                         // in the device's table, where units merge their groups, with the number of
+                                           // splits << kSplitBits added
     int32_t q_start, cache_row;            // copied from the request: a unit starts with one lookup
 };
+constexpr int kMergeSplits = 8;            // up to this many splits the last unit of a group merges them itself
+constexpr int kSplitBits = 24;
 
 // One group of output rows merged from split partials (host only; the kernel reads CombineRows).
 struct CombineEntry {
@@ -100,7 +103,10 @@ struct WsHeader {
     uint32_t next_pitem_xcd[kXcdQueues][32];
     // Next decode unit of each per-XCD queue (offset inside the queue), claimed by wavefronts.
     uint32_t next_dunit_xcd[kXcdQueues][32];
-    uint32_t reserved[512][32];            // zero; not used (the block of counters at the head of a workspace keeps its size)
+    // Units that have stored their partials, for the groups of a plan whose last units merge: the counter of a group
+    // is the word whose index is its first decode partial row (a plan of one round of wavefronts has up to
+    // 4 units a compute unit and 16 rows a unit).  The unit that merges clears it.
+    uint32_t arrived[512 * 32];
 };
 
 // Set in the counter of an XCD's decode queue once a wavefront of that XCD has found every queue used up.
@@ -167,6 +173,7 @@ struct KernelArgs {
     float *part_ml;                        // [n_partial_rows][2]  running max (log2 domain), weight sum
     WsHeader *hdr;
     TraceRecord *trace;                    // optional: one record per workgroup of the attention kernels
+    uint32_t *arrived;                     // decode units merge their groups (WsHeader::arrived), or null: the combine kernel does
     uint32_t *evlog;                       // optional: event log (16-byte header, then EventRecords)
     uint32_t evlog_cap;                    // records the event log can hold
     int64_t kv_seq_stride;
@@ -183,6 +190,7 @@ struct KernelArgs {
     int32_t combine_groups[2];             // [op]: thread groups of the combine kernel that share a row's splits
     int32_t n_pitems, n_dunits, n_dwgs;      // n_dwgs: decode worker workgroups
     int32_t n_prefill_rows;
+    int32_t decode_prow0;                  // first decode partial row
     int32_t fused_grid;
     int32_t pq_begin[kXcdQueues + 1];      // prefill queue q holds items pq_begin[q] .. pq_begin[q+1]-1
     const int32_t *dq_begin;               // [kXcdQueues + 1]: decode queue q holds units dq_begin[q] .. dq_begin[q+1]-1

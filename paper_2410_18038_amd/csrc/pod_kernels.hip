@@ -173,7 +173,7 @@ __device__ __forceinline__ void store16_untracked(void *p, u32x4 v)
 }
 __device__ __forceinline__ void store8_untracked(void *p, u32x2 v)
 {
-    asm volatile("global_store_dwordx2 %0, %1, off" ::"v"(p), "v"(v) : "memory");
+    asm volatile("global_store_dwordx2 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory");
 }
 
 // Append one record to the event log (one lane calls this).
@@ -789,13 +789,12 @@ __device__ __forceinline__ int prefill_open_queue(const KernelArgs &a, int q)
     return open == 0u ? -1 : (q + __builtin_ctz(turned)) & (kXcdQueues - 1);
 }
 
-// One claim from decode queue cq.  It is waited for on the spot and is one opaque instruction pair
-// (see "claims" in the decode worker).
-__device__ __forceinline__ int decode_claim(const KernelArgs &a, int cq, int lane)
+// Adds one to a counter for the wavefront and returns what it held.  It is waited for on the spot and is one opaque
+// instruction pair (see "claims" in the decode worker).
+__device__ __forceinline__ int count_one(uint32_t *ctr, int lane)
 {
     uint32_t v = 0;
     if (lane == 0) {
-        uint32_t *ctr = &a.hdr->next_dunit_xcd[cq][0];
         asm volatile("global_atomic_add %0, %1, %2, off sc0\n\ts_waitcnt vmcnt(0)"
                      : "=&v"(v) : "v"(ctr), "v"(1u) : "memory");
     }
@@ -803,9 +802,97 @@ __device__ __forceinline__ int decode_claim(const KernelArgs &a, int cq, int lan
     return (int)__builtin_amdgcn_readfirstlane(v);
 }
 
+// One claim from decode queue cq.
+__device__ __forceinline__ int decode_claim(const KernelArgs &a, int cq, int lane)
+{
+    return count_one(&a.hdr->next_dunit_xcd[cq][0], lane);
+}
+
 template <int N_OPS> __device__ __forceinline__ void wait_loads_but()
 {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N_OPS) : "memory");
+}
+
+// Merges the decode group of a unit whose partial rows this wavefront has just stored, if all other units of the
+// group have stored theirs (the combine kernel's merge, in the order of the splits, whoever comes last).  The
+// rows were written through (sc1) and are complete when the wavefront counts itself in; the loads below ask for
+// coherent data (agent scope), whichever XCD wrote it.  `lds` is the wavefront's own area.
+// A kernel launch less, us before / after: 4 heads of 64 channels, 128 tokens beside 8 decodes 13.4 / 10.6; 8 decodes of
+// 32 heads at 0.5K-4K 54.7 / 53.1; 16 decodes of 160 keys 10.9 / 8.6.  What bounds the merge is the three round
+// trips of the wavefront that comes last (its stores, the counter, the partials), about 3 us; rows of all splits are fetched
+// together, which is why it stops at 8 of them: 94 splits by one wavefront would be 12 fetches.
+template <int DT, int D>
+__device__ __forceinline__ void merge_if_last(const KernelArgs &a, POD_LDS unsigned char *lds, int unit, int lane)
+{
+    using N = Num<DT>;
+    const POD_CONST int32_t *w = (const POD_CONST int32_t *)a.dunits + 8 * (int64_t)unit;
+    const int kv_head = w[1], prow0 = w[4], n_splits = w[5] >> kSplitBits, split = w[5] & ((1 << kSplitBits) - 1), q_start = w[6];
+    const int group = a.group;
+    if (prow0 < 0) return;
+    const int first = prow0 - split * group;       // the group's first partial row
+    uint32_t *ctr = a.arrived + (first - a.decode_prow0);
+    wait_all_loads();                              // (stores count as well)
+    if (count_one(ctr, lane) != n_splits - 1) return;
+    if (lane == 0) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    lane_test_done();
+    auto load8 = [](const float *p) __attribute__((always_inline)) {
+        return __builtin_bit_cast(u32x2, __hip_atomic_load((const uint64_t *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    };
+    // Weights: lane = (row, split), eight rows at a time; kept in LDS with the reciprocal of each row's sum.
+    POD_LDS float *const wts = (POD_LDS float *)lds, *const invs = wts + kMaxGroup * kMergeSplits;
+    static_assert(kMergeSplits == 8 && kMaxGroup * (kMergeSplits + 1) * 4 <= DecodeLds<D>::kBytesPerWave, "weights of a group");
+    for (int r0 = 0; r0 < group; r0 += kWaveSize / kMergeSplits) {
+        const int row = r0 + (lane >> 3), s = lane & 7;
+        float m = neg_inf(), l = 0.f;
+        if (row < group && s < n_splits) {
+            const u32x2 ml = load8(a.part_ml + ((int64_t)first + s * group + row) * 2);
+            m = __uint_as_float(ml[0]);
+            l = __uint_as_float(ml[1]);
+        }
+        lane_test_done();
+        float M = m;
+#pragma unroll
+        for (int x = 1; x < 8; x *= 2) M = fmaxf(M, __shfl_xor(M, x));
+        const float wt = fast_exp2(m - (M == neg_inf() ? 0.f : M));      // as in the combine kernel
+        float sum = l * wt;
+#pragma unroll
+        for (int x = 1; x < 8; x *= 2) sum += __shfl_xor(sum, x);
+        if (row < group) {
+            wts[row * kMergeSplits + s] = wt;
+            if (s == 0) invs[row] = 1.f / sum;
+        }
+        lane_test_done();
+    }
+    wave_lds_sync();
+    // Two channels a lane, kBatch times 64 lanes of them fetched together.
+    constexpr int kPairs = D / 2, kBatch = 2;
+    const int n_pairs = group * kPairs;
+    typename N::elem *const out = (typename N::elem *)a.out + ((int64_t)(a.n_prefill_rows + q_start) * a.n_q_heads + kv_head * group) * D;
+    for (int e0 = 0; e0 < n_pairs; e0 += kBatch * kWaveSize) {
+        u32x2 v[kBatch][kMergeSplits];
+#pragma unroll
+        for (int b = 0; b < kBatch; ++b)
+#pragma unroll
+            for (int s = 0; s < kMergeSplits; ++s) {
+                const int e = min(e0 + b * kWaveSize + lane, n_pairs - 1);
+                v[b][s] = load8(a.part_o + ((int64_t)first + min(s, n_splits - 1) * group) * D + 2 * e);
+            }
+#pragma unroll
+        for (int b = 0; b < kBatch; ++b) {
+            const int e = e0 + b * kWaveSize + lane, row = min(e, n_pairs - 1) / kPairs;
+            float x = 0.f, y = 0.f;
+#pragma unroll
+            for (int s = 0; s < kMergeSplits; ++s) {
+                const float wt = wts[row * kMergeSplits + s];
+                x += __uint_as_float(v[b][s][0]) * wt;
+                y += __uint_as_float(v[b][s][1]) * wt;
+            }
+            const float inv = invs[row];
+            typedef typename N::elem e2 __attribute__((ext_vector_type(2)));
+            if (e < n_pairs) *(e2 *)(out + 2 * e) = e2{(typename N::elem)(x * inv), (typename N::elem)(y * inv)};
+            lane_test_done();
+        }
+    }
 }
 
 // A decode worker.  Worker number `seat` (seats are handed out once per workgroup) starts with the
@@ -1231,6 +1318,7 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
             }
         }
     }
+    if (a.arrived) merge_if_last<DT, D>(a, lds_k, cu.id, lane);      // (the wavefront had one unit)
     return n_done;
 }
 

@@ -383,10 +383,10 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
             // Above half of the units (176 items, 8 x 1000: 25.9 / 26.2; 256 channels, 8 x 4000: 62 / 102) the workers need them all.
             const int64_t waves = few_items && longest_item > share ? (int64_t)kWavesPerWg * (n_cus - n_items) : n_waves;
             const int64_t own_share = (token_heads + waves - 1) / waves;
-            // Cutting costs a merge pass, which takes as long as about a hundred more keys in the unit (twenty at 256
-            // channels).  It is not worth it when the requests are short: us whole / cut at 160 keys 10.2 / 10.9, at
-            // 176 11.4 / 10.8, at 250 14.6 / 10.8 (64 channels 8.3 / 11.5, 8.4 / 11.5, 10.3 / 11.4; 256 channels at
-            // 100 keys 17.0 / 14.6, at 250 34 / 15).  Nor when the prefill items beside them take longer than the
+            // Cutting costs a merge, in the units or in a kernel of its own.  With the latter it is not worth it when the
+            // requests are short: us whole / cut at 160 keys 10.2 / 10.9, at 176 11.4 / 10.8, at 250 14.6 / 10.8 (64
+            // channels 8.3 / 11.5, 8.4 / 11.5, 10.3 / 11.4; 256 channels at 100 keys 17.0 / 14.6, at 250 34 / 15).
+            // (Merging in the units, which came later, 112 keys would be the line: at 128 8.8 / 8.4, at 160 10.2 / 8.4.)  Nor when the prefill items beside them take longer than the
             // whole requests anyway (64 keys of an item take about 1.1 us, 16 of a unit 0.7, at 256 channels 2)
             // and need no merge themselves: items of 1128 keys beside 16 x 500 27.8 / 33.5, x 700 36 / 34;
             // of 2028 beside 16 x 700 44.6 / 50.7, 2 x 1000 50.1 / 48.1; of 128 beside 16 x 200 14.0 / 12.2; 256
@@ -414,6 +414,16 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
                     else lo = mid + 1;
                 }
                 chunk = shortest + lo * kDecodeStep;
+                // Up to kMergeSplits splits the units merge by themselves, which is worth a unit that is 2 us longer, or
+                // any that the items beside it outlast by far: cut to merge in a kernel of its own / in the units, items of
+                // 2028 keys beside 2 x 1000 47.4 / 44.2, of 256 channels 70.4 / 67.3, 1128 beside 16 x 700 with 4 K/V
+                // heads 31.0 / 27.7.
+                const int piece = round_up(ceil_div(longest_decode, kMergeSplits), kDecodeStep);
+                const int64_t workers = (units_of_length(prm, seq_meta, piece) + kWavesPerWg - 1) / kWavesPerWg;
+                if (piece > chunk && plan.centries.empty() &&
+                    (piece <= chunk + (prm.head_dim > 128 ? 16 : 48) ||
+                     (longest_item > 0 && piece <= beside_items / 2 && n_items + workers <= (int64_t)kSlotsPerUnit * n_cus)))
+                    chunk = piece;
             }
         } else {
             // Enough work for every wavefront: pieces of at most one wavefront's share, and the second
@@ -470,6 +480,7 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
             }
         }
         plan.decode_chunk = chunk;
+        plan.decode_prow0 = next_prow;
         const Cut how = given_chunk > 0 ? Cut::kGiven : one_round ? Cut::kEqual : Cut::kTaper;
         {
             size_t n_est = 0;
@@ -524,6 +535,12 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
         // 656 us on a 4.3 GB batch; the eight wavefronts of a unit and the XCDs among each other
         // then get very unequal shares, and the slowest wavefronts decide when the launch ends).
         plan.n_dwgs = std::min(n_cus, ceil_div((int)plan.dunits.size(), kWavesPerWg));
+        // With one unit a wavefront the unit that finishes a group last merges it, and no kernel follows for the decode
+        // rows.  (With more units every one of them would wait for its stores in the middle of the stream; with
+        // more splits a single wavefront takes longer than the combine kernel.)
+        plan.units_merge = plan.max_dsplits >= 2 && plan.max_dsplits <= kMergeSplits &&
+                           (int64_t)plan.dunits.size() <= (int64_t)kWavesPerWg * n_cus &&
+                           next_prow - plan.decode_prow0 <= (int64_t)(sizeof(WsHeader::arrived) / sizeof(uint32_t));
         // The first workers to take a decode seat (one per compute unit) start with four fixed
         // units each, the longest ones, and claim nothing for them.  The other units are dealt
         // round-robin, still longest first, to one queue per XCD: a wavefront claims from the
@@ -540,6 +557,15 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
         }
         plan.dq_begin[kXcdQueues] = n_units;
         std::copy(dealt.begin(), dealt.end(), plan.dunits.begin() + n_fixed);
+        if (plan.units_merge) {
+            std::vector<uint8_t> n_splits((size_t)(next_prow - plan.decode_prow0), 0);     // by the group's first partial row
+            for (int pass = 0; pass < 2; ++pass)
+                for (const DecodeUnit &u : plan.dunits) {
+                    uint8_t none = 0, &n = u.prow0 < 0 ? none : n_splits[(size_t)(u.prow0 - u.split * group - plan.decode_prow0)];
+                    if (pass == 0) ++n;
+                    else plan.unit_splits.push_back(n);
+                }
+        }
     }
     if (next_prow > (int64_t)1 << 30) { err = "too many partial rows"; return POD_ERR_INVALID_ARG; }
     plan.n_partial_rows = next_prow;

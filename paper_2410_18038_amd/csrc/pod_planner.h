@@ -31,6 +31,11 @@ struct Plan {
     int n_crows_prefill = 0;                // rows of merge_rows that are prefill rows
     int64_t n_prefill_rows = 0;
     int64_t n_partial_rows = 0;
+    int64_t decode_prow0 = 0;               // first partial row of a decode unit
+    // Whether the last unit of each decode group merges it (unless the combine kernel has to), and then the number of
+    // splits of each unit's group, in the order of `dunits`.
+    bool units_merge = false;
+    std::vector<uint8_t> unit_splits;
     int p_ratio = 1, d_ratio = 1;
     int decode_chunk = 0;
     int max_psplits = 1, max_dsplits = 1;

@@ -785,3 +785,37 @@ def test_fused_calls_that_take_the_prefill_heavy_configuration_keep_stream_order
         assert torch.equal(out.view(torch.int16), want.view(torch.int16))
         assert (attn.forward(batch).float() - eager.float()).abs().max().item() == 0
     attn.close()
+
+
+@pytest.mark.parametrize("hq,hkv,d,dtype,bs", [(4, 4, 64, wl.F16, 0), (8, 4, 128, wl.BF16, 16), (16, 2, 128, wl.F16, 24),
+                                               (32, 2, 64, wl.BF16, 16), (16, 2, 256, wl.BF16, 16), (3, 1, 128, wl.F16, 5)])
+def test_units_of_one_round_merge_their_groups_themselves(hq, hkv, d, dtype, bs):
+    """Plans of one round with two to eight splits per request: whichever unit of a group ends last merges it, in every
+    mode and launch after launch with the same bits; the group counters at the head of the workspace are zero after
+    each call; merging switched off leaves the decode rows of split requests alone."""
+    for lens, chunk, chunk_rows in [([200, 64, 510, 129, 16], 64, 0), ([700] * 3 + [65], 96, 70)]:
+        batch = wl.make_batch(f"merge-{hq}/{hkv}-d{d}", prefill=[(chunk_rows, 200)] if chunk_rows else [], decode_kv_lens=lens,
+                              n_q_heads=hq, n_kv_heads=hkv, head_dim=d, dtype=dtype, seed=77 + d + hq, block_size=bs, poison=float("nan"))
+        dev_batch = batch.to("cuda:0")
+        attn = pod.HybridAttention(dev_batch, decode_chunk=chunk)
+        assert 2 <= attn.info.max_decode_splits <= 8 and attn.info.n_decode_units <= 4 * attn.info.n_compute_units
+        want = oracle_out(batch)
+        first = attn.ws_ptr - attn.workspace.data_ptr()
+        bits = None
+        for i in range(24):
+            mode = ["fused", "serial", "streams", "fused_cta"][i % 4]
+            out = attn.forward(dev_batch, out=torch.full((batch.n_rows, hq, d), float("nan"), dtype=batch.torch_dtype, device="cuda:0"),
+                               mode=pod.MODES[mode])
+            torch.cuda.synchronize()
+            if bits is None:
+                bits = out.view(torch.int16).clone()
+                assert np.abs(out.to(torch.float64).cpu().numpy() - want).max() <= TOL[dtype]
+            assert torch.equal(out.view(torch.int16), bits), (mode, i)
+            assert not attn.workspace[first:first + 70912].any()
+        out.fill_(float("nan"))
+        attn.forward(dev_batch, out=out, mode=pod.MODE_FUSED | pod.MODE_FLAG_NO_COMBINE)
+        rows = [batch.n_prefill_rows + i for i, n in enumerate(lens) if n > chunk]
+        assert torch.isnan(out[rows].float()).all()
+        attn.forward(dev_batch, out=out)
+        assert torch.equal(out.view(torch.int16), bits)
+        attn.close()
