@@ -864,35 +864,40 @@ __device__ __forceinline__ void merge_if_last(const KernelArgs &a, POD_LDS unsig
         lane_test_done();
     }
     wave_lds_sync();
-    // Two channels a lane, kBatch times 64 lanes of them fetched together.
-    constexpr int kPairs = D / 2, kBatch = 2;
+    // Two channels a lane, and 2 or 8 times 64 lanes of them fetched together (8 heads of 128 channels in one go).
+    constexpr int kPairs = D / 2;
     const int n_pairs = group * kPairs;
     typename N::elem *const out = (typename N::elem *)a.out + ((int64_t)(a.n_prefill_rows + q_start) * a.n_q_heads + kv_head * group) * D;
-    for (int e0 = 0; e0 < n_pairs; e0 += kBatch * kWaveSize) {
-        u32x2 v[kBatch][kMergeSplits];
+    auto merge = [&](auto batch) __attribute__((always_inline)) {
+        constexpr int kBatch = decltype(batch)::value;
+        for (int e0 = 0; e0 < n_pairs; e0 += kBatch * kWaveSize) {
+            u32x2 v[kBatch][kMergeSplits];
 #pragma unroll
-        for (int b = 0; b < kBatch; ++b)
+            for (int b = 0; b < kBatch; ++b)
 #pragma unroll
-            for (int s = 0; s < kMergeSplits; ++s) {
-                const int e = min(e0 + b * kWaveSize + lane, n_pairs - 1);
-                v[b][s] = load8(a.part_o + ((int64_t)first + min(s, n_splits - 1) * group) * D + 2 * e);
+                for (int s = 0; s < kMergeSplits; ++s) {
+                    const int e = min(e0 + b * kWaveSize + lane, n_pairs - 1);
+                    v[b][s] = load8(a.part_o + ((int64_t)first + min(s, n_splits - 1) * group) * D + 2 * e);
+                }
+#pragma unroll
+            for (int b = 0; b < kBatch; ++b) {
+                const int e = e0 + b * kWaveSize + lane, row = min(e, n_pairs - 1) / kPairs;
+                float x = 0.f, y = 0.f;
+#pragma unroll
+                for (int s = 0; s < kMergeSplits; ++s) {
+                    const float wt = wts[row * kMergeSplits + s];
+                    x += __uint_as_float(v[b][s][0]) * wt;
+                    y += __uint_as_float(v[b][s][1]) * wt;
+                }
+                const float inv = invs[row];
+                typedef typename N::elem e2 __attribute__((ext_vector_type(2)));
+                if (e < n_pairs) *(e2 *)(out + 2 * e) = e2{(typename N::elem)(x * inv), (typename N::elem)(y * inv)};
+                lane_test_done();
             }
-#pragma unroll
-        for (int b = 0; b < kBatch; ++b) {
-            const int e = e0 + b * kWaveSize + lane, row = min(e, n_pairs - 1) / kPairs;
-            float x = 0.f, y = 0.f;
-#pragma unroll
-            for (int s = 0; s < kMergeSplits; ++s) {
-                const float wt = wts[row * kMergeSplits + s];
-                x += __uint_as_float(v[b][s][0]) * wt;
-                y += __uint_as_float(v[b][s][1]) * wt;
-            }
-            const float inv = invs[row];
-            typedef typename N::elem e2 __attribute__((ext_vector_type(2)));
-            if (e < n_pairs) *(e2 *)(out + 2 * e) = e2{(typename N::elem)(x * inv), (typename N::elem)(y * inv)};
-            lane_test_done();
         }
-    }
+    };
+    if (n_pairs <= 2 * kWaveSize) merge(std::integral_constant<int, 2>{});
+    else merge(std::integral_constant<int, 8>{});
 }
 
 // A decode worker.  Worker number `seat` (seats are handed out once per workgroup) starts with the

@@ -414,15 +414,14 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
                     else lo = mid + 1;
                 }
                 chunk = shortest + lo * kDecodeStep;
-                // Up to kMergeSplits splits the units merge by themselves, which is worth a unit that is 2 us longer, or
-                // any that the items beside it outlast by far: cut to merge in a kernel of its own / in the units, items of
-                // 2028 keys beside 2 x 1000 47.4 / 44.2, of 256 channels 70.4 / 67.3, 1128 beside 16 x 700 with 4 K/V
-                // heads 31.0 / 27.7.
+                // Up to kMergeSplits splits the units merge by themselves, which is worth any unit that the items beside it
+                // outlast by far: cut to merge in a kernel of its own / in the units, items of 2028 keys beside 2 x 1000
+                // 47.4 / 44.2, 1128 beside 16 x 700 with 4 K/V heads 31.0 / 27.7.  (Without items it is not: 3 x 677 in
+                // 11 splits of 64 keys 9.4, in 8 of 96 10.0.)
                 const int piece = round_up(ceil_div(longest_decode, kMergeSplits), kDecodeStep);
                 const int64_t workers = (units_of_length(prm, seq_meta, piece) + kWavesPerWg - 1) / kWavesPerWg;
-                if (piece > chunk && plan.centries.empty() &&
-                    (piece <= chunk + (prm.head_dim > 128 ? 16 : 48) ||
-                     (longest_item > 0 && piece <= beside_items / 2 && n_items + workers <= (int64_t)kSlotsPerUnit * n_cus)))
+                if (piece > chunk && plan.centries.empty() && longest_item > 0 && piece <= beside_items / 2 &&
+                    n_items + workers <= (int64_t)kSlotsPerUnit * n_cus)
                     chunk = piece;
             }
         } else {
@@ -537,8 +536,10 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
         plan.n_dwgs = std::min(n_cus, ceil_div((int)plan.dunits.size(), kWavesPerWg));
         // With one unit a wavefront the unit that finishes a group last merges it, and no kernel follows for the decode
         // rows.  (With more units every one of them would wait for its stores in the middle of the stream; with
-        // more splits a single wavefront takes longer than the combine kernel.)
-        plan.units_merge = plan.max_dsplits >= 2 && plan.max_dsplits <= kMergeSplits &&
+        // more splits or rows a single wavefront takes longer than the combine kernel.)  us per call, combine kernel /
+        // in the units: 8 requests of 400 keys, 32 / 8 heads 9.3 / 8.6, 8 query heads on one K/V head 9.3 / 9.0, 16 of them
+        // (64 channels) 9.8 / 10.7; 256 channels with two 14.7 / 14.6, with four 14.8 / 15.1.
+        plan.units_merge = group <= 8 && prm.head_dim <= 128 && plan.max_dsplits >= 2 && plan.max_dsplits <= kMergeSplits &&
                            (int64_t)plan.dunits.size() <= (int64_t)kWavesPerWg * n_cus &&
                            next_prow - plan.decode_prow0 <= (int64_t)(sizeof(WsHeader::arrived) / sizeof(uint32_t));
         // The first workers to take a decode seat (one per compute unit) start with four fixed
