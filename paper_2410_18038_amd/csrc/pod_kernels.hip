@@ -979,6 +979,8 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
     // anywhere.  The queues of a launch run out within a few microseconds of each other, and seven round trips
     // are 5 us that every wavefront would spend at the very end.  So whoever has come round to the queue of its
     // XCD, where it started, says so in that queue's counter: the others of the XCD see it with the claim that fails.
+    // It waits until that has arrived: in a call without a combine kernel the counters are cleared as soon as every
+    // workgroup has counted itself in, and the barrier ahead of that does not wait for a wavefront's memory operations.
     // Decode alone, us before / after, with the walk moved behind the unit's last step: 16 requests 118.0 / 115.9, 48 of
     // 64 channels 78.0 / 74.7, 128 requests 773 / 770.  (A look at all eight counters with one load each took
     // longer than the walk: 622 / 643 with 8192 units, 77 / 82 with 64 channels; it slows the claims on them.)
@@ -990,7 +992,7 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
             if (cq == home) {
                 if (lane == 0) {
                     uint32_t *ctr = &a.hdr->next_dunit_xcd[home][0];
-                    asm volatile("global_atomic_or %0, %1, off" ::"v"(ctr), "v"(kAllQueuesEmpty) : "memory");
+                    asm volatile("global_atomic_or %0, %1, off\n\ts_waitcnt vmcnt(0)" ::"v"(ctr), "v"(kAllQueuesEmpty) : "memory");
                 }
                 lane_test_done();
                 st |= kExhausted;
@@ -1421,7 +1423,8 @@ __device__ __forceinline__ void finish_and_reset(const KernelArgs &a, int *flag)
     if (a.combine_resets) return;
     __syncthreads();
     if (threadIdx.x == 0) {
-        // (every claim of this workgroup has returned: their values have been used)
+        // (nothing of this workgroup is on its way to the counters any more: every claim has returned a value that
+        // was used, and whoever marks a queue waits for it)
         const uint32_t done = atomicAdd(&hdr->done[0][0], 1u);
         *flag = (done == gridDim.x - 1) ? 1 : 0;
     }

@@ -1,4 +1,4 @@
-"""What the compiler made of the attention kernels, read from the code-object metadata of the built library.
+"""What the compiler made of the attention kernels, read from the code objects of the built library.
 
 The decode worker counts the loads it has in flight and the prefill loop has no room to wait for reloads, so
 spilled registers cost more than the values they hold: no kernel may have any scratch memory, except the two of the
@@ -15,6 +15,7 @@ import pytest
 from paper_2410_18038_amd import pod
 
 READELF = shutil.which("llvm-readelf") or "/opt/rocm/llvm/bin/llvm-readelf"
+OBJDUMP = shutil.which("llvm-objdump") or "/opt/rocm/llvm/bin/llvm-objdump"
 MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
 
 
@@ -48,3 +49,24 @@ def test_attention_kernels_have_no_scratch_memory(tmp_path):
     # 2 types x 3 head_dims x (4 kernels x 4 layouts + combine)
     assert len(attention) == 2 * 3 * (4 * 4 + 1)
     assert {k: v for k, v in attention.items() if v} == {}
+
+
+@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no llvm-objdump")
+def test_counter_updates_without_a_result_are_waited_for(tmp_path):
+    """The last workgroup of an attention kernel clears the counters after all have counted themselves in.  An atomic
+    that returns its old value has arrived once that is used; one that returns nothing (the mark of an XCD whose
+    queues are used up) has to be waited for on the spot, or it may land after the clearing and stay into the next call."""
+    with open(pod.LIB_PATH, "rb") as f:
+        blob = f.read()
+    n_marks = 0
+    for i, obj in enumerate(code_objects(blob)):
+        path = tmp_path / f"{i}.elf"
+        path.write_bytes(obj)
+        text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", str(path)], capture_output=True, text=True, check=True).stdout
+        lines = [line.split("//")[0].split() for line in text.splitlines() if line.startswith("\t")]
+        for at, words in enumerate(lines):
+            if words[0].startswith("global_atomic") and "sc0" not in words:      # sc0: returns the old value
+                n_marks += 1
+                assert lines[at + 1][:2] == ["s_waitcnt", "vmcnt(0)"], " ".join(words + ["|"] + lines[at + 1])
+    # 2 types x 3 head_dims x 3 kernels (decode, fused, fused_cta) x 4 layouts, as often as the compiler copies the walk
+    assert n_marks >= 2 * 3 * 3 * 4
