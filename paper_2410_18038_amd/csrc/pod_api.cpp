@@ -386,12 +386,9 @@ static pod_status forward_impl(const void *prefill_q, const void *decode_q, cons
     if (p.prm.n_prefill > 0 && !prefill_q) return fail(POD_ERR_INVALID_ARG, "prefill_q is null");
     if (p.prm.n_decode > 0 && !decode_q) return fail(POD_ERR_INVALID_ARG, "decode_q is null");
     if (paged && !block_table) return fail(POD_ERR_INVALID_ARG, "block_table is null for a paged cache");
-    if (heavy) {
-        const bool block_wise = !paged || ((p.prm.block_size & (p.prm.block_size - 1)) == 0 && p.prm.block_size >= 16);
-        if (p.prm.head_dim != 128 || !block_wise)
-            return fail(POD_ERR_UNSUPPORTED, "the prefill-heavy configuration is built for head_dim 128 and contiguous or "
-                                             "power-of-two (>= 16) block caches");
-    }
+    if (heavy && !pod::built_for_prefill_heavy(p.prm.block_size, p.prm.head_dim, p.prm.n_kv_heads))
+        return fail(POD_ERR_UNSUPPORTED, "the prefill-heavy configuration is built for head_dim 128 and contiguous or "
+                                         "power-of-two (>= 16) block caches, with blocks of less than 4 GB");
     if (use_static) {
         if (mode == POD_MODE_STREAMS || (heavy && mode == POD_MODE_FUSED))
             return fail(POD_ERR_UNSUPPORTED, "the two-stream mode creates streams and events; it is not available "

@@ -49,6 +49,12 @@ inline Layout cache_layout(int block_size, int head_dim, int n_kv_heads)
     if (block_size >= 16 && (block_size & (block_size - 1)) == 0 && small) return kLayoutPaged16;
     return block_size % (kWaveSize / (head_dim / 8)) == 0 ? kLayoutPagedRows : kLayoutPagedAny;
 }
+// What the two kernels of the prefill-heavy configuration are built for.
+inline bool built_for_prefill_heavy(int block_size, int head_dim, int n_kv_heads)
+{
+    const Layout layout = cache_layout(block_size, head_dim, n_kv_heads);
+    return head_dim == 128 && (layout == kLayoutContiguous || layout == kLayoutPaged16);
+}
 
 // One prefill work item: a block of packed query rows of one K/V head over a key range.
 // Packed row R of a request stands for token R / group, query head kv_head * group + R % group,

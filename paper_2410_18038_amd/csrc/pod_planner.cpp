@@ -646,8 +646,8 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
         }
         const double flop_time = 4.0 * prm.head_dim * pairs * prm.n_q_heads / 2.5e15;
         const double byte_time = kv_tokens * prm.n_kv_heads * prm.head_dim * 4.0 / 8.0e12;
-        const bool block_wise = prm.block_size == 0 || (prm.block_size >= 16 && (prm.block_size & (prm.block_size - 1)) == 0);
-        plan.heavy_advised = prm.head_dim == 128 && block_wise && prm.n_prefill > 0 && prm.n_decode > 0 &&
+        const bool built = built_for_prefill_heavy(prm.block_size, prm.head_dim, prm.n_kv_heads);
+        plan.heavy_advised = built && prm.n_prefill > 0 && prm.n_decode > 0 &&
                              flop_time > 1.2 * byte_time;
         // The automatic policy takes that configuration where it was ahead by more than its two streams and three
         // events cost (20 us a call): an item for every slot, so that decode workers of the fused launch hold up items,
@@ -661,7 +661,7 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
         double decode_tokens = 0.0;
         for (int r = prm.n_prefill; r < n_req; ++r) decode_tokens += seq_meta[4 * r + 2];
         const double decode_time = decode_tokens * prm.n_kv_heads * prm.head_dim * 4.0 / 8.0e12;
-        plan.heavy_pays = prm.policy == POD_POLICY_AUTO && prm.head_dim == 128 && block_wise && prm.n_decode > 0 &&
+        plan.heavy_pays = prm.policy == POD_POLICY_AUTO && built && prm.n_decode > 0 &&
                           (int)plan.pitems.size() >= kSlotsPerUnit * n_cus && flop_time >= 200e-6 &&
                           flop_time >= 0.8 * decode_time && flop_time <= 3.3 * decode_time;
     }

@@ -737,3 +737,22 @@ def test_fused_calls_take_the_prefill_heavy_configuration_where_every_slot_has_a
         plan = pod.pod_attn_plan_create(prm, meta)
         assert plan.info().prefill_heavy_chosen == want, (change, tuning)
         plan.close()
+
+
+@pytest.mark.parametrize("block_size,hkv,built", [(0, 4, True), (16, 4, True), (1 << 21, 4, True), (1 << 22, 4, False),
+                                                  (1 << 20, 32, False), (8, 4, False), (48, 4, False)])
+def test_prefill_heavy_configuration_is_kept_from_caches_it_is_not_built_for(block_size, hkv, built):
+    """Blocks of 4 GB or more need 64-bit offsets inside a block, which the two kernels do not have: such a batch is neither
+    advised nor given that configuration, and asking for it is refused before anything is launched."""
+    prm, meta = meta_only("heavy-built", [(2048, 32768)], [32768] * 32, hq=32, hkv=hkv, block_size=block_size)
+    prm.max_blocks_per_seq = 8192 if block_size else 0
+    plan = pod.pod_attn_plan_create(prm, meta)
+    info = plan.info()
+    assert info.prefill_heavy_chosen == (built and hkv == 4)
+    if not built:
+        assert info.prefill_heavy_advised == 0
+        for mode in ("fused_heavy", "prefill_only_heavy", "decode_only_lite"):
+            with pytest.raises(pod.PodError) as refused:
+                pod.pod_attn_forward(4096, 4096, 4096, 4096, 4096, 4096, 4096, plan, 4096, 1 << 40, pod.MODES[mode])
+            assert refused.value.status == -2
+    plan.close()
