@@ -88,10 +88,9 @@ typedef enum {
  * contiguous caches or paged ones with power-of-two blocks of at least 16 tokens and less than 4 GB
  * (block_size * Hkv * d * 2 bytes); otherwise POD_ERR_UNSUPPORTED.
  * POD_MODE_FUSED takes it by itself under the automatic policy where it is
- * ahead (an item for every workgroup slot, 200 us or more of matrix time, 0.8 to 3.3 times the byte
- * time of the decode stream: 2048 tokens at 32K beside 32 decodes at 32K 1114 us against 1198), in calls
- * that are not recorded into a graph and write no trace or event log; it is 6-35 % slower on
- * decode-bound batches.
+ * ahead (a plan for the whole chip, an item for every workgroup slot, 200 us or more of matrix time, 0.8
+ * to 3.3 times the byte time of the decode stream: 2048 tokens at 32K beside 32 decodes at 32K 1114 us
+ * against 1198), in calls
  * that are not recorded into a graph and write no trace or event log; it is 6-35 % slower on
  * decode-bound batches.
  * Also accepted with POD_MODE_PREFILL_ONLY and POD_MODE_DECODE_ONLY, which then run that

@@ -29,6 +29,7 @@ constexpr int kMaxGroup256 = 8;            // query heads per K/V head at head_d
 constexpr int kMaxGroup = 16;              // query heads per K/V head a decode unit can hold
 constexpr int kXcdQueues = 8;               // work is queued per XCD (one L2 each); a queue's counter is claimed mostly from its own XCD
 constexpr int kSlotsPerUnit = 2;            // resident workgroups per compute unit (register and LDS budget)
+constexpr int kChipUnits = 256;            // compute units of the chip (measured rules that hold for all of it)
 constexpr int kCombineFetch = 8;            // splits a thread group of the combine kernel fetches together (independent loads)
 constexpr int kCuSlots = 1024;             // hardware unit ids are sparse: (xcc << 6 | se << 4 | cu) < 1024
 

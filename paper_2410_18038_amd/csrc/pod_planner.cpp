@@ -661,7 +661,9 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
         double decode_tokens = 0.0;
         for (int r = prm.n_prefill; r < n_req; ++r) decode_tokens += seq_meta[4 * r + 2];
         const double decode_time = decode_tokens * prm.n_kv_heads * prm.head_dim * 4.0 / 8.0e12;
-        plan.heavy_pays = prm.policy == POD_POLICY_AUTO && built && prm.n_decode > 0 &&
+        // (Rates and times are those of the whole chip.  A plan for fewer units keeps to the workgroups of its fused launch,
+        // where the prefill kernel has one per item.)
+        plan.heavy_pays = prm.policy == POD_POLICY_AUTO && built && prm.n_decode > 0 && n_cus == kChipUnits &&
                           (int)plan.pitems.size() >= kSlotsPerUnit * n_cus && flop_time >= 200e-6 &&
                           flop_time >= 0.8 * decode_time && flop_time <= 3.3 * decode_time;
     }

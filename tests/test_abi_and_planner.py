@@ -756,3 +756,15 @@ def test_prefill_heavy_configuration_is_kept_from_caches_it_is_not_built_for(blo
                 pod.pod_attn_forward(4096, 4096, 4096, 4096, 4096, 4096, 4096, plan, 4096, 1 << 40, pod.MODES[mode])
             assert refused.value.status == -2
     plan.close()
+
+
+@pytest.mark.parametrize("n_units,want", [(256, 1), (255, 0), (16, 0), (512, 0)])
+def test_plans_for_part_of_the_chip_keep_to_the_workgroups_of_their_fused_launch(n_units, want):
+    """The prefill-heavy configuration launches a workgroup per item: a caller that limits the compute units gets the
+    fused launch, with at most two workgroups per unit, also where the batch is one for that configuration."""
+    prm, meta = meta_only("limited", [(2048, 32768)], [32768] * 32, hq=32, hkv=4)
+    prm.n_compute_units = n_units
+    plan = pod.pod_attn_plan_create(prm, meta)
+    info = plan.info()
+    assert info.prefill_heavy_chosen == want and info.fused_grid <= 2 * n_units
+    plan.close()
