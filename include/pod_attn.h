@@ -83,16 +83,18 @@ typedef enum {
  * started together on the library's two side streams: the prefill kernel held to 208 registers
  * and a light decode kernel of 96 registers and 16 KB of LDS, so that every compute unit holds two
  * prefill workgroups AND one decode workgroup for the whole launch (what places them together is
- * that nothing else fits; the trace records show where each workgroup ran).  Same result within
- * rounding (the decode kernel adds its weights in another order).  Built for head_dim 128 and for
+ * that nothing else fits; the trace records show where each workgroup ran).  Items and units give the
+ * same bits; split rows are merged by the combine kernel, also where the units of the default configuration
+ * merge them themselves (plans of one round of units), which can change their rounding.  Built for head_dim 128 and for
  * contiguous caches or paged ones with power-of-two blocks of at least 16 tokens and less than 4 GB
  * (block_size * Hkv * d * 2 bytes); otherwise POD_ERR_UNSUPPORTED.
  * POD_MODE_FUSED takes it by itself under the automatic policy where it is
  * ahead (a plan for the whole chip, an item for every workgroup slot, 200 us or more of matrix time, 0.8
  * to 3.3 times the byte time of the decode stream: 2048 tokens at 32K beside 32 decodes at 32K 1114 us
- * against 1198), in calls
- * that are not recorded into a graph and write no trace or event log; it is 6-35 % slower on
- * decode-bound batches.
+ * against 1198; the bits are those of the fused kernel), in calls that are not recorded into a graph, write
+ * no trace or event log, and are made on a stream of default priority without a compute-unit mask while the
+ * side streams hold no work of another stream's calls; otherwise the fused kernel runs.  It is 6-35 % slower
+ * on decode-bound batches.
  * Also accepted with POD_MODE_PREFILL_ONLY and POD_MODE_DECODE_ONLY, which then run that
  * configuration's prefill or decode kernel alone.  Like POD_MODE_STREAMS it creates streams and
  * events on first use, is not meant for graph capture, and is rejected by pod_attn_forward_static. */
@@ -253,6 +255,10 @@ pod_status pod_attn_plan_upload(const pod_attn_plan *plan, void *workspace, size
  * process ends, and three events per plan, destroyed with it, on first use and is not meant for capture.
  * For plans whose FUSED calls take the prefill-heavy configuration by themselves pod_attn_plan_upload
  * creates them; such a call forks from `stream` and joins it again, and behaves in stream order like any other.
+ * Calls that ask for two kernels share the side streams of their GPU, whichever stream they are made on, and so queue
+ * up behind each other.  A FUSED call that would have to runs the fused kernel on `stream` instead; calls on
+ * streams of their own stay independent of each other.  (A HIP process has four hardware queues, which all its
+ * streams share: a side stream that waits for its caller's earlier work holds up streams that share its queue.)
  * Two forward calls that use the same workspace must not overlap in time.
  */
 pod_status pod_attn_forward(const void *prefill_q, const void *decode_q,

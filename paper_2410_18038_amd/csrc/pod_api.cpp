@@ -125,60 +125,79 @@ pod::KernelArgs make_args(const pod::Plan &p, const void *prefill_q, const void 
     return a;
 }
 
-// The two streams the two-kernel modes run their kernels on: one pair per GPU, created at the
-// first such call on that GPU and kept until the process ends.  (A pair per plan would be spread
-// over the few hardware queues a process has in creation order, and a later plan's pair can land
-// on one queue, where its two kernels run one after the other.)
-pod_status side_streams(hipStream_t *s0, hipStream_t *s1)
+// The two streams the two-kernel modes run their kernels on: one pair per GPU, created when it is first
+// needed and kept until the process ends.  (A pair per plan would be spread over the few hardware queues a process
+// has in creation order, and a later plan's pair can land on one queue, where its two kernels run one after the other.
+// A second pair for the calls that take two kernels by themselves did: 1350 us instead of 1130.)
+// Calls that ask for two streams share the pair, whoever makes them.  A fused call must not wait for what another
+// stream does, so it takes two kernels by itself only while the pair holds no work of another caller's stream.
+struct SideStreams {
+    std::mutex enqueue;                     // held while a call enqueues: a wait refers to what its event was last recorded for
+    hipStream_t st[2] = {};
+    hipStream_t caller = nullptr;           // stream of the last call that enqueued here
+};
+SideStreams g_side[kMaxDevices];
+std::mutex g_side_mu;                       // creation of streams, and the events of plans
+
+// Creates what a two-kernel call of plan p needs on the current device.
+pod_status ensure_side(pod::Plan &p, int *device)
 {
-    static std::mutex mu;
-    static hipStream_t pair[kMaxDevices][2] = {};
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
+    hipError_t e = hipGetDevice(device);
     if (e != hipSuccess) return fail_hip(e, "asking for the current device");
-    if (dev < 0 || dev >= kMaxDevices) return fail(POD_ERR_UNSUPPORTED, "device index beyond what the library tracks");
-    std::lock_guard<std::mutex> lock(mu);
-    for (hipStream_t &st : pair[dev])
+    if (*device < 0 || *device >= kMaxDevices) return fail(POD_ERR_UNSUPPORTED, "device index beyond what the library tracks");
+    std::lock_guard<std::mutex> lock(g_side_mu);
+    for (hipStream_t &st : g_side[*device].st)
         if (!st) {
             e = hipStreamCreateWithFlags(&st, hipStreamNonBlocking);
             if (e != hipSuccess) { st = nullptr; return fail_hip(e, "creating side stream"); }
         }
-    *s0 = pair[dev][0];
-    *s1 = pair[dev][1];
-    return POD_OK;
-}
-
-// Held while a call of a two-kernel mode enqueues: a wait refers to what its event was last recorded for, and
-// the streams, and the events of a plan, are shared by all host threads.
-std::mutex g_two_streams_mu;
-
-// The events of a plan, on the current device (under the lock above).
-pod_status ensure_events(pod::Plan &p)
-{
     for (void *&ev : p.events)
         if (!ev) {
             hipEvent_t ne;
-            const hipError_t e = hipEventCreateWithFlags(&ne, hipEventDisableTiming);
+            e = hipEventCreateWithFlags(&ne, hipEventDisableTiming);
             if (e != hipSuccess) return fail_hip(e, "creating event");
             ev = ne;
-            if (hipGetDevice(&p.events_device) != hipSuccess) p.events_device = -1;
+            p.events_device = *device;
         }
     return POD_OK;
 }
 
-// May this fused call take the prefill-heavy configuration?  Not where a launch is being recorded (graph
-// capture), where the records of the fused kernel are asked for, or where streams or events would have to be
-// created first.
-bool heavy_is_ready(const pod::Plan &p, hipStream_t s)
+// May this fused call take the prefill-heavy configuration?  Then the lock that lets it enqueue on the pair is in
+// `hold`.  Not where the records of the fused kernel are asked for, where streams or events would have to be
+// created first, where a launch is being recorded (graph capture), or where the work would run otherwise on the side
+// streams than on s: with a compute-unit mask or a priority of its own, or behind another stream's work.
+bool heavy_is_ready(const pod::Plan &p, hipStream_t s, std::unique_lock<std::mutex> &hold)
 {
-    if (!p.heavy_pays || p.trace || p.evlog || !p.events[2]) return false;
-    int dev = -1;
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusActive;
-    if (hipGetDevice(&dev) != hipSuccess || dev != p.events_device || hipStreamIsCapturing(s, &capture) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    return capture == hipStreamCaptureStatusNone;
+    if (!p.heavy_pays || p.trace || p.evlog || s == hipStreamPerThread) return false;   // (that handle names many streams)
+    auto usable = [&]() -> bool {
+        int dev = -1, priority = 0, units = 0;
+        uint32_t mask[pod::kChipUnits / 32] = {};
+        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return false;
+        {
+            std::lock_guard<std::mutex> lock(g_side_mu);
+            if (!p.events[2] || p.events_device != dev) return false;
+        }
+        auto recorded = [](hipStream_t x) {
+            hipStreamCaptureStatus status = hipStreamCaptureStatusActive;
+            return hipStreamIsCapturing(x, &status) != hipSuccess || status != hipStreamCaptureStatusNone;
+        };
+        if (recorded(s) || hipStreamGetPriority(s, &priority) != hipSuccess || priority != 0 ||
+            hipExtStreamGetCUMask(s, pod::kChipUnits / 32, mask) != hipSuccess)
+            return false;
+        for (uint32_t word : mask) units += __builtin_popcount(word);
+        if (units != pod::kChipUnits) return false;
+        SideStreams &side = g_side[dev];
+        hold = std::unique_lock<std::mutex>(side.enqueue);
+        if (side.caller != s)
+            for (hipStream_t st : side.st)
+                if (recorded(st) || hipStreamQuery(st) != hipSuccess) return false;
+        side.caller = s;
+        return true;
+    };
+    if (usable()) return true;
+    (void)hipGetLastError();
+    if (hold.owns_lock()) hold.unlock();
+    return false;
 }
 
 // Clear the counters at the head of `workspace` (with a kernel, not a memset) and copy the plan's
@@ -352,13 +371,10 @@ pod_status pod_attn_plan_upload(const pod_attn_plan *plan, void *workspace, size
     if (!workspace || workspace_bytes < p.ws_bytes) return fail(POD_ERR_WORKSPACE, "workspace missing or too small");
     if (((uintptr_t)workspace & 255u) != 0) return fail(POD_ERR_WORKSPACE, "workspace must be 256-byte aligned");
     const pod_status st = upload_tables(p, workspace, (hipStream_t)stream);
-    if (st == POD_OK && p.heavy_pays) {
-        // What a fused call of this plan needs to take the prefill-heavy configuration is made here, so that the
-        // call itself creates nothing.  Without it the fused kernel runs.
-        std::lock_guard<std::mutex> lock(g_two_streams_mu);
-        hipStream_t s0 = nullptr, s1 = nullptr;
-        if (side_streams(&s0, &s1) != POD_OK || ensure_events(const_cast<pod_attn_plan *>(plan)->p) != POD_OK) (void)hipGetLastError();
-    }
+    // What a fused call of this plan needs to take the prefill-heavy configuration is made here, so that the call itself
+    // creates nothing.  Without it the fused kernel runs.
+    int dev = -1;
+    if (st == POD_OK && p.heavy_pays && ensure_side(const_cast<pod_attn_plan *>(plan)->p, &dev) != POD_OK) (void)hipGetLastError();
     return st;
 }
 
@@ -444,7 +460,8 @@ static pod_status forward_impl(const void *prefill_q, const void *decode_q, cons
 
     // Where the decode units merge their groups the combine kernel is left with the prefill rows.  (The light decode
     // kernel does not merge.)
-    const bool two_kernels = heavy || (mode == POD_MODE_FUSED && !cta_parallel && !use_static && heavy_is_ready(p, s));
+    std::unique_lock<std::mutex> side_held;
+    const bool two_kernels = heavy || (mode == POD_MODE_FUSED && !cta_parallel && !use_static && heavy_is_ready(p, s, side_held));
     if (p.units_merge && !no_combine && !two_kernels) {
         a.arrived = a.hdr->arrived;
         a.n_crows = p.n_crows_prefill;
@@ -459,11 +476,15 @@ static pod_status forward_impl(const void *prefill_q, const void *decode_q, cons
     // Prefill kernel and decode kernel on the library's two side streams, forked from and joined
     // back into the caller's stream; the merge follows on the caller's stream.
     auto two_streams = [&](int prefill_kind, int decode_kind) -> pod_status {
-        hipStream_t s0 = nullptr, s1 = nullptr;
-        std::lock_guard<std::mutex> lock(g_two_streams_mu);
-        pod_status st = side_streams(&s0, &s1);
-        if (st == POD_OK) st = ensure_events(p);
+        int dev = -1;
+        const pod_status st = ensure_side(p, &dev);
         if (st != POD_OK) return st;
+        SideStreams &side = g_side[dev];
+        if (!side_held.owns_lock()) {
+            side_held = std::unique_lock<std::mutex>(side.enqueue);
+            side.caller = s;
+        }
+        const hipStream_t s0 = side.st[0], s1 = side.st[1];
         hipEvent_t fork = (hipEvent_t)p.events[0], j0 = (hipEvent_t)p.events[1], j1 = (hipEvent_t)p.events[2];
         auto chk = [&](hipError_t x) { if (e == hipSuccess) e = x; };
         chk(hipEventRecord(fork, s));

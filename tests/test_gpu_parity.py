@@ -819,3 +819,72 @@ def test_units_of_one_round_merge_their_groups_themselves(hq, hkv, d, dtype, bs)
         attn.forward(dev_batch, out=out)
         assert torch.equal(out.view(torch.int16), bits)
         attn.close()
+
+
+
+def _kernels_of(call):
+    """Names of the library's kernels that a call launches."""
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    return {name for e in prof.key_averages() for name in ("prefill_heavy_kernel", "decode_lite_kernel", "fused_kernel",
+                                                           "fused_cta_kernel", "combine_kernel") if "pod::" + name in e.key}
+
+
+def test_fused_calls_take_two_kernels_only_where_their_stream_has_the_side_streams_to_itself():
+    """Which kernels a fused call of a plan for the prefill-heavy configuration launches: that configuration's two on the
+    stream it is made on, whichever that is; the fused kernel while another stream's call holds the library's side
+    streams, on a stream with a compute-unit mask, with an event log attached and in a recorded call.  Same bits."""
+    import ctypes
+    batch = wl.config_batch(4, device="cuda:0")
+    attn, other = pod.HybridAttention(batch), pod.HybridAttention(batch)
+    assert attn.info.prefill_heavy_chosen == 1
+    two, one = {"prefill_heavy_kernel", "decode_lite_kernel", "combine_kernel"}, {"fused_kernel", "combine_kernel"}
+    want = attn.forward(batch, mode=pod.MODE_SERIAL)
+    outs = [torch.empty_like(want) for _ in range(2)]
+    torch.cuda.synchronize()
+
+    def fused(a, out, stream=None):
+        with torch.cuda.stream(stream or torch.cuda.current_stream()):
+            out.fill_(float("nan"))
+            a.forward(batch, out=out)
+
+    def same_bits(*got):
+        torch.cuda.synchronize()
+        return all(torch.equal(x.view(torch.int16), want.view(torch.int16)) for x in got)
+
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    for stream in (None, *streams):
+        assert _kernels_of(lambda: fused(attn, outs[0], stream)) == two and same_bits(outs[0])
+
+    # The first stream is held up, and so is the call behind that; the other stream's call does not queue up behind it.
+    def held_up():
+        with torch.cuda.stream(streams[0]):
+            torch.cuda._sleep(20_000_000)
+            fused(attn, outs[0], streams[0])
+            waiting = torch.cuda.Event()
+            waiting.record()
+        fused(other, outs[1], streams[1])
+        assert not waiting.query()
+    assert _kernels_of(held_up) == two | one and same_bits(*outs)
+    assert _kernels_of(lambda: fused(other, outs[1], streams[1])) == two and same_bits(outs[1])
+
+    hip = pod.lib()                                  # (its symbols include those of the HIP runtime it runs on)
+    masked, mask = ctypes.c_void_p(), (ctypes.c_uint32 * 8)(*[0x0000ffff] * 8)
+    assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(masked), 8, mask) == 0
+    stream = torch.cuda.ExternalStream(masked.value)
+    assert _kernels_of(lambda: fused(attn, outs[0], stream)) == one and same_bits(outs[0])
+    assert hip.hipStreamDestroy(masked) == 0
+
+    attn.enable_event_log()
+    assert _kernels_of(lambda: fused(attn, outs[0])) == one and same_bits(outs[0])
+    attn.disable_event_log()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        attn.forward(batch, out=outs[0])
+    outs[0].fill_(float("nan"))
+    assert _kernels_of(graph.replay) == one and same_bits(outs[0])
+    attn.close()
+    other.close()
