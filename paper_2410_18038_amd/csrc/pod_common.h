@@ -77,7 +77,9 @@ struct DecodeUnit {
                                            // splits << kSplitBits added
     int32_t q_start, cache_row;            // copied from the request: a unit starts with one lookup
 };
-constexpr int kMergeSplits = 8;            // up to this many splits the last unit of a group merges them itself
+constexpr int kMergeSplits = 8;            // the last unit of a group merges it itself up to this many splits,
+constexpr int kMergeRows = 8;              // query heads
+constexpr int kMergeDim = 128;             // and channels
 constexpr int kSplitBits = 24;
 
 // One group of output rows merged from split partials (host only; the kernel reads CombineRows).
@@ -111,8 +113,8 @@ struct WsHeader {
     // Next decode unit of each per-XCD queue (offset inside the queue), claimed by wavefronts.
     uint32_t next_dunit_xcd[kXcdQueues][32];
     // Units that have stored their partials, for the groups of a plan whose last units merge: the counter of a group
-    // is the word whose index is its first decode partial row (a plan of one round of wavefronts has up to
-    // 4 units a compute unit and 16 rows a unit).  The unit that merges clears it.
+    // is the word whose index is its first decode partial row (one round of the chip's wavefronts has up to 1024 units of
+    // kMergeRows rows, half of this).  The unit that merges clears it.
     uint32_t arrived[512 * 32];
 };
 

@@ -162,8 +162,9 @@ __device__ __forceinline__ void write_trace(const KernelArgs &a, int slot, int c
 // unit's results, so it issues those few stores this way.  A wait sized for the loads alone is
 // still safe with extra stores in flight: loads complete in order among themselves, so by the
 // time all but the newest N operations have completed, the oldest load is among the completed.
-// Nothing in these kernels reads the stored data back, and a kernel's end completes its stores.
-// The 16-byte form writes through to memory (sc1).  Left in L2, a result is evicted whenever the K/V stream
+// A kernel's end completes its stores; the only one that reads the data back before that, the merge of a decode group,
+// waits for its own and then for the others' count.  They write through to memory (sc1), where a merge on
+// another XCD finds them.  Left in L2, a result is evicted whenever the K/V stream
 // pushes it out, a line at a time, and each such write turns a memory channel around between reads:
 // 20280 units of 512 keys (41 MB of partial rows beside 5 GB of K/V) took 852 us, 782 with their stores left
 // out, and take 816 with whole rows written through at once; units of 2048 keys 797 -> 784.
@@ -838,11 +839,12 @@ __device__ __forceinline__ void merge_if_last(const KernelArgs &a, POD_LDS unsig
     auto load8 = [](const float *p) __attribute__((always_inline)) {
         return __builtin_bit_cast(u32x2, __hip_atomic_load((const uint64_t *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     };
-    // Weights: lane = (row, split), eight rows at a time; kept in LDS with the reciprocal of each row's sum.
-    POD_LDS float *const wts = (POD_LDS float *)lds, *const invs = wts + kMaxGroup * kMergeSplits;
-    static_assert(kMergeSplits == 8 && kMaxGroup * (kMergeSplits + 1) * 4 <= DecodeLds<D>::kBytesPerWave, "weights of a group");
-    for (int r0 = 0; r0 < group; r0 += kWaveSize / kMergeSplits) {
-        const int row = r0 + (lane >> 3), s = lane & 7;
+    // Weights: lane = (row, split); kept in LDS with the reciprocal of each row's sum.
+    POD_LDS float *const wts = (POD_LDS float *)lds, *const invs = wts + kMergeRows * kMergeSplits;
+    static_assert(kMergeSplits == 8 && kMergeRows * kMergeSplits == kWaveSize, "a lane for each row and split");
+    static_assert(kMergeRows * (kMergeSplits + 1) * 4 <= DecodeLds<D>::kBytesPerWave, "weights of a group");
+    {
+        const int row = lane >> 3, s = lane & 7;
         float m = neg_inf(), l = 0.f;
         if (row < group && s < n_splits) {
             const u32x2 ml = load8(a.part_ml + ((int64_t)first + s * group + row) * 2);
@@ -1325,7 +1327,8 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
             }
         }
     }
-    if (a.arrived) merge_if_last<DT, D>(a, lds_k, cu.id, lane);      // (the wavefront had one unit)
+    if constexpr (D <= kMergeDim)
+        if (a.arrived) merge_if_last<DT, D>(a, lds_k, cu.id, lane);      // (the wavefront had one unit)
     return n_done;
 }
 

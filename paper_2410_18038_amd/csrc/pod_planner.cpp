@@ -417,7 +417,9 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
                 // Up to kMergeSplits splits the units merge by themselves, which is worth any unit that the items beside it
                 // outlast by far: cut to merge in a kernel of its own / in the units, items of 2028 keys beside 2 x 1000
                 // 47.4 / 44.2, 1128 beside 16 x 700 with 4 K/V heads 31.0 / 27.7.  (Without items it is not: 3 x 677 in
-                // 11 splits of 64 keys 9.4, in 8 of 96 10.0.)
+                // 11 splits of 64 keys 9.4, in 8 of 96 10.0.)  Where they cannot merge, 256 channels or more than 8 query
+                // heads per K/V head, the combine kernel still has fewer splits to fetch: items of 2028 keys beside 4 x 1500
+                // 70.4 / 69.9 (16 / 8 heads of 256 channels), 1500 beside 2 x 1500 38.1 / 37.6 (9 / 1 heads of 128).
                 const int piece = round_up(ceil_div(longest_decode, kMergeSplits), kDecodeStep);
                 const int64_t workers = (units_of_length(prm, seq_meta, piece) + kWavesPerWg - 1) / kWavesPerWg;
                 if (piece > chunk && plan.centries.empty() && longest_item > 0 && piece <= beside_items / 2 &&
@@ -539,7 +541,7 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
         // more splits or rows a single wavefront takes longer than the combine kernel.)  us per call, combine kernel /
         // in the units: 8 requests of 400 keys, 32 / 8 heads 9.3 / 8.6, 8 query heads on one K/V head 9.3 / 9.0, 16 of them
         // (64 channels) 9.8 / 10.7; 256 channels with two 14.7 / 14.6, with four 14.8 / 15.1.
-        plan.units_merge = group <= 8 && prm.head_dim <= 128 && plan.max_dsplits >= 2 && plan.max_dsplits <= kMergeSplits &&
+        plan.units_merge = group <= kMergeRows && prm.head_dim <= kMergeDim && plan.max_dsplits >= 2 && plan.max_dsplits <= kMergeSplits &&
                            (int64_t)plan.dunits.size() <= (int64_t)kWavesPerWg * n_cus &&
                            next_prow - plan.decode_prow0 <= (int64_t)(sizeof(WsHeader::arrived) / sizeof(uint32_t));
         // The first workers to take a decode seat (one per compute unit) start with four fixed
