@@ -3,6 +3,8 @@
 Bar (max-abs over the whole batch, GPU 16-bit output widened to fp64): 2e-3 for fp16 inputs,
 1e-2 for bf16 inputs; fp32 accumulation on the GPU.  Every call goes through the C ABI.
 """
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -829,8 +831,9 @@ def _kernels_of(call):
     with profile(activities=[ProfilerActivity.CUDA]) as prof:
         call()
         torch.cuda.synchronize()
-    return {name for e in prof.key_averages() for name in ("prefill_heavy_kernel", "decode_lite_kernel", "fused_kernel",
-                                                           "fused_cta_kernel", "combine_kernel") if "pod::" + name in e.key}
+    names = ("prefill_kernel", "decode_kernel", "prefill_heavy_kernel", "decode_lite_kernel", "fused_kernel", "fused_cta_kernel",
+             "combine_kernel")
+    return {name for e in prof.key_averages() for name in names if "pod::" + name in e.key}
 
 
 def test_fused_calls_take_two_kernels_only_where_their_stream_has_the_side_streams_to_itself():
@@ -888,3 +891,49 @@ def test_fused_calls_take_two_kernels_only_where_their_stream_has_the_side_strea
     assert _kernels_of(graph.replay) == one and same_bits(outs[0])
     attn.close()
     other.close()
+
+
+@pytest.mark.parametrize("hq,hkv,d,bs,merges", [(4, 4, 64, 0, True), (16, 2, 64, 16, True), (8, 4, 128, 16, True), (16, 2, 128, 24, True),
+                                                (3, 1, 128, 5, True), (18, 2, 128, 16, False), (32, 2, 64, 16, False), (16, 2, 256, 16, False)])
+def test_units_merge_groups_with_nan_and_infinite_scores(hq, hkv, d, bs, merges):
+    """Which plans of one round merge their groups in the units (up to 8 query heads and 128 channels): those launch no
+    combine kernel.  Whole splits of NaN scores make the rows of their request NaN and no other; splits whose scores are
+    all -inf drop out, and +inf makes a row NaN, as in the oracle; the header at the start of the workspace (1024
+    tickets, 20 counters on lines of 128 bytes, 512 * 32 group counters) is zero again after each call."""
+    lens = [200, 64, 510, 129, 16, 257]
+    batch = wl.make_batch(f"merge-special-{hq}/{hkv}-d{d}", prefill=[], decode_kv_lens=lens, n_q_heads=hq, n_kv_heads=hkv,
+                          head_dim=d, dtype=wl.F16, seed=41 + d + hq, block_size=0)
+    row = [int(r) for r in batch.seq_meta[:, 3]]
+    batch.k_cache[row[0], 64:128] = float("nan")          # a split of four
+    batch.k_cache[row[2], 128:256, :, 3] = float("inf")   # two splits of eight: +inf or -inf by the sign of the query
+    batch.k_cache[row[3], :129] = float("nan")            # every split
+    batch.k_cache[row[5], 256, :, 3] = float("inf")       # the last split, of one key
+    want = oracle_out(batch)
+    infinite = np.isnan(want[[batch.seq_meta[2][0], batch.seq_meta[5][0]]]).all(axis=-1)
+    assert infinite.any() and not infinite.all()          # both signs
+    if bs:                                                # the same cache, in blocks
+        per_row, n_rows = -(-max(lens) // bs), len(lens)
+
+        def in_blocks(cache):
+            padded = torch.zeros((n_rows, per_row * bs, hkv, d), dtype=cache.dtype)
+            padded[:, :max(lens)] = cache[:, :max(lens)]
+            return padded.reshape(n_rows * per_row, bs, hkv, d)
+        batch = dataclasses.replace(batch, k_cache=in_blocks(batch.k_cache), v_cache=in_blocks(batch.v_cache), block_size=bs,
+                                    block_table=torch.arange(n_rows * per_row, dtype=torch.int32).reshape(n_rows, per_row),
+                                    max_blocks_per_seq=per_row, n_blocks=n_rows * per_row, n_cache_rows=n_rows, kv_seq_stride=0)
+        assert np.array_equal(oracle_out(batch), want, equal_nan=True)
+    dev_batch = batch.to("cuda:0")
+    attn = pod.HybridAttention(dev_batch, decode_chunk=64)
+    assert attn.info.max_decode_splits == 8 and attn.info.n_decode_units <= 4 * attn.info.n_compute_units
+    out = torch.empty((batch.n_rows, hq, d), dtype=batch.torch_dtype, device="cuda:0")
+    first = attn.ws_ptr - attn.workspace.data_ptr()
+    assert _kernels_of(lambda: attn.forward(dev_batch, out=out)) == {"decode_kernel"} | (set() if merges else {"combine_kernel"})
+    for mode in ("fused", "serial", "decode_only", "fused_cta") * 2:
+        out.zero_()
+        attn.forward(dev_batch, out=out, mode=pod.MODES[mode])
+        got = out.to(torch.float64).cpu().numpy()
+        assert (np.isnan(got) == np.isnan(want)).all(), mode
+        seen = ~np.isnan(want)
+        assert np.abs(got[seen] - want[seen]).max() <= TOL[batch.dtype], mode
+        assert not attn.workspace[first:first + 4 * 1024 + 20 * 128 + 4 * 512 * 32].any()
+    attn.close()
