@@ -230,6 +230,20 @@ KERNEL_OF_MODE = {"serial": "prefill_kernel + decode_kernel",
                   "fused_heavy": "prefill_heavy_kernel + decode_lite_kernel"}
 
 
+def kernels_of_fused(attn, pod):
+    """Names of the attention kernels that a fused call of this plan launches (the combine kernel aside)."""
+    info = attn.info
+    if info.prefill_heavy_chosen:
+        return KERNEL_OF_MODE["fused_heavy"]
+    if info.n_prefill_items == 0 or info.n_decode_units == 0:
+        return "decode_kernel" if info.n_prefill_items == 0 else "prefill_kernel"
+    # roles by ticket, or by workgroup index: the host model of the launch with every workgroup on one unit tells them apart
+    n = info.fused_grid
+    first = pod.pod_attn_simulate_launch(attn.plan, [0] * n, range(0, 4 * n, 4))[1].tolist()
+    by_ticket = [pod.pod_attn_role_for_ticket(t, info.prefill_ratio, info.decode_ratio) for t in range(n)]
+    return "fused_kernel" if first == by_ticket else "fused_cta_kernel"
+
+
 def oracle_check(batch, out, wl, torch):
     """A function rows -> (max-abs error of `out` on those rows against the fp64 oracle, oracle seconds)."""
     from oracle import reference
@@ -358,10 +372,9 @@ def run_config(config, batch_index, steps, warmup, want_cpu, main_mode, torch, p
         achieved, peak, unit = kv_bytes / (kernel_us * 1e-6) / 1e9, PEAK_HBM / 1e9, "GB/s"
     else:
         achieved, peak, unit = flops / (kernel_us * 1e-6) / 1e12, PEAK_MFMA_16BIT / 1e12, "TFLOP/s"
-    launched = {"fused": "fused_kernel", "fused_cta": "fused_cta_kernel"}.get(main_mode)
-    if main_mode == "fused" and info.prefill_heavy_chosen:
-        launched = KERNEL_OF_MODE["fused_heavy"]
-    traffic = MEASURED_TRAFFIC_BYTES.get((config, batch_index), {}).get(launched)
+    launched = kernels_of_fused(attn, pod) if main_mode == "fused" else KERNEL_OF_MODE[main_mode]
+    per_kernel = [MEASURED_TRAFFIC_BYTES.get((config, batch_index), {}).get(k) for k in launched.split(" + ")]
+    traffic = sum(per_kernel) if all(per_kernel) else None
     head = {
         "metric": "hybrid-batch attention us per batch (fused prefill+decode)",
         "value": value_us, "unit": "us", "n_gpus": 1, "steps": steps, "warmup": warmup,
@@ -379,7 +392,7 @@ def run_config(config, batch_index, steps, warmup, want_cpu, main_mode, torch, p
         "roofline": {"bound": bound, "achieved": achieved, "peak": peak, "unit": unit, "frac": achieved / peak,
                      "traffic": traffic,
                      "traffic_source": "rocprofv3 --pmc summaries under profiles/ (separate runs of this command), not this run",
-                     "kernel": launched or KERNEL_OF_MODE[main_mode], "kernel_us": kernel_us,
+                     "kernel": launched, "kernel_us": kernel_us,
                      "algorithmic_bytes": kv_bytes, "algorithmic_flops": flops},
         # value, the roofline percentage and the speed-ups all use the same clock: exactly `steps`
         # back-to-back forward calls (combine pass included) bracketed by synchronisation

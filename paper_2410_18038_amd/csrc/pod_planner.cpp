@@ -386,7 +386,8 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
             // Cutting costs a merge, in the units or in a kernel of its own.  With the latter it is not worth it when the
             // requests are short: us whole / cut at 160 keys 10.2 / 10.9, at 176 11.4 / 10.8, at 250 14.6 / 10.8 (64
             // channels 8.3 / 11.5, 8.4 / 11.5, 10.3 / 11.4; 256 channels at 100 keys 17.0 / 14.6, at 250 34 / 15).
-            // (Merging in the units, which came later, 112 keys would be the line: at 128 8.8 / 8.4, at 160 10.2 / 8.4.)  Nor when the prefill items beside them take longer than the
+            // (That line is the merge kernel's.  Where the units merge, 112 keys would be it, at 128 8.8 / 8.4, at 160 10.2 /
+            // 8.4; the rule does not tell the two apart.)  Nor when the prefill items beside them take longer than the
             // whole requests anyway (64 keys of an item take about 1.1 us, 16 of a unit 0.7, at 256 channels 2)
             // and need no merge themselves: items of 1128 keys beside 16 x 500 27.8 / 33.5, x 700 36 / 34;
             // of 2028 beside 16 x 700 44.6 / 50.7, 2 x 1000 50.1 / 48.1; of 128 beside 16 x 200 14.0 / 12.2; 256
@@ -659,7 +660,8 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
         // (220, 1.1) 743 / 659; 32 / 8 heads 4096 at 16K beside 32 x 32K (385, 0.95) 1181 / 1105, 8192 beside 32 x 8K (220,
         // 2.2) 620 / 580; 32 / 32 heads 2048 at 32K beside 16 x 4K (426, 3.2) 1089 / 1036.  Outside: ratio 0.54 (220)
         // 903 / 868, 0.24 (96) 579 / 692; 3.8 (385) 920 / 906, 6.6 (220) 539 / 549; 96 us of matrix time, ratio 1.9 268 /
-        // 279; an item for every second slot (210, 1.04) 737 / 735.
+        // 279; an item for every second slot (210, 1.04) 737 / 735.  (Towards long decode streams the two are level somewhere
+        // between 0.24 and 0.54; the line keeps clear of that.)
         double decode_tokens = 0.0;
         for (int r = prm.n_prefill; r < n_req; ++r) decode_tokens += seq_meta[4 * r + 2];
         const double decode_time = decode_tokens * prm.n_kv_heads * prm.head_dim * 4.0 / 8.0e12;
