@@ -231,7 +231,8 @@ KERNEL_OF_MODE = {"serial": "prefill_kernel + decode_kernel",
 
 
 def kernels_of_fused(attn, pod):
-    """Names of the attention kernels that a fused call of this plan launches (the combine kernel aside)."""
+    """Names of the attention kernels that a fused call of this plan launches (the combine kernel aside; where units merge
+    their groups, as in the tiny batch, its form for such plans: fused_cta_merging for fused_cta_kernel, and so on)."""
     info = attn.info
     if info.prefill_heavy_chosen:
         return KERNEL_OF_MODE["fused_heavy"]

@@ -906,8 +906,11 @@ __device__ __forceinline__ void merge_if_last(const KernelArgs &a, POD_LDS unsig
 // fixed units 4*seat .. 4*seat+3, one per wavefront, when seat < n_static_seats: a chip-wide
 // burst of claims at the start of a launch would be served one at a time by the memory system.
 // After that a wavefront claims units from the queue of its XCD, then from the other queues.
-// Returns the number of units the wavefront ran.
-template <int DT, int D, int LAYOUT>
+// Returns the number of units the wavefront ran.  MERGE: the plan has one unit a wavefront, and the last unit of a group
+// merges it.  Kernels of plans that do not are built without that code: jumped over, its 750 instructions still cost
+// launches of 20-25 us 0.4-0.6 us, prefill roles included (126 decodes of up to 192 keys beside three short chunks,
+// 32 / 4 heads, 20.0 / 19.4 us with / without it; 80 of them, 32 / 8 heads, 26.3 / 25.7).
+template <int DT, int D, int LAYOUT, bool MERGE>
 __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned char *smem, const int seat,
                                                  const int xcd)
 {
@@ -961,7 +964,7 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
     constexpr uint32_t kDone = 16u;                // the tail has finished the last unit
     // In the CTA-parallel launch a wavefront runs the one unit it was given: the queues count as
     // used up from the start, so no claim is ever issued and the worker ends with its unit.
-    uint32_t st = kHeadInTail | (a.single_unit ? kExhausted : 0u);
+    uint32_t st = kHeadInTail | (MERGE || a.single_unit ? kExhausted : 0u);
 
     // ---- claims ------------------------------------------------------------------------
     // The compiler keeps exact counts of the loads in flight only as long as every path through
@@ -1140,6 +1143,7 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
     // the wavefront is at is asked; the others are, where that one is used up, when the tail has finished its unit and
     // the wavefront has nothing else to do.
     auto fetch_next = [&](bool ahead) __attribute__((always_inline)) {
+        if constexpr (MERGE) return;               // (one unit a wavefront: nothing is ever claimed)
         int idx = -1;
         if (!(st & (kExhausted | kQueueEmpty))) idx = claim_here();
         if (idx < 0 && !ahead && !(st & kExhausted)) idx = claim_elsewhere();
@@ -1256,7 +1260,7 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
     int n_done = 0;
     {
         int idx0;
-        if (seat < a.n_static_seats) idx0 = __builtin_amdgcn_readfirstlane(seat) * kWavesPerWg + wave;
+        if (MERGE || seat < a.n_static_seats) idx0 = __builtin_amdgcn_readfirstlane(seat) * kWavesPerWg + wave;
         else idx0 = claim_here();
         if (idx0 < 0 || idx0 >= a.n_dunits) return 0;
         set_head(load_desc(idx0));
@@ -1327,8 +1331,7 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
             }
         }
     }
-    if constexpr (D <= kMergeDim)
-        if (a.arrived) merge_if_last<DT, D>(a, lds_k, cu.id, lane);      // (the wavefront had one unit)
+    if constexpr (MERGE) merge_if_last<DT, D>(a, lds_k, cu.id, lane);
     return n_done;
 }
 
@@ -1435,15 +1438,15 @@ __device__ __forceinline__ void finish_and_reset(const KernelArgs &a, int *flag)
     if (*flag) reset_counters(hdr);
 }
 
-template <int DT, int D, int LAYOUT>
-__global__ __launch_bounds__(kWgThreads, 2) void decode_kernel(KernelArgs a)
+template <int DT, int D, int LAYOUT, bool MERGE>
+__device__ __forceinline__ void decode_workgroup(const KernelArgs a)
 {
     __shared__ __attribute__((aligned(16))) unsigned char smem[DecodeLds<D>::kBytes];
     __shared__ int flag;
     const uint64_t t0 = a.trace ? wall_clock64() : 0;
     // every workgroup of this kernel is a decode worker; its seat is its index
     const int xcd = __builtin_amdgcn_readfirstlane((int)(__smid() >> 6));
-    const int n_done = decode_worker_run<DT, D, LAYOUT>(a, smem, blockIdx.x, xcd);
+    const int n_done = decode_worker_run<DT, D, LAYOUT, MERGE>(a, smem, blockIdx.x, xcd);
     if (a.trace) {
         __syncthreads();
         if (threadIdx.x == 0)
@@ -1451,6 +1454,10 @@ __global__ __launch_bounds__(kWgThreads, 2) void decode_kernel(KernelArgs a)
     }
     if (!a.single_unit) finish_and_reset(a, &flag);      // (nothing was counted)
 }
+template <int DT, int D, int LAYOUT>
+__global__ __launch_bounds__(kWgThreads, 2) void decode_kernel(KernelArgs a) { decode_workgroup<DT, D, LAYOUT, false>(a); }
+template <int DT, int D, int LAYOUT>
+__global__ __launch_bounds__(kWgThreads, 2) void decode_merging(KernelArgs a) { decode_workgroup<DT, D, LAYOUT, true>(a); }
 
 // ------------------------------------------------------------------------------------------
 // The prefill-heavy configuration (the second of the two occupancy configurations of
@@ -1742,8 +1749,8 @@ __global__ __launch_bounds__(kWgThreads, 2) __attribute__((amdgpu_num_vgpr(kHeav
 // one item at a time; as a decode worker each of its wavefronts takes units on its own
 // (Section 4.2.3).  No workgroup ever waits for another one.
 // ------------------------------------------------------------------------------------------
-template <int DT, int D, int LAYOUT>
-__global__ __launch_bounds__(kWgThreads, 2) void fused_kernel(KernelArgs a)
+template <int DT, int D, int LAYOUT, bool MERGE>
+__device__ __forceinline__ void fused_workgroup(const KernelArgs a)
 {
     __shared__ __attribute__((aligned(16))) unsigned char smem[FusedLds<D>::kBytes];
     __shared__ int bind[6];                                  // role, seat, unit id, last flag, item, queue
@@ -1777,10 +1784,10 @@ __global__ __launch_bounds__(kWgThreads, 2) void fused_kernel(KernelArgs a)
         n_first = prefill_worker_run<DT, D, LAYOUT>(a, smem, &bind[4], xcd);
         if (a.trace) t_switch = wall_clock64();
         const int seat = take_seat();
-        n_second = seat < a.n_dwgs ? decode_worker_run<DT, D, LAYOUT>(a, smem, seat, xcd) : 0;
+        n_second = seat < a.n_dwgs ? decode_worker_run<DT, D, LAYOUT, MERGE>(a, smem, seat, xcd) : 0;
     } else {
         const int seat = take_seat();
-        n_first = seat < a.n_dwgs ? decode_worker_run<DT, D, LAYOUT>(a, smem, seat, xcd) : 0;
+        n_first = seat < a.n_dwgs ? decode_worker_run<DT, D, LAYOUT, MERGE>(a, smem, seat, xcd) : 0;
         if (a.trace) t_switch = wall_clock64();
         n_second = prefill_worker_run<DT, D, LAYOUT>(a, smem, &bind[4], xcd);
     }
@@ -1788,6 +1795,10 @@ __global__ __launch_bounds__(kWgThreads, 2) void fused_kernel(KernelArgs a)
     if (threadIdx.x == 0 && a.trace) write_trace(a, blockIdx.x, bind[2], first, n_first, n_second, t0, t_switch);
     finish_and_reset(a, &bind[3]);
 }
+template <int DT, int D, int LAYOUT>
+__global__ __launch_bounds__(kWgThreads, 2) void fused_kernel(KernelArgs a) { fused_workgroup<DT, D, LAYOUT, false>(a); }
+template <int DT, int D, int LAYOUT>
+__global__ __launch_bounds__(kWgThreads, 2) void fused_merging(KernelArgs a) { fused_workgroup<DT, D, LAYOUT, true>(a); }
 
 // ------------------------------------------------------------------------------------------
 // CTA-parallel fused kernel: the launch of Section 4.1's listing as printed.  One workgroup per
@@ -1800,8 +1811,8 @@ __global__ __launch_bounds__(kWgThreads, 2) void fused_kernel(KernelArgs a)
 // It is also the kernel of launches whose work is all resident at once (fixed_roles): operation and piece
 // of work then follow from the workgroup index, and only decode units beyond the fixed ones are claimed.
 // ------------------------------------------------------------------------------------------
-template <int DT, int D, int LAYOUT>
-__global__ __launch_bounds__(kWgThreads, 2) void fused_cta_kernel(KernelArgs a)
+template <int DT, int D, int LAYOUT, bool MERGE>
+__device__ __forceinline__ void fused_cta_workgroup(const KernelArgs a)
 {
     __shared__ __attribute__((aligned(16))) unsigned char smem[FusedLds<D>::kBytes];
     __shared__ int bind[4];                                  // role, work id, unit id, last flag
@@ -1841,12 +1852,16 @@ __global__ __launch_bounds__(kWgThreads, 2) void fused_cta_kernel(KernelArgs a)
         if (a.evlog && threadIdx.x == 0) log_event(a, kPrefill, a.fixed_roles ? a.pitem_of_wg[id] : id, tb);
         n_done = 1;
     } else if (role == kDecode && (id < a.n_dwgs || !a.fixed_roles)) {
-        n_done = decode_worker_run<DT, D, LAYOUT>(a, smem, id, bind[2] >> 6);
+        n_done = decode_worker_run<DT, D, LAYOUT, MERGE>(a, smem, id, bind[2] >> 6);
     }
     __syncthreads();
     if (threadIdx.x == 0 && a.trace) write_trace(a, blockIdx.x, bind[2], role, n_done, 0, t0, wall_clock64());
     if (!(a.fixed_roles && a.single_unit)) finish_and_reset(a, &bind[3]);
 }
+template <int DT, int D, int LAYOUT>
+__global__ __launch_bounds__(kWgThreads, 2) void fused_cta_kernel(KernelArgs a) { fused_cta_workgroup<DT, D, LAYOUT, false>(a); }
+template <int DT, int D, int LAYOUT>
+__global__ __launch_bounds__(kWgThreads, 2) void fused_cta_merging(KernelArgs a) { fused_cta_workgroup<DT, D, LAYOUT, true>(a); }
 
 // ------------------------------------------------------------------------------------------
 // Combine: merge split-KV partials.  With running maxima m_s (log2 domain), weight sums l_s and
@@ -1952,6 +1967,26 @@ __global__ __launch_bounds__(kWgThreads) void combine_kernel(KernelArgs a)
 template <int DT, int D, int LAYOUT>
 static hipError_t launch_variant(int which, const KernelArgs &a, hipStream_t stream)
 {
+    if (a.arrived) {                               // the units merge their groups
+        if constexpr (D <= kMergeDim) {
+            switch (which) {
+            case kLaunchDecode:
+                if (a.n_dwgs > 0) decode_merging<DT, D, LAYOUT><<<dim3(a.n_dwgs), dim3(kWgThreads), 0, stream>>>(a);
+                return hipGetLastError();
+            case kLaunchFused:
+                if (a.fused_grid > 0) fused_merging<DT, D, LAYOUT><<<dim3(a.fused_grid), dim3(kWgThreads), 0, stream>>>(a);
+                return hipGetLastError();
+            case kLaunchFusedCta:
+                if (a.n_pitems + a.n_dctas > 0)
+                    fused_cta_merging<DT, D, LAYOUT><<<dim3(a.n_pitems + a.n_dctas), dim3(kWgThreads), 0, stream>>>(a);
+                return hipGetLastError();
+            default:
+                break;                             // kernels without decode units
+            }
+        } else {
+            return hipErrorInvalidValue;
+        }
+    }
     switch (which) {
     case kLaunchPrefill:
         if (a.n_pitems > 0)

@@ -832,7 +832,7 @@ def _kernels_of(call):
         call()
         torch.cuda.synchronize()
     names = ("prefill_kernel", "decode_kernel", "prefill_heavy_kernel", "decode_lite_kernel", "fused_kernel", "fused_cta_kernel",
-             "combine_kernel")
+             "decode_merging", "fused_merging", "fused_cta_merging", "combine_kernel")
     return {name for e in prof.key_averages() for name in names if "pod::" + name in e.key}
 
 
@@ -927,7 +927,7 @@ def test_units_merge_groups_with_nan_and_infinite_scores(hq, hkv, d, bs, merges)
     assert attn.info.max_decode_splits == 8 and attn.info.n_decode_units <= 4 * attn.info.n_compute_units
     out = torch.empty((batch.n_rows, hq, d), dtype=batch.torch_dtype, device="cuda:0")
     first = attn.ws_ptr - attn.workspace.data_ptr()
-    assert _kernels_of(lambda: attn.forward(dev_batch, out=out)) == {"decode_kernel"} | (set() if merges else {"combine_kernel"})
+    assert _kernels_of(lambda: attn.forward(dev_batch, out=out)) == ({"decode_merging"} if merges else {"decode_kernel", "combine_kernel"})
     for mode in ("fused", "serial", "decode_only", "fused_cta") * 2:
         out.zero_()
         attn.forward(dev_batch, out=out, mode=pod.MODES[mode])

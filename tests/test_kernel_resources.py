@@ -51,6 +51,23 @@ def test_attention_kernels_have_no_scratch_memory(tmp_path):
     assert {k: v for k, v in attention.items() if v} == {}
 
 
+@pytest.mark.skipif(not os.path.exists(READELF), reason="no llvm-readelf")
+def test_kernels_whose_units_merge_have_no_scratch_memory_either(tmp_path):
+    with open(pod.LIB_PATH, "rb") as f:
+        blob = f.read()
+    scratch = {}
+    for i, obj in enumerate(code_objects(blob)):
+        path = tmp_path / f"{i}.elf"
+        path.write_bytes(obj)
+        notes = subprocess.run([READELF, "--notes", str(path)], capture_output=True, text=True, check=True).stdout
+        for name, size in re.findall(r"\.name:\s+(\S+).*?\.private_segment_fixed_size:\s+(\d+)", notes, re.S):
+            if re.search(r"(decode|fused|fused_cta)_merging", name):
+                scratch[name] = int(size)
+    # 2 types x 2 head_dims x 3 kernels x 4 layouts
+    assert len(scratch) == 2 * 2 * 3 * 4
+    assert {k: v for k, v in scratch.items() if v} == {}
+
+
 @pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no llvm-objdump")
 def test_counter_updates_without_a_result_are_waited_for(tmp_path):
     """The last workgroup of an attention kernel clears the counters after all have counted themselves in.  An atomic
@@ -69,4 +86,5 @@ def test_counter_updates_without_a_result_are_waited_for(tmp_path):
                 n_marks += 1
                 assert lines[at + 1][:2] == ["s_waitcnt", "vmcnt(0)"], " ".join(words + ["|"] + lines[at + 1])
     # 2 types x 3 head_dims x 3 kernels (decode, fused, fused_cta) x 4 layouts, as often as the compiler copies the walk
+    # (the kernels whose units merge claim nothing)
     assert n_marks >= 2 * 3 * 3 * 4
