@@ -35,15 +35,13 @@ PEAK_HBM = 8.0e12               # bytes/s, MI355X HBM3E
 MEASURED_TRAFFIC_BYTES = {
     # (config, batch_index): {kernel: FETCH_SIZE KiB x 2.0 (copy calibration: the counter reads half of a
     # plain copy's bytes) + WRITE_SIZE KiB x 1.0, per launch}  (files under profiles/)
-    (2, 0): {"fused_kernel": 4388586189, "fused_cta_kernel": 4573902541},
-    #   fused_kernel: 2136292.1 KiB fetched, 13144.5 KiB written
-    #   fused_cta_kernel: 2226925.4 KiB fetched, 12850.9 KiB written
-    (3, 0): {"fused_kernel": 4979373978, "fused_cta_kernel": 5138292736},
-    #   fused_kernel: 2416193.4 KiB fetched, 30283.1 KiB written
-    #   fused_cta_kernel: 2493943.4 KiB fetched, 29977.2 KiB written
-    (4, 0): {"fused_kernel": 2468465459, "fused_cta_kernel": 2736429978},
-    #   fused_kernel: 1192242.0 KiB fetched, 26126.8 KiB written
-    #   fused_cta_kernel: 1323216.9 KiB fetched, 25861.1 KiB written
+    (2, 0): {"fused_kernel": 4395653302},
+    #   fused_kernel: 2139800.2 KiB fetched, 13029.8 KiB written
+    (3, 0): {"fused_cta_kernel": 4980747554},
+    #   fused_cta_kernel (roles by workgroup index): 2416967.4 KiB fetched, 30076.4 KiB written
+    (4, 0): {"prefill_heavy_kernel": 178707644, "decode_lite_kernel": 2163709976},
+    #   prefill_heavy_kernel: 76251.6 KiB fetched, 22016.0 KiB written
+    #   decode_lite_kernel: 1051158.6 KiB fetched, 10680.8 KiB written
 }
 
 
