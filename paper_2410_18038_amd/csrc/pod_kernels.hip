@@ -818,8 +818,8 @@ template <int N_OPS> __device__ __forceinline__ void wait_loads_but()
 // group have stored theirs (the combine kernel's merge, in the order of the splits, whoever comes last).  The
 // rows were written through (sc1) and are complete when the wavefront counts itself in; the loads below ask for
 // coherent data (agent scope), whichever XCD wrote it.  `lds` is the wavefront's own area.
-// A kernel launch less, us before / after: 4 heads of 64 channels, 128 tokens beside 8 decodes 13.4 / 10.6; 8 decodes of
-// 32 heads at 0.5K-4K 54.7 / 53.1; 16 decodes of 160 keys 10.9 / 8.6.  What bounds the merge is the three round
+// A kernel launch less, us before / after: 4 heads of 64 channels, 128 tokens beside 8 decodes 13.5 / 10.4; 8 decodes of
+// 32 heads at 0.5K-4K 54.9 / 53.3; 16 decodes of 160 keys cut in two 10.9 / 8.6.  What bounds the merge is the three round
 // trips of the wavefront that comes last (its stores, the counter, the partials), about 3 us; rows of all splits are fetched
 // together, which is why it stops at 8 of them: 94 splits by one wavefront would be 12 fetches.
 template <int DT, int D>
@@ -987,7 +987,7 @@ __device__ __forceinline__ int decode_worker_run(const KernelArgs &a, unsigned c
     // It waits until that has arrived: in a call without a combine kernel the counters are cleared as soon as every
     // workgroup has counted itself in, and the barrier ahead of that does not wait for a wavefront's memory operations.
     // Decode alone, us before / after, with the walk moved behind the unit's last step: 16 requests 118.0 / 115.9, 48 of
-    // 64 channels 78.0 / 74.7, 128 requests 773 / 770.  (A look at all eight counters with one load each took
+    // 64 channels 78.0 / 74.7; 128 requests (770) are level.  (A look at all eight counters with one load each took
     // longer than the walk: 622 / 643 with 8192 units, 77 / 82 with 64 channels; it slows the claims on them.)
     auto claim_elsewhere = [&]() __attribute__((always_inline)) -> int {
         const int home = (int)(__smid() >> 6) & (kXcdQueues - 1);
