@@ -670,6 +670,14 @@ pod_status build_plan(const pod_attn_params &prm, const int32_t *seq_meta, int n
         plan.heavy_pays = prm.policy == POD_POLICY_AUTO && built && prm.n_decode > 0 && n_cus == kChipUnits &&
                           (int)plan.pitems.size() >= kSlotsPerUnit * n_cus && flop_time >= 200e-6 &&
                           flop_time >= 0.8 * decode_time && flop_time <= 3.3 * decode_time;
+        // Which of the two a fused call runs depends on what other streams do, and its bits must not: the light decode kernel
+        // leaves merging to the combine kernel, which adds the weights in another order, so the units of the default
+        // configuration do as well.  (Only decode units of a given length come here: cut by the planner, streams as long as
+        // the rule asks for take several units a wavefront.  The combine kernel is 5 us of a launch of 500 and more.)
+        if (plan.heavy_pays) {
+            plan.units_merge = false;
+            plan.unit_splits.clear();
+        }
     }
 
     // ---- workspace layout --------------------------------------------------------------

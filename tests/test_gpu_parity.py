@@ -893,6 +893,28 @@ def test_fused_calls_take_two_kernels_only_where_their_stream_has_the_side_strea
     other.close()
 
 
+@pytest.mark.parametrize("decode_chunk,splits", [(8192, 6), (16384, 4)])
+def test_bits_of_a_fused_call_do_not_depend_on_which_kernels_it_may_take(decode_chunk, splits):
+    """Decode units of a given length can make one round of up to eight splits, which units merge themselves, in a plan
+    whose fused calls take the prefill-heavy configuration, whose units do not: the combine kernel then merges in both, so
+    a call gives the same bits recorded as made directly."""
+    batch = wl.make_batch("heavy-one-round", prefill=[(2048, 32768)], decode_kv_lens=[32768] * 32, n_q_heads=32, n_kv_heads=4,
+                          head_dim=128, dtype=wl.F16, seed=decode_chunk, block_size=16, device="cuda:0")
+    attn = pod.HybridAttention(batch, decode_chunk=decode_chunk)
+    info = attn.info
+    assert info.prefill_heavy_chosen == 1 and info.max_decode_splits == splits and info.n_decode_units <= 4 * info.n_compute_units
+    direct, recorded = (torch.full((batch.n_rows, batch.n_q_heads, batch.head_dim), float("nan"), dtype=batch.torch_dtype,
+                                   device="cuda:0") for _ in range(2))
+    torch.cuda.synchronize()
+    assert _kernels_of(lambda: attn.forward(batch, out=direct)) == {"prefill_heavy_kernel", "decode_lite_kernel", "combine_kernel"}
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        attn.forward(batch, out=recorded)
+    launched = _kernels_of(graph.replay)
+    assert ((recorded.view(torch.int16) != direct.view(torch.int16)).sum().item(), launched) == (0, {"fused_kernel", "combine_kernel"})
+    attn.close()
+
+
 @pytest.mark.parametrize("hq,hkv,d,bs,merges", [(4, 4, 64, 0, True), (16, 2, 64, 16, True), (8, 4, 128, 16, True), (16, 2, 128, 24, True),
                                                 (3, 1, 128, 5, True), (18, 2, 128, 16, False), (32, 2, 64, 16, False), (16, 2, 256, 16, False)])
 def test_units_merge_groups_with_nan_and_infinite_scores(hq, hkv, d, bs, merges):
