@@ -736,6 +736,7 @@ def test_fused_calls_that_take_the_prefill_heavy_configuration_keep_stream_order
     import threading
     batch = wl.config_batch(4, device="cuda:0")
     attn = pod.HybridAttention(batch)
+    assert attn.info.prefill_heavy_chosen == 1
     want = attn.forward(batch, mode=pod.MODES["serial"]).clone()
     queries = batch.prefill_q.clone(), batch.decode_q.clone()
 
@@ -792,8 +793,9 @@ def test_fused_calls_that_take_the_prefill_heavy_configuration_keep_stream_order
 @pytest.mark.parametrize("hq,hkv,d,dtype,bs", [(4, 4, 64, wl.F16, 0), (8, 4, 128, wl.BF16, 16), (16, 2, 128, wl.F16, 24),
                                                (32, 2, 64, wl.BF16, 16), (16, 2, 256, wl.BF16, 16), (3, 1, 128, wl.F16, 5)])
 def test_units_of_one_round_merge_their_groups_themselves(hq, hkv, d, dtype, bs):
-    """Plans of one round with two to eight splits per request: whichever unit of a group ends last merges it, in every
-    mode and launch after launch with the same bits; the group counters at the head of the workspace are zero after
+    """Plans of one round with two to eight splits per request: whichever unit of a group ends last merges it (up to eight
+    query heads per K/V head and 128 channels; the two shapes beyond that have the combine kernel do it), in every mode and
+    launch after launch with the same bits; the header of the workspace, group counters included, is zero after
     each call; merging switched off leaves the decode rows of split requests alone."""
     for lens, chunk, chunk_rows in [([200, 64, 510, 129, 16], 64, 0), ([700] * 3 + [65], 96, 70)]:
         batch = wl.make_batch(f"merge-{hq}/{hkv}-d{d}", prefill=[(chunk_rows, 200)] if chunk_rows else [], decode_kv_lens=lens,
@@ -813,7 +815,7 @@ def test_units_of_one_round_merge_their_groups_themselves(hq, hkv, d, dtype, bs)
                 bits = out.view(torch.int16).clone()
                 assert np.abs(out.to(torch.float64).cpu().numpy() - want).max() <= TOL[dtype]
             assert torch.equal(out.view(torch.int16), bits), (mode, i)
-            assert not attn.workspace[first:first + 70912].any()
+            assert not attn.workspace[first:first + 4 * 1024 + 20 * 128 + 4 * 512 * 32].any()
         out.fill_(float("nan"))
         attn.forward(dev_batch, out=out, mode=pod.MODE_FUSED | pod.MODE_FLAG_NO_COMBINE)
         rows = [batch.n_prefill_rows + i for i, n in enumerate(lens) if n > chunk]
